@@ -339,9 +339,13 @@ bem_status bem_panel_points(bem_ctx* ctx, int64_t L, const int32_t* panel, const
  *                line); 3 = all lines together, each stage one launch whose blocks first
  *                finish the previous stage of their lines from the partial fields the
  *                previous launch wrote, then evaluate the new stage (at most 131072 panels);
- *                2 = one persistent launch, one workgroup per line; 0 (default) = 1 while
- *                more than "trace_tail" lines are live, then 3 (1 throughout above 131072
- *                panels).  Layout 3 (and the tail of 0) runs all its remaining stages in one
+ *                2 = one persistent launch, one workgroup per line; 0 (default) = in FP64 with
+ *                the CONSTANT basis, clusters of "trace_blocks" blocks that keep their panels in
+ *                LDS (from about 27,000 panels on, read them each stage) and run all their
+ *                lines' stages in one cooperative launch, exchanging partial fields through device
+ *                memory; otherwise, or where that launch is refused or one of its waits reaches
+ *                "trace_spin" polls, 1 while more than "trace_tail" lines are live, then 3 (1
+ *                throughout above 131072 panels).  Layout 3 (and the tail of 0) runs all its remaining stages in one
  *                persistent launch once at most "trace_loop" line slots remain and their grid
  *                fits the GPU at once (cooperative launch): blocks of a line group then exchange
  *                their partial fields through device memory and wait for each other between
@@ -377,13 +381,16 @@ bem_status bem_panel_points(bem_ctx* ctx, int64_t L, const int32_t* panel, const
  *                 trace_split 0 or above the line count) results do not depend on the grouping
  *  "trace_fold":  1 (default) = with two line groups, fold the second into the first once all
  *                 live lines fit one 64-line tile; 0 = keep both groups to the end
- *  "trace_tail":  trace_mode 0: live-line count at or below which the run goes on in the
+ *  "trace_tail":  trace_mode 0 outside the cluster layout: live-line count at or below which the run goes on in the
  *                 one-launch layout (0..4096; default 16; 0 = never); checked every 32 passes
  *  "trace_loop":  one-launch layout: line-slot count at or below which the remaining stages
  *                 run in one persistent launch (0..4096; default 4; 0 = never)
- *  "trace_spin":  persistent launch: polls of one wait between its blocks before the launch
- *                 gives up and the call fails with BEM_ERR_HIP (0..2^30; default 2^22, seconds;
- *                 a safety bound, not reached in normal runs)
+ *  "trace_spin":  persistent launches: polls of one wait between their blocks before the launch
+ *                 gives up (0..2^30; default 2^22, seconds; a safety bound, not reached in normal
+ *                 runs).  The one-launch layout's call then fails with BEM_ERR_HIP; the cluster
+ *                 layout's lines run again in the other layout
+ *  "trace_blocks": cluster layout: blocks per cluster (8, 16, 32; 0, the default: the fewest
+ *                 whose LDS holds the panels; raised to 32 where a smaller count does not)
  *  "trace_lpb":   one-launch layout: line slots per block (1, 2, 4, 8; 0, the default: by the
  *                 live count)
  *  "trace_rnd":   one-launch layout: 256-panel rounds per block (1, 2, 4; 0, the default: by

@@ -914,6 +914,12 @@ bem_status bem_set_tuning(bem_ctx* c, const char* key, int64_t value) {
         c->near_rule = (int32_t)value;
         return BEM_OK;
     }
+    if (std::strcmp(key, "trace_blocks") == 0) {
+        if (value != 0 && value != 8 && value != 16 && value != 32)
+            return fail(BEM_ERR_INVALID, "trace_blocks must be 0, 8, 16 or 32");
+        c->tune_trace_blocks = (int32_t)value;
+        return BEM_OK;
+    }
     struct Knob {
         const char* name;
         int32_t bem_ctx::*field;
@@ -968,6 +974,7 @@ bem_status bem_get_tuning(const bem_ctx* c, const char* key, int64_t* value) {
     else if (std::strcmp(key, "trace_tail") == 0) *value = c->tune_trace_tail;
     else if (std::strcmp(key, "trace_loop") == 0) *value = c->tune_trace_loop;
     else if (std::strcmp(key, "trace_spin") == 0) *value = c->tune_trace_spin;
+    else if (std::strcmp(key, "trace_blocks") == 0) *value = c->tune_trace_blocks;
     else return fail(BEM_ERR_INVALID, std::string("unknown tuning key ") + key);
     return BEM_OK;
 }

@@ -159,7 +159,7 @@ struct bem_ctx {
     // scratch
     bem::DBuf gm_V, gm_w, gm_z, gm_h, gm_part, gm_x, gm_r, gm_b, gm_misc;
     bem::HBuf host_stage;
-    bem::DBuf ev_part, ev_mask, ev_ptr, ev_col, ev_row, ev_tmp, tr_queue, lb_state, lb_part, lf_part, lf_loop, lf_cnt;
+    bem::DBuf ev_part, ev_mask, ev_ptr, ev_col, ev_row, ev_tmp, tr_queue, lb_state, lb_part, lf_part, lf_loop, lf_cnt, lc_buf, lc_image;
 
     bem::DBuf bg_V, bg_W, bg_part, bg_small, bg_z, bg_B, bg_X, gemm_part, rows_part;   // batched GMRES
     bem::DBuf near_sf;   // S, F of the near list by the near-singular rule (near_rule 1)
@@ -205,6 +205,7 @@ struct bem_ctx {
     int32_t tune_trace_tail = 16;     // trace_mode 0: live lines at or below which the one-launch layout takes over
     int32_t tune_trace_loop = 4;      // one-launch layout: line slots at or below which one persistent launch runs the rest
     int32_t tune_trace_spin = 1 << 22;   // persistent launch: polls of one wait between its blocks at most
+    int32_t tune_trace_blocks = 0;    // cluster layout: blocks per cluster (8, 16, 32; 0: by the panel count)
     int32_t coop_launch = -1;         // the device takes cooperative launches (1) or not (0); -1: not asked yet
     int32_t grad_batch = 131072;      // points per batch of the gradient's pair passes (bounds scratch memory)
 
@@ -315,6 +316,11 @@ void launch_trace_nodal_cases(bem_ctx* c, int32_t nrhs, const double* sol, int64
 void launch_trace_batched(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const int32_t* line_rhs,
                           const double* starts, const bem_trace_params* tp, int32_t* n_steps, int32_t* stop_code,
                           double* path, double* integral, uint8_t* exceeds, bool fused_tail);   // trace_batched.hip
+// clusters of blocks that keep their panels in LDS for the whole run (trace_cluster.hip); false:
+// nothing done (the device or the panel count does not allow it)
+bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const int32_t* line_rhs,
+                          const double* starts, const bem_trace_params* tp, int32_t* n_steps, int32_t* stop_code,
+                          double* path, double* integral, uint8_t* exceeds);
 // one launch per RK4 stage (trace_fused.hip); fused_trace_blocks: its panel blocks of 256 rnd
 // panels, 0 when N needs more than it allows
 void launch_trace_fused(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const int32_t* line_rhs,

@@ -361,11 +361,18 @@ void launch_trace(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const 
     if (L == 0) return;
     int cus = 0;
     BEM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
-    // default: all lines advance together (measured faster than one workgroup per line for
+    // default in FP64, constant basis: clusters of blocks resident for the whole run (measured faster
+    // than the two-kernel layout with its tails from 1 to 4096 lines and 320 to 57,230 panels, ms a
+    // run: 19,732 panels 36 -> 20 with 1 line, 167 -> 107 with 256, 467 -> 440 with 4096 lines of 300
+    // steps; 1,280 panels, 16 lines 13.4 -> 4.6)
+    // otherwise: all lines advance together (measured faster than one workgroup per line for
     // 4 to 4096 lines; the per-line layout is bound by per-CU load bandwidth), a far pass and a
     // step kernel per stage while many lines are live, one launch per stage for the last few
     // (measured on the 19,732-panel coax: 47 against 64 us a stage at 256 lines, 21.4 against
     // 17.1 us at 16, 16.1 against 12.4 us at 3)
+    if (c->trace_mode == 0 && c->opt.precision == BEM_FP64 && c->opt.basis == BEM_BASIS_CONSTANT &&
+        launch_trace_cluster(c, nrhs, sol, L, line_rhs, starts, tp, n_steps, stop_code, path, integral, exceeds))
+        return;
     const int mode = c->trace_mode != 0 ? c->trace_mode : 1;
     if (mode == 1 || mode == 3) {
         if (c->opt.basis == BEM_BASIS_LINEAR && nrhs > 1 && line_rhs)

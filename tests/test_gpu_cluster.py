@@ -1,0 +1,129 @@
+"""Field lines by clusters of blocks that stay on the GPU for the whole run (trace_mode 0 in FP64,
+constant basis) against the FP64 oracle and the two-kernel layout.
+
+Cases sit at the edges of the layout: panel counts that leave blocks of a cluster with unequal
+shares or none, line counts of one, a cluster's slots (64) and past them (slots taken over by
+later lines), 8, 16 and 32 blocks per cluster, densities of several load cases in LDS and in
+memory, panels beyond LDS, and meshes on which almost every pair is near (the closed forms over
+four lanes, several rounds of them a turn).  Step counts and stop codes exact; integrals 1e-10
+relative (the workload's FP64 bar)."""
+
+import numpy as np
+import pytest
+
+import oracle
+from workloads import coax_problem, electrode_line_starts, sphere_problem
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def bem():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2003_12663_amd as bem
+    return bem
+
+
+def _density(p, nrhs, seed):
+    """Smooth positive densities (the lines only need a field), one row per load case, with the
+    unknown potentials of floating bodies after them."""
+    rng = np.random.default_rng(seed)
+    c = p.vert[p.tri].mean(axis=1)
+    k = rng.uniform(-1.0, 1.0, (nrhs, 3)) / np.abs(c).max()
+    s = 60.0 * rng.uniform(0.8, 1.2, (nrhs, 1)) * (1.0 + 0.3 * np.sin(k @ c.T))
+    return np.concatenate([s, np.zeros((nrhs, p.n_float))], axis=1)
+
+
+def _check(bem, p, L, nrhs=1, h=1e-3, max_steps=12, seed=3, want_path=False, **tuning):
+    print(f"[gpu-cluster] {p.name} N={p.n_tri} L={L} rhs={nrhs} {tuning}", flush=True)
+    x = _density(p, nrhs, seed)
+    starts, _, _ = electrode_line_starts(p, L, seed=seed)
+    owner = (np.arange(L) % nrhs).astype(np.int32)
+    ns_o, st_o, I_o = np.zeros(L, int), np.zeros(L, int), np.zeros(L)
+    o = oracle.Oracle(p)
+    for r in range(nrhs):
+        m = owner == r
+        if m.any():
+            ns_o[m], st_o[m], I_o[m] = o.trace(x[r], starts[m], oracle.trace_params(h=h, max_steps=max_steps))[:3]
+    with bem.Context.from_problem(p) as c:
+        for k, v in tuning.items():
+            c.set_tuning(k, v)
+        sol = torch.tensor(x, device="cuda")
+        tp = bem.trace_params(h=h, max_steps=max_steps)
+        lr = torch.tensor(owner, device="cuda") if nrhs > 1 else None
+        I, ns, st, _ = c.streamer_integral(sol, starts, tp, line_rhs=lr)
+        assert np.array_equal(ns.cpu().numpy(), ns_o) and np.array_equal(st.cpu().numpy(), st_o)
+        assert np.abs(I.cpu().numpy() - I_o).max() <= 1e-10 * np.abs(I_o).max()
+        again = c.streamer_integral(sol, starts, tp, line_rhs=lr)[0]
+        assert torch.equal(I, again)   # the same sums in the same order
+        if want_path:
+            ns2, st2, path = c.trace_lines(sol, starts, tp, line_rhs=lr, want_path=True)
+            assert torch.equal(ns2, ns) and torch.equal(st2, st)
+            c.set_tuning("trace_mode", 1)
+            ref = c.trace_lines(sol, starts, tp, line_rhs=lr, want_path=True)[2]
+            a, b = path.cpu().numpy(), ref.cpu().numpy()
+            assert np.array_equal(np.isnan(a), np.isnan(b))   # slots past the last point untouched
+            fin = ~np.isnan(b)
+            assert np.abs(a[fin] - b[fin]).max() <= 1e-12 * np.abs(b[fin]).max()
+    return ns_o, st_o
+
+
+@pytest.mark.parametrize("level,L", [(0, 1), (0, 70), (1, 3), (1, 64), (2, 33), (2, 700)])
+def test_few_panels(bem, level, L):
+    """20, 80 and 320 panels: blocks without a panel, and nearly every pair near."""
+    _check(bem, sphere_problem(level), L, h=2e-3, want_path=L <= 70)
+
+
+@pytest.mark.parametrize("blocks", [8, 16, 32])
+@pytest.mark.parametrize("L", [1, 9, 2100])
+def test_blocks_and_slots(bem, blocks, L):
+    """One line; an odd count; more lines than the slots of all clusters."""
+    _check(bem, sphere_problem(3), L, trace_blocks=blocks, max_steps=6)
+
+
+def test_lines_that_stop_at_different_steps(bem):
+    """Short and long lines in one cluster: the shell, the ring and the spacer stop them at
+    different steps, slots are taken over by later lines."""
+    ns, st = _check(bem, coax_problem(0.012), 700, h=0.0105, max_steps=12, trace_blocks=32, want_path=True)
+    assert len(set(st.tolist())) > 1 and ns.min() < ns.max()
+
+
+@pytest.mark.parametrize("nrhs,blocks", [(3, 0), (40, 32), (64, 32)])
+def test_load_cases(bem, nrhs, blocks):
+    """Densities of several load cases beside the panels in LDS."""
+    p = coax_problem(0.012) if nrhs == 64 else sphere_problem(3)
+    _check(bem, p, 2 * nrhs + 1, nrhs=nrhs, trace_blocks=blocks, h=1e-4 if nrhs == 64 else 1e-3, max_steps=4)
+
+
+@pytest.mark.parametrize("nrhs", [1, 2])
+def test_panels_beyond_lds(bem, nrhs):
+    """35,142 panels: the records are read from memory each turn."""
+    p = coax_problem(0.00274)
+    assert p.n_tri > 32000
+    _check(bem, p, 5, nrhs=nrhs, h=1e-4, max_steps=3)
+
+
+def test_memory_densities(bem):
+    """21,794 panels in LDS, 64 load cases' densities in memory."""
+    _check(bem, coax_problem(0.0035), 64, nrhs=64, h=1e-4, max_steps=2)
+
+
+def test_wait_bound_falls_back(bem):
+    """A bound of zero polls on the blocks' waits: the lines run in the other layout, same results."""
+    _check(bem, sphere_problem(2), 40, trace_spin=0)
+
+
+def test_line_groups_agree_with_single_lines(bem):
+    """A line's result does not depend on how many others run beside it, beyond rounding."""
+    p = sphere_problem(3)
+    x = torch.tensor(_density(p, 1, 5), device="cuda")
+    starts, _, _ = electrode_line_starts(p, 200, seed=5)
+    with bem.Context.from_problem(p) as c:
+        tp = bem.trace_params(h=1e-3, max_steps=20)
+        I, ns, st, _ = c.streamer_integral(x, starts, tp)
+        for l in (0, 63, 64, 199):
+            I1, ns1, st1, _ = c.streamer_integral(x, starts[l:l + 1], tp)
+            assert int(ns1[0]) == int(ns[l]) and int(st1[0]) == int(st[l])
+            assert abs(float(I1[0] - I[l])) <= 1e-12 * abs(float(I[l]))
