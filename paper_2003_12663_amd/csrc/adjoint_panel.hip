@@ -26,10 +26,12 @@
 
 namespace bem {
 
-void launch_reverse_sweep(bem_ctx* c, const double* sol, int64_t L, const int32_t* line_rhs, const int32_t* ns,
-                          const double* path, int64_t pstride, const bem_trace_params* tp, const double* gI,
-                          const int64_t* sbase, int32_t max_ns, double* SX, double* SE, double* x0bar);
-void launch_rows_EH(bem_ctx* c, const double* sigma, int64_t P, const double* pts, double* out);
+void launch_reverse_sweep(bem_ctx* c, int32_t nrhs, const double* sol, const std::vector<int32_t>& order,
+                          const std::vector<int64_t>& obeg, const int32_t* d_order, const std::vector<int32_t>& h_ns,
+                          const std::vector<int64_t>& h_sbase, const int32_t* ns, const double* path, int64_t pstride,
+                          const bem_trace_params* tp, const double* gI, const int64_t* sbase, double* SX, double* SE,
+                          double* x0bar);
+void launch_rows_EH(bem_ctx* c, const double* sigma, int64_t P, double* pts, double* out);
 int gmres_solve_t(bem_ctx* c, const double* b, double* x, double tol, int max_iter, int* iters, double* relres);
 
 namespace {
@@ -595,18 +597,21 @@ void streamer_grad(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const
         if (line_rhs) BEM_HIP(hipMemcpyAsync(h_rhs.data(), line_rhs, sizeof(int32_t) * L, hipMemcpyDeviceToHost, s));
         BEM_HIP(hipStreamSynchronize(s));
     }
-    std::vector<int64_t> sbase(L), rbeg(nrhs + 1, 0);
-    int32_t max_ns = 0;
+    std::vector<int64_t> sbase(L), rbeg(nrhs + 1, 0), obeg(nrhs + 1, 0);
+    std::vector<int32_t> order;   // lines by load case; their records follow one another in this order
     {
+        for (int64_t l = 0; l < L; ++l) ++obeg[h_rhs[l] + 1];
+        for (int32_t r = 0; r < nrhs; ++r) obeg[r + 1] += obeg[r];
+        order.resize(L);
+        std::vector<int64_t> fill(obeg.begin(), obeg.end() - 1);
+        for (int64_t l = 0; l < L; ++l) order[fill[h_rhs[l]]++] = (int32_t)l;
         int64_t off = 0;
         for (int32_t r = 0; r < nrhs; ++r) {
             rbeg[r] = off;
-            for (int64_t l = 0; l < L; ++l)
-                if (h_rhs[l] == r) {
-                    sbase[l] = off;
-                    off += 4 * (int64_t)h_ns[l];
-                    max_ns = std::max(max_ns, h_ns[l]);
-                }
+            for (int64_t o = obeg[r]; o < obeg[r + 1]; ++o) {
+                sbase[order[o]] = off;
+                off += 4 * (int64_t)h_ns[order[o]];
+            }
         }
         rbeg[nrhs] = off;
     }
@@ -620,7 +625,10 @@ void streamer_grad(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const
     if (L > 0) {
         BEM_HIP(hipMemcpyAsync(d_sbase, sbase.data(), sizeof(int64_t) * L, hipMemcpyHostToDevice, s));
         // 3. reverse sweep
-        launch_reverse_sweep(c, sol, L, line_rhs, ns, path, pstride, tp, gI, d_sbase, max_ns, SX, SE, x0bar);
+        c->ad_order.alloc(sizeof(int32_t) * (size_t)L);
+        BEM_HIP(hipMemcpyAsync(c->ad_order.p, order.data(), sizeof(int32_t) * L, hipMemcpyHostToDevice, s));
+        launch_reverse_sweep(c, nrhs, sol, order, obeg, c->ad_order.as<int32_t>(), h_ns, sbase, ns, path, pstride, tp,
+                             gI, d_sbase, SX, SE, x0bar);
     }
     // 4. per-panel adjoint buffers
     const size_t accs = (size_t)N * PA_ACC;

@@ -166,7 +166,7 @@ struct bem_ctx {
     bem::HMatrix* hm = nullptr;   // compressed operator in use (bem_compress), else the dense matrix
 
     // gradient of the streamer integrals
-    bem::DBuf ad_state, ad_part, ad_mask, ad_cnt, ad_self, ad_ppart, ad_list, ad_path, ad_stage, ad_geo, ad_seg,
+    bem::DBuf ad_state, ad_part, ad_rec, ad_order, ad_mask, ad_cnt, ad_self, ad_ppart, ad_list, ad_path, ad_stage, ad_geo, ad_seg,
         ad_vptr, ad_vcorner;
 
     // kernel-side launch timing (profiling mode 2): KCLK_SUB word pairs per launch slot, the
@@ -269,6 +269,8 @@ void launch_quad_pair_integrals(bem_ctx* c, int64_t P, const double* pts, const 
                                 double* F);
 // the Sec. 4 rule for the assembly's near list into sf[4 k .. 4 k + 3] (duffy.hip)
 void launch_near_duffy(bem_ctx* c, int64_t nnz, const int32_t* row, const int32_t* col, double* sf);
+// records of the 7-point rule about the centroid with the densities sol (or none), in B groups (geometry.hip)
+void launch_median_records(bem_ctx* c, const double* sol, DBuf& out, int B = 1, int64_t P = 0);
 void launch_panel_points(bem_ctx* c, int64_t L, const int32_t* panel, const double* bary, double offset,
                          double* out);                                // geometry.hip
 void launch_far_assemble(bem_ctx* c);                              // assemble.hip

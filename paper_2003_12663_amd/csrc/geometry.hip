@@ -3,6 +3,7 @@
 // the Sec. 4 pair classification) and the nodes and scaled weights of the
 // degree-5, 7-point triangle rule used for regular pairs.
 #include "bem_device.h"
+#include "median_device.h"
 
 namespace bem {
 namespace {
@@ -122,7 +123,50 @@ __global__ __launch_bounds__(256) void k_panel_points(int64_t L, const int32_t* 
         out[3 * l + k] = b0 * T[TR_V + k] + b1 * T[TR_V + 3 + k] + b2 * T[TR_V + 6 + k] + offset * T[TR_N + k];
 }
 
+// Records of the 7-point rule about the centroid (median_device.h), with the densities sol (nullptr:
+// none), in B groups of at most P: record [k][i] is panel j = i B + k.  One lane per panel.
+__global__ __launch_bounds__(256) void k_median_records(int64_t N, int64_t Np, int64_t P, int B,
+                                                  const double* __restrict__ tri64, const double* __restrict__ far64,
+                                                  const double* __restrict__ sol, double* __restrict__ image) {
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (j >= N) return;
+    const double* T = tri64 + (int64_t)TRI_REC * j;
+    double* r = image + ((j % B) * P + j / B) * MED_REC;
+    double m[3][3];
+#pragma unroll
+    for (int v = 0; v < 3; ++v)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) m[v][c] = MED_SC * (T[TR_V + 3 * v + c] - T[TR_C + c]);
+    double cc[3], off = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        r[c] = T[TR_C + c];
+        r[3 + c] = m[0][c];
+        r[6 + c] = m[1][c];
+        cc[c] = far64[(int64_t)(FR_CC + c) * Np + j];
+        r[MD_CC + c] = cc[c];
+        const double d = cc[c] - T[TR_C + c];
+        off += d * d;
+    }
+#pragma unroll
+    for (int v = 0; v < 3; ++v) r[9 + v] = m[v][0] * m[v][0] + m[v][1] * m[v][1] + m[v][2] * m[v][2];
+    const double rr = far64[(int64_t)FR_RR * Np + j];
+    r[MD_DENS] = sol ? sol[j] * (MED_W1 * INV4PI * T[TR_A]) : 0.0;
+    const double reach = (sqrt(rr) + sqrt(off)) * (1.0 + 1e-6);   // far above the rounding of either distance
+    r[MD_REACH] = reach * reach;
+    r[MD_RR] = rr;
+}
+
 }  // namespace
+
+void launch_median_records(bem_ctx* c, const double* sol, DBuf& out, int B, int64_t P) {
+    const int64_t N = c->N, Np = (int64_t)(c->far64.bytes / (sizeof(double) * FAR_REC));
+    if (P == 0) P = ceil_div(N, B);
+    out.alloc(sizeof(double) * MED_REC * (size_t)(B * P));
+    hipLaunchKernelGGL(k_median_records, dim3((unsigned)ceil_div(N, 256)), dim3(256), 0, c->stream, N, Np, P, B,
+                       c->tri64.as<double>(), c->far64.as<double>(), sol, out.as<double>());
+    BEM_CHECK_LAUNCH();
+}
 
 void launch_panel_points(bem_ctx* c, int64_t L, const int32_t* panel, const double* bary, double offset,
                          double* out) {

@@ -26,13 +26,8 @@
 // bound the block raises err and leaves, and so, at their own bounds, do the blocks that wait for
 // it.  The grid must be resident at once (cooperative launch).
 //
-// The 7-point rule is taken about the panel's centroid c.  Its nodes are c and c + m_i, c + rho m_i
-// on the three medians (m_i = s (v_i - c), s = 1 - 3 a_1, rho = (1 - 3 a_2) / s, m_0 + m_1 + m_2 =
-// 0), so with t = x - c, T = |t|^2 and p_i = t . m_i the squared node distances are T, T - 2 p_i +
-// |m_i|^2 and T - 2 rho p_i + rho^2 |m_i|^2: two operations a node instead of six, and the field is
-// t sum g - sum_i m_i (g_1i + rho w_2 / w_1 g_2i) w_1 with g = r^-3 (and w_0 / w_1, w_2 / w_1 in
-// the sum).  On a regular pair |t| is at least 5 circumradii, so nothing cancels.  A pair takes 104
-// FP64 instructions (7 of them v_rsq_f64) where the node-by-node form takes 129, and 14 values of
+// Regular pairs take the 7-point rule about the panel's centroid (median_device.h): 104 FP64
+// instructions a pair (7 of them v_rsq_f64) where the node-by-node form takes 129, and 14 values of
 // its record where that one reads 32.
 //
 // What bounds a turn (19,732 panels): the FP64 instructions of the regular pairs while many lines
@@ -48,6 +43,7 @@
 #include <climits>
 
 #include "bem_device.h"
+#include "median_device.h"
 #include "trace_device.h"
 
 #include <hip/hip_ext.h>
@@ -58,10 +54,8 @@ namespace {
 constexpr int LC_PW = 8;             // waves of a block that read records
 constexpr int LC_S = 64;             // line slots of a cluster
 constexpr int LC_XCD_CUS = 32;       // CUs of an XCD
-// Doubles per panel: [0] c, [3] m_0, [6] m_1, [9] |m_i|^2, [12] density x w_1 area / 4 pi, [13] squared
-// reach, [14] circumcentre, [17] (eta R)^2.  A stride of 36 banks: lanes on consecutive panels do
-// not collide in LDS.
-constexpr int LC_REC = 18;
+// Doubles per panel: a stride of 36 banks, so lanes on consecutive panels do not collide in LDS.
+constexpr int LC_REC = MED_REC;
 constexpr int LC_Q = 192;            // near pairs a wave holds back (at most 64 + two rounds of 64)
 constexpr int LC_NONE = 255;         // end of a thread's chain of held pairs
 constexpr int LC_WORDS = 4;          // record words of a line: field (3) and hit parameter (the hit panel in
@@ -138,31 +132,6 @@ __device__ __forceinline__ double quad_d(double v) {
 }
 constexpr int QUAD_1 = 0xB1, QUAD_2 = 0x4E;   // quad_perm [1,0,3,2] and [2,3,0,1]: lane ^ 1, lane ^ 2
 
-// Constants of the median form, held in registers (none is an inline FP64 constant; left as
-// literals they are rebuilt at every use).
-struct LCConst {
-    double m2rho, rho2, kap, kap0, kaprho, c15, c1875;
-};
-constexpr double LC_S15 = 3.8729833462074168852;   // sqrt(15)
-constexpr double LC_A1 = (6.0 - LC_S15) / 21.0, LC_A2 = (6.0 + LC_S15) / 21.0;
-constexpr double LC_W1 = (155.0 - LC_S15) / 1200.0, LC_W2 = (155.0 + LC_S15) / 1200.0;
-constexpr double LC_SC = 1.0 - 3.0 * LC_A1;                    // medians' scale
-constexpr double LC_RHO = (1.0 - 3.0 * LC_A2) / LC_SC;
-__device__ __forceinline__ LCConst lc_consts() {
-    LCConst k{-2.0 * LC_RHO, LC_RHO * LC_RHO, LC_W2 / LC_W1, 0.225 / LC_W1, LC_W2 / LC_W1 * LC_RHO, 1.5, 1.875};
-    asm volatile("" : "+s"(k.m2rho), "+s"(k.rho2), "+s"(k.kap), "+s"(k.kap0), "+s"(k.kaprho), "+v"(k.c15),
-                 "+s"(k.c1875));
-    return k;
-}
-// r^-3 from r^2 (lb_w_r3 without the weight)
-__device__ __forceinline__ double lc_r3(double r2, const LCConst& k) {
-    const double y = __builtin_amdgcn_rsq(r2);
-    const double y2 = y * y;
-    const double e = __fma_rn(-r2, y2, 1.0);
-    const double y3 = y2 * y;
-    return __fma_rn(y3 * e, __fma_rn(e, k.c1875, k.c15), y3);
-}
-
 // What a regular pair needs first: t = x - c and |t|^2.
 struct LCPoint {
     double t0, t1, t2, T;
@@ -175,20 +144,20 @@ __device__ __forceinline__ LCPoint lc_point(const double (&v)[14], double p0, do
 // One regular pair: the field of the panel with record v at the point, times its density, added
 // to a.  A lane whose pair is not regular (or that has none) takes a density of 0 at a distance
 // that keeps every term finite, so that the pairs of a wave run without a branch.
-__device__ __forceinline__ void lc_pair(const double (&v)[14], const LCPoint& p, bool on, const LCConst& kc,
+__device__ __forceinline__ void lc_pair(const double (&v)[14], const LCPoint& p, bool on, const MedConst& kc,
                                         double& a0, double& a1, double& a2) {
     const double T = on ? p.T : 1.0e60;
     const double sg = on ? v[12] : 0.0;
     const double pa = __fma_rn(p.t0, v[3], __fma_rn(p.t1, v[4], p.t2 * v[5]));
     const double pb = __fma_rn(p.t0, v[6], __fma_rn(p.t1, v[7], p.t2 * v[8]));
     const double pc = -(pa + pb);
-    const double g10 = lc_r3(__fma_rn(-2.0, pa, T + v[9]), kc);
-    const double g11 = lc_r3(__fma_rn(-2.0, pb, T + v[10]), kc);
-    const double g12 = lc_r3(__fma_rn(-2.0, pc, T + v[11]), kc);
-    const double g20 = lc_r3(__fma_rn(kc.m2rho, pa, __fma_rn(kc.rho2, v[9], T)), kc);
-    const double g21 = lc_r3(__fma_rn(kc.m2rho, pb, __fma_rn(kc.rho2, v[10], T)), kc);
-    const double g22 = lc_r3(__fma_rn(kc.m2rho, pc, __fma_rn(kc.rho2, v[11], T)), kc);
-    const double g0 = lc_r3(T, kc);
+    const double g10 = med_r3(__fma_rn(-2.0, pa, T + v[9]), kc);
+    const double g11 = med_r3(__fma_rn(-2.0, pb, T + v[10]), kc);
+    const double g12 = med_r3(__fma_rn(-2.0, pc, T + v[11]), kc);
+    const double g20 = med_r3(__fma_rn(kc.m2rho, pa, __fma_rn(kc.rho2, v[9], T)), kc);
+    const double g21 = med_r3(__fma_rn(kc.m2rho, pb, __fma_rn(kc.rho2, v[10], T)), kc);
+    const double g22 = med_r3(__fma_rn(kc.m2rho, pc, __fma_rn(kc.rho2, v[11], T)), kc);
+    const double g0 = med_r3(T, kc);
     const double G = __fma_rn(kc.kap0, g0, __fma_rn(kc.kap, (g20 + g21) + g22, (g10 + g11) + g12));
     const double h0 = __fma_rn(kc.kaprho, g20, g10), h1 = __fma_rn(kc.kaprho, g21, g11);
     const double h2 = __fma_rn(kc.kaprho, g22, g12);
@@ -332,7 +301,7 @@ __global__ __launch_bounds__(64 * W) void k_lc_trace(LCArgs P) {
         s_rec_hit = 0;
     }
     __syncthreads();
-    const LCConst kc = lc_consts();
+    const MedConst kc = med_consts();
     unsigned long long pairs = 0, nears = 0;   // this block's (thread 0)
     int nl1 = 0, nl2 = 0;   // live counts of the previous two turns
     const int64_t rstride = (int64_t)LC_S * LC_WORDS;   // one block's records of a turn
@@ -727,46 +696,12 @@ __global__ void k_lc_count(const unsigned long long* __restrict__ counts, unsign
     if (threadIdx.x < 2) total[threadIdx.x] += counts[threadIdx.x];
 }
 
-// The panel records of one call, grouped by the block that holds them: record [k][i] is panel
-// j = i B + k.  One lane per panel; sol nullptr: no density (several load cases, k_lc_density).
-__global__ __launch_bounds__(256) void k_lc_image(int64_t N, int64_t Np, int64_t P, int B,
-                                                  const double* __restrict__ tri64, const double* __restrict__ far64,
-                                                  const double* __restrict__ sol, double* __restrict__ image) {
-    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (j >= N) return;
-    const double* T = tri64 + (int64_t)TRI_REC * j;
-    double* r = image + ((j % B) * P + j / B) * LC_REC;
-    double m[3][3];
-#pragma unroll
-    for (int v = 0; v < 3; ++v)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) m[v][c] = LC_SC * (T[TR_V + 3 * v + c] - T[TR_C + c]);
-    double cc[3], off = 0.0;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        r[c] = T[TR_C + c];
-        r[3 + c] = m[0][c];
-        r[6 + c] = m[1][c];
-        cc[c] = far64[(int64_t)(FR_CC + c) * Np + j];
-        r[14 + c] = cc[c];
-        const double d = cc[c] - T[TR_C + c];
-        off += d * d;
-    }
-#pragma unroll
-    for (int v = 0; v < 3; ++v) r[9 + v] = m[v][0] * m[v][0] + m[v][1] * m[v][1] + m[v][2] * m[v][2];
-    const double rr = far64[(int64_t)FR_RR * Np + j];
-    r[12] = sol ? sol[j] * (LC_W1 * INV4PI * T[TR_A]) : 0.0;
-    const double reach = (sqrt(rr) + sqrt(off)) * (1.0 + 1e-6);   // far above the rounding of either distance
-    r[13] = reach * reach;
-    r[17] = rr;
-}
-
 __global__ __launch_bounds__(256) void k_lc_density(int64_t N, int64_t P, int B, const double* __restrict__ tri64,
                                                     const double* __restrict__ sol, int64_t n,
                                                     double* __restrict__ sw) {
     const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x, rhs = blockIdx.y;
     if (j >= N) return;
-    sw[(rhs * B + j % B) * P + j / B] = sol[rhs * n + j] * (LC_W1 * INV4PI * tri64[(int64_t)TRI_REC * j + TR_A]);
+    sw[(rhs * B + j % B) * P + j / B] = sol[rhs * n + j] * (MED_W1 * INV4PI * tri64[(int64_t)TRI_REC * j + TR_A]);
 }
 
 // 8 and 16 blocks a cluster only with everything in LDS (launch_trace_cluster)
@@ -796,7 +731,7 @@ bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L
     int cus = 0;
     BEM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
     if (c->coop_launch == 0 || cus < LC_XCD_CUS) return false;
-    const int64_t N = c->N, Np = (int64_t)(c->far64.bytes / (sizeof(double) * FAR_REC));
+    const int64_t N = c->N;
     if (!line_rhs) nrhs = 1;   // every line takes the first load case
     // blocks per cluster: as few as hold the panels (and the load cases' densities) in LDS.  Fewer
     // blocks exchange faster and leave more clusters to share the lines (us a turn, 1,280 panels,
@@ -842,9 +777,7 @@ bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L
     hipLaunchKernelGGL(k_lc_fill, dim3(256), dim3(256), 0, c->stream, words,
                        reinterpret_cast<unsigned long long*>(A.buf), A.counts, A.err);
     BEM_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_lc_image, dim3((unsigned)ceil_div(N, 256)), dim3(256), 0, c->stream, N, Np, P, B,
-                       c->tri64.as<double>(), c->far64.as<double>(), nrhs > 1 ? nullptr : sol, c->lc_image.as<double>());
-    BEM_CHECK_LAUNCH();
+    launch_median_records(c, nrhs > 1 ? nullptr : sol, c->lc_image, B, P);
     if (nrhs > 1) {
         hipLaunchKernelGGL(k_lc_density, dim3((unsigned)ceil_div(N, 256), (unsigned)nrhs), dim3(256), 0, c->stream, N,
                            P, B, c->tri64.as<double>(), sol, c->n, const_cast<double*>(A.sw));

@@ -362,3 +362,17 @@ def test_gradient_c5_coax_against_central_differences():
     print(f"[grad] C5 coax: |grad| {scale:.3e}, FD error {worst:.2e} (relative to |grad|), "
           f"{skipped} draws skipped", flush=True)
     assert worst <= 1e-5
+
+
+@pytest.mark.parametrize("batch", [64, 100, 1024])
+def test_stage_fields_in_batches(bem, oracle_mod, batch):
+    """The stage points of all steps go in batches of grad_batch points and groups of 8 grad_batch
+    steps: batches that end inside a line, groups of one and of several lines, and a last ragged
+    one give the gradient of one batch (sums in another order: 1e-11 of the largest entry)."""
+    p = floating_shell_problem(2, V0=80.0)
+    kw = dict(L=23, steps=37, h=5e-3, nrhs=2)
+    a = _case(bem, oracle_mod, p, **kw)
+    b = _case(bem, oracle_mod, p, batch=batch, **kw)
+    assert a["ns"].min() < a["ns"].max() or a["ns"].min() > 0
+    for k in ("dvert", "dV", "dstart"):
+        assert np.abs(a[k] - b[k]).max() <= 1e-11 * np.abs(a[k]).max(), k
