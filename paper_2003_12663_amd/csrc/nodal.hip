@@ -16,8 +16,8 @@
 // in LDS and leave as 128-byte row segments (64 bytes when the rows are stored
 // in FP32, MIXED precision).  This pass takes the regular
 // pairs only; the near-singular and singular ones (a small fraction, each a
-// long closed form) follow in a second pass with one lane per row, which adds
-// all three hats of a near triangle into its own row, so the first pass keeps
+// long closed form) follow in a second pass with one wave per row, which adds
+// all three hats of the near triangles into its row, so the first pass keeps
 // few registers and many waves in flight.
 #include <cmath>
 
@@ -264,62 +264,110 @@ __global__ __launch_bounds__(256) void k_nodal_chunk_bounds(int64_t N, int64_t N
     cb[4 * ch + 3] = r;
 }
 
-__device__ __forceinline__ double lane_bcast(double v, int k) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, k), hi = __builtin_amdgcn_readlane((int)(b >> 32), k);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
+constexpr int NN_H = 256;   // slots of a wave's column table (192 columns at most: 64 triangles a round)
 
-// Near-singular and singular pairs of the vertex rows (one lane per row, 64 rows
-// per block, the rows taken in a spatial (Morton) order of the vertices so that
-// a block's rows are neighbours).  Chunks of 64 triangles whose bound is beyond
-// reach of the rows' ball are skipped; in the others every triangle is classified with the
-// predicate of the first pass, its circumcentre, (eta R)^2 and vertex indices
-// loaded by the lanes together (component-major records) and broadcast from a
-// lane register.  A near triangle adds its three hats into the lane's own row.
-template <class T>
-__global__ __launch_bounds__(64) void k_nodal_near(int64_t nv, int64_t ld, int64_t N, int64_t Np,
+// Near-singular and singular pairs of one row, by one wave: the vertex rows (KP false: x the vertex
+// i, hats by hat_edges) or the centroid rows below (KP true: x the centroid of triangle trow[i] with
+// its normal, the hats' normal field).
+// The lanes test 64 chunk bounds at a time; of the chunks within reach they classify the 64 triangles
+// with the predicate of the regular pass, and the near ones queue up, ascending.  A round takes 64 of
+// them, one closed form per lane.  Their hats meet in the row's entries, up to six triangles an entry:
+// the round's distinct columns go into a table in LDS, and each column's lane adds its hats in the
+// triangles' order, rounding to the stored type after each, as one lane walking the triangles would
+// (so FP32 rows hold the same bits).  One lane per row, the earlier form, ran each closed form for a
+// few lanes at a time and had 141 waves for 9,036 rows: 4.0 ms, where this takes 0.2.
+template <class T, bool KP>
+__global__ __launch_bounds__(64) void k_nodal_near(int64_t nr, int64_t ld, int64_t N, int64_t Np,
                                                    const int32_t* __restrict__ row_order,
-                                                   const double* __restrict__ vert, const int32_t* __restrict__ tri,
-                                                   const double* __restrict__ far64, const double* __restrict__ cb,
-                                                   const double* __restrict__ tri64, T* __restrict__ A) {
+                                                   const double* __restrict__ vert, const int32_t* __restrict__ trow,
+                                                   const int32_t* __restrict__ tri, const double* __restrict__ far64,
+                                                   const double* __restrict__ cb, const double* __restrict__ tri64,
+                                                   T* __restrict__ A) {
+    __shared__ int32_t lt[128];            // near triangles waiting, ascending
+    __shared__ int32_t hkey[NN_H], used[192], s_used;
+    __shared__ double hval[NN_H];
+    __shared__ uint32_t eslot[64];         // slots of a triangle's three columns, 8 bits each
+    __shared__ double ev[3][64];
     const int lane = threadIdx.x;
-    const int64_t s = (int64_t)blockIdx.x * 64 + lane;
-    const bool live = s < nv;
-    const int64_t ic = row_order[live ? s : nv - 1];
-    const int64_t i = live ? ic : -1;   // -1 matches no vertex
-    const double x0 = vert[3 * ic], x1 = vert[3 * ic + 1], x2 = vert[3 * ic + 2];
-    T* row = A + ic * ld;
-    // ball of the 64 rows
-    const double g0 = wave_sum(x0) / 64.0, g1 = wave_sum(x1) / 64.0, g2 = wave_sum(x2) / 64.0;
-    double rg = sqrt((x0 - g0) * (x0 - g0) + (x1 - g1) * (x1 - g1) + (x2 - g2) * (x2 - g2));
+    // blocks go to the 8 XCDs in turn: XCD x takes a contiguous part of the rows' spatial order, so
+    // that neighbours' triangle records share its L2
+    const int64_t per = (nr + 7) / 8, sx = (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if ((int64_t)(blockIdx.x >> 3) >= per || sx >= nr) return;
+    const int64_t i = KP ? sx : row_order[sx];
+    const int64_t own = KP ? trow[i] : -1;
+    const double* Tx = tri64 + (int64_t)TRI_REC * (KP ? own : 0);
+    const double x0 = KP ? Tx[TR_C] : vert[3 * i], x1 = KP ? Tx[TR_C + 1] : vert[3 * i + 1],
+                 x2 = KP ? Tx[TR_C + 2] : vert[3 * i + 2];
+    T* row = A + i * ld;
+    const int64_t nch = (N + 63) >> 6;
+    int m = 0;             // triangles waiting
+    int64_t cbase = -64, t0 = 0;
+    uint64_t todo = 0;     // chunks of [cbase, cbase + 64) within reach, not yet classified
+    for (;;) {
+        while (m < 64) {
+            while (todo == 0 && cbase + 64 < nch) {
+                cbase += 64;
+                const int64_t ch = cbase + lane;
+                bool in = false;
+                if (ch < nch) {
+                    const double* Bd = cb + 4 * ch;
+                    const double e0 = Bd[0] - x0, e1 = Bd[1] - x1, e2 = Bd[2] - x2;
+                    const double reach = Bd[3] * (1.0 + 1e-9) + 1e-300;
+                    in = !(e0 * e0 + e1 * e1 + e2 * e2 > reach * reach);
+                }
+                todo = __ballot(in);
+            }
+            if (todo == 0) break;
+            t0 = (cbase + __builtin_ctzll(todo)) * 64;
+            todo &= todo - 1;
+            const int64_t t = t0 + lane;
+            bool near = false;
+            if (t < N) {
+                near = !is_regular(x0 - far64[(int64_t)(FR_CC + 0) * Np + t], x1 - far64[(int64_t)(FR_CC + 1) * Np + t],
+                                   x2 - far64[(int64_t)(FR_CC + 2) * Np + t], far64[(int64_t)FR_RR * Np + t]);
+                if (KP)
+                    near = near && t != own;
+                else
+                    near = near || tri[3 * t] == i || tri[3 * t + 1] == i || tri[3 * t + 2] == i;
+            }
+            const uint64_t nm = __ballot(near);
+            if (near)
+                lt[m + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(nm >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)nm, 0u))] = (int32_t)t;
+            m += __popcll(nm);
+        }
+        if (m == 0) break;
+        const int n = m < 64 ? m : 64;
+        __syncthreads();
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const double other = __shfl_xor(rg, o, 64);
-        rg = other > rg ? other : rg;
-    }
-    for (int64_t t0 = 0; t0 < N; t0 += 64) {
-        const double* B = cb + 4 * (t0 >> 6);
-        const double e0 = B[0] - g0, e1 = B[1] - g1, e2 = B[2] - g2;
-        const double reach = (rg + B[3]) * (1.0 + 1e-9) + 1e-300;
-        if (e0 * e0 + e1 * e1 + e2 * e2 > reach * reach) continue;   // every pair regular
-        const int64_t tl = t0 + lane < N ? t0 + lane : N - 1;
-        const double c0 = far64[(int64_t)(FR_CC + 0) * Np + tl], c1 = far64[(int64_t)(FR_CC + 1) * Np + tl];
-        const double c2 = far64[(int64_t)(FR_CC + 2) * Np + tl], rr = far64[(int64_t)FR_RR * Np + tl];
-        const int32_t v0 = tri[3 * tl], v1 = tri[3 * tl + 1], v2 = tri[3 * tl + 2];
-        const int kend = N - t0 < 64 ? (int)(N - t0) : 64;
-        for (int k = 0; k < kend; ++k) {
-            const double cc0 = lane_bcast(c0, k), cc1 = lane_bcast(c1, k), cc2 = lane_bcast(c2, k);
-            const double crr = lane_bcast(rr, k);
-            const int32_t a = __builtin_amdgcn_readlane(v0, k), b = __builtin_amdgcn_readlane(v1, k);
-            const int32_t c = __builtin_amdgcn_readlane(v2, k);
-            bool vtx = (a == i) || (b == i) || (c == i);
-            const bool near = vtx || !is_regular(x0 - cc0, x1 - cc1, x2 - cc2, crr);
-            if (near && live) {
-                // the three entries are read first so that their latency overlaps the closed form;
-                // the sum is formed in FP64 and rounded once to the stored type
-                const double ya = (double)row[a], yb = (double)row[b], yc = (double)row[c];
-                const double* Tr = tri64 + (int64_t)TRI_REC * (t0 + k);
+        for (int k = 0; k < NN_H / 64; ++k) hkey[lane + 64 * k] = -1;
+        if (lane == 0) s_used = 0;
+        __syncthreads();
+        if (lane < n) {
+            const int64_t t = lt[lane];
+            const double* Tr = tri64 + (int64_t)TRI_REC * t;
+            uint32_t slots = 0;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const int32_t col = tri[3 * t + c];
+                uint32_t h = ((uint32_t)col * 2654435761u) >> 24;
+                for (;;) {   // fewer columns than slots: a free or equal one is found
+                    const int32_t k = atomicCAS(&hkey[h], -1, col);
+                    if (k == -1) {
+                        hval[h] = (double)row[col];
+                        used[atomicAdd(&s_used, 1)] = (int32_t)h;
+                    }
+                    if (k == -1 || k == col) break;
+                    h = (h + 1) & (NN_H - 1);
+                }
+                slots |= h << (8 * c);
+            }
+            eslot[lane] = slots;
+            double out[3] = {0.0, 0.0, 0.0};
+            if constexpr (KP) {
+                nodal_tri_hats_nE(Tr, x0, x1, x2, Tx[TR_N], Tx[TR_N + 1], Tx[TR_N + 2], out);
+            } else {
+                bool vtx = tri[3 * t] == i || tri[3 * t + 1] == i || tri[3 * t + 2] == i;
                 // a vertex of another body at x (bodies that touch): the singular closed form at
                 // that vertex's own position
                 double xs0 = x0, xs1 = x1, xs2 = x2;
@@ -334,11 +382,30 @@ __global__ __launch_bounds__(64) void k_nodal_near(int64_t nv, int64_t ld, int64
                 }
                 double I0, r0, r1, r2, J0, J1, J2;
                 hat_edges(Tr, xs0, xs1, xs2, vtx, I0, r0, r1, r2, J0, J1, J2);
-                row[a] = (T)(ya + hat_value(Tr, 0, I0, r0, r1, r2, J0, J1, J2));
-                row[b] = (T)(yb + hat_value(Tr, 1, I0, r0, r1, r2, J0, J1, J2));
-                row[c] = (T)(yc + hat_value(Tr, 2, I0, r0, r1, r2, J0, J1, J2));
+#pragma unroll
+                for (int c = 0; c < 3; ++c) out[c] = hat_value(Tr, c, I0, r0, r1, r2, J0, J1, J2);
             }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) ev[c][lane] = out[c];
         }
+        __syncthreads();
+        for (int u = lane; u < s_used; u += 64) {
+            const uint32_t h = (uint32_t)used[u];
+            double y = hval[h];
+            for (int e = 0; e < n; ++e) {
+                const uint32_t w = eslot[e];
+                if ((w & 0xffu) == h) y = (double)(T)(y + ev[0][e]);
+                else if (((w >> 8) & 0xffu) == h) y = (double)(T)(y + ev[1][e]);
+                else if (((w >> 16) & 0xffu) == h) y = (double)(T)(y + ev[2][e]);
+            }
+            row[hkey[h]] = (T)y;
+        }
+        const int left = m - n;
+        const int32_t mv = lt[64 + lane];
+        __syncthreads();   // and the row's entries are there for the next round's columns
+        if (lane < left) lt[lane] = mv;
+        __syncthreads();
+        m = left;
     }
 }
 
@@ -413,57 +480,6 @@ __global__ __launch_bounds__(256) void k_nodal_kp_assemble(int64_t nc, int64_t n
         const int rr = (lane >> 4) + 4 * sgm, cc = lane & 15;
         const int64_t ii = r0 + rr, jj = j0 + cc;
         if (ii < nc && jj < nv) Kc[ii * ld + jj] = tile[wv][cc][rr];
-    }
-}
-
-// Near pairs of the centroid rows (one lane per row, chunks of 64 triangles beyond reach of the
-// rows' ball skipped, as k_nodal_near): the closed form of the three hats' normal field.
-__global__ __launch_bounds__(64) void k_nodal_kp_near(int64_t nc, int64_t ld, int64_t N, int64_t Np,
-                                                      const int32_t* __restrict__ trow,
-                                                      const int32_t* __restrict__ tri,
-                                                      const double* __restrict__ far64, const double* __restrict__ cb,
-                                                      const double* __restrict__ tri64, double* __restrict__ Kc) {
-    const int lane = threadIdx.x;
-    const int64_t r = (int64_t)blockIdx.x * 64 + lane;
-    const bool live = r < nc;
-    const int64_t rc = live ? r : nc - 1;
-    const int64_t T = trow[rc];
-    const double* Tx = tri64 + (int64_t)TRI_REC * T;
-    const double x0 = Tx[TR_C], x1 = Tx[TR_C + 1], x2 = Tx[TR_C + 2];
-    const double m0 = Tx[TR_N], m1 = Tx[TR_N + 1], m2 = Tx[TR_N + 2];
-    double* row = Kc + rc * ld;
-    const double g0 = wave_sum(x0) / 64.0, g1 = wave_sum(x1) / 64.0, g2 = wave_sum(x2) / 64.0;
-    double rg = sqrt((x0 - g0) * (x0 - g0) + (x1 - g1) * (x1 - g1) + (x2 - g2) * (x2 - g2));
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const double other = __shfl_xor(rg, o, 64);
-        rg = other > rg ? other : rg;
-    }
-    for (int64_t t0 = 0; t0 < N; t0 += 64) {
-        const double* B = cb + 4 * (t0 >> 6);
-        const double e0 = B[0] - g0, e1 = B[1] - g1, e2 = B[2] - g2;
-        const double reach = (rg + B[3]) * (1.0 + 1e-9) + 1e-300;
-        if (e0 * e0 + e1 * e1 + e2 * e2 > reach * reach) continue;   // every pair regular
-        const int64_t tl = t0 + lane < N ? t0 + lane : N - 1;
-        const double c0 = far64[(int64_t)(FR_CC + 0) * Np + tl], c1 = far64[(int64_t)(FR_CC + 1) * Np + tl];
-        const double c2 = far64[(int64_t)(FR_CC + 2) * Np + tl], rr = far64[(int64_t)FR_RR * Np + tl];
-        const int32_t v0 = tri[3 * tl], v1 = tri[3 * tl + 1], v2 = tri[3 * tl + 2];
-        const int kend = N - t0 < 64 ? (int)(N - t0) : 64;
-        for (int k = 0; k < kend; ++k) {
-            const double cc0 = lane_bcast(c0, k), cc1 = lane_bcast(c1, k), cc2 = lane_bcast(c2, k);
-            const double crr = lane_bcast(rr, k);
-            const int32_t a = __builtin_amdgcn_readlane(v0, k), b = __builtin_amdgcn_readlane(v1, k);
-            const int32_t c = __builtin_amdgcn_readlane(v2, k);
-            const bool near = (t0 + k != T) && !is_regular(x0 - cc0, x1 - cc1, x2 - cc2, crr);
-            if (near && live) {
-                const double ya = row[a], yb = row[b], yc = row[c];
-                double out[3] = {0.0, 0.0, 0.0};
-                nodal_tri_hats_nE(tri64 + (int64_t)TRI_REC * (t0 + k), x0, x1, x2, m0, m1, m2, out);
-                row[a] = ya + out[0];
-                row[b] = yb + out[1];
-                row[c] = yc + out[2];
-            }
-        }
     }
 }
 
@@ -728,9 +744,9 @@ static void nodal_assemble_t(bem_ctx* c, T* A, double* Atail, int64_t tail_row0)
     hipLaunchKernelGGL(k_nodal_chunk_bounds, dim3((unsigned)ceil_div(nch, 256)), dim3(256), 0, s, c->N, Np,
                        c->far64.as<double>(), c->nodal_bounds.as<double>());
     BEM_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_nodal_near<T>, dim3((unsigned)ceil_div(nv, 64)), dim3(64), 0, s, nv, ld, c->N, Np,
-                       c->row_order.as<int32_t>(), c->vert.as<double>(), c->tri.as<int32_t>(), c->far64.as<double>(),
-                       c->nodal_bounds.as<double>(), c->tri64.as<double>(), A);
+    hipLaunchKernelGGL((k_nodal_near<T, false>), dim3((unsigned)(ceil_div(nv, 8) * 8)), dim3(64), 0, s, nv, ld, c->N, Np,
+                       c->row_order.as<int32_t>(), c->vert.as<double>(), (const int32_t*)nullptr, c->tri.as<int32_t>(),
+                       c->far64.as<double>(), c->nodal_bounds.as<double>(), c->tri64.as<double>(), A);
     BEM_CHECK_LAUNCH();
     const int64_t nc = (int64_t)c->h_crow_tri.size(), niv = (int64_t)c->h_iface_v.size();
     const bool need_mass = c->n_float > 0 || niv > 0;
@@ -751,9 +767,10 @@ static void nodal_assemble_t(bem_ctx* c, T* A, double* Atail, int64_t tail_row0)
                            c->nod_trow.as<int32_t>(), c->grp_ptr.as<int32_t>(), c->grp_tri.as<int32_t>(),
                            c->grp_loc.as<uint32_t>(), c->pan64.as<double>(), c->tri64.as<double>(), Kc);
         BEM_CHECK_LAUNCH();
-        hipLaunchKernelGGL(k_nodal_kp_near, dim3((unsigned)ceil_div(nc, 64)), dim3(64), 0, s, nc, ld, c->N, Np,
-                           c->nod_trow.as<int32_t>(), c->tri.as<int32_t>(), c->far64.as<double>(),
-                           c->nodal_bounds.as<double>(), c->tri64.as<double>(), Kc);
+        hipLaunchKernelGGL((k_nodal_near<double, true>), dim3((unsigned)(ceil_div(nc, 8) * 8)), dim3(64), 0, s, nc, ld,
+                           c->N, Np, (const int32_t*)nullptr, (const double*)nullptr, c->nod_trow.as<int32_t>(),
+                           c->tri.as<int32_t>(), c->far64.as<double>(), c->nodal_bounds.as<double>(),
+                           c->tri64.as<double>(), Kc);
         BEM_CHECK_LAUNCH();
         if (niv > 0) {
             hipLaunchKernelGGL(k_nodal_iface_rows<T>, dim3((unsigned)niv), dim3(256), 0, s, nv, ld,
