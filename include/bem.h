@@ -339,8 +339,8 @@ bem_status bem_panel_points(bem_ctx* ctx, int64_t L, const int32_t* panel, const
  *                line); 3 = all lines together, each stage one launch whose blocks first
  *                finish the previous stage of their lines from the partial fields the
  *                previous launch wrote, then evaluate the new stage (at most 131072 panels);
- *                2 = one persistent launch, one workgroup per line; 0 (default) = in FP64 with
- *                the CONSTANT basis, clusters of "trace_blocks" blocks that keep their panels in
+ *                2 = one persistent launch, one workgroup per line; 0 (default) = in FP64 (and
+ *                with the LINEAR basis in either precision) clusters of "trace_blocks" blocks that keep their panels in
  *                LDS (from about 27,000 panels on, read them each stage) and run all their
  *                lines' stages in one cooperative launch, exchanging partial fields through device
  *                memory; otherwise, or where that launch is refused or one of its waits reaches

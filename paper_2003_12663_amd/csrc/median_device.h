@@ -24,13 +24,13 @@ constexpr double MED_RHO = (1.0 - 3.0 * MED_A2) / MED_SC;
 // weights over w_1: kap0 of the centroid, kap of the second orbit; and the rule's other constants,
 // held in registers (none is an inline FP64 constant; left as literals they are rebuilt at every use)
 struct MedConst {
-    double m2rho, rho2, kap, kap0, kaprho, kaprho2, c15, c1875;
+    double m2rho, rho2, kap, kap0, kaprho, kaprho2, c15, c1875, rho;
 };
 __device__ __forceinline__ MedConst med_consts() {
     MedConst k{-2.0 * MED_RHO,           MED_RHO * MED_RHO,  MED_W2 / MED_W1, 0.225 / MED_W1, MED_W2 / MED_W1 * MED_RHO,
-               MED_W2 / MED_W1 * MED_RHO * MED_RHO, 1.5, 1.875};
+               MED_W2 / MED_W1 * MED_RHO * MED_RHO, 1.5, 1.875, MED_RHO};
     asm volatile("" : "+s"(k.m2rho), "+s"(k.rho2), "+s"(k.kap), "+s"(k.kap0), "+s"(k.kaprho), "+s"(k.kaprho2),
-                 "+v"(k.c15), "+s"(k.c1875));
+                 "+v"(k.c15), "+s"(k.c1875), "+s"(k.rho));
     return k;
 }
 

@@ -361,7 +361,7 @@ void launch_trace(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const 
     if (L == 0) return;
     int cus = 0;
     BEM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
-    // default in FP64, constant basis: clusters of blocks resident for the whole run (measured faster
+    // default where the far field is FP64 (FP64 contexts, and the nodal basis in either precision): clusters of blocks resident for the whole run (measured faster
     // than the two-kernel layout with its tails from 1 to 4096 lines and 320 to 57,230 panels, ms a
     // run: 19,732 panels 36 -> 20 with 1 line, 167 -> 107 with 256, 467 -> 440 with 4096 lines of 300
     // steps; 1,280 panels, 16 lines 13.4 -> 4.6)
@@ -370,7 +370,7 @@ void launch_trace(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const 
     // step kernel per stage while many lines are live, one launch per stage for the last few
     // (measured on the 19,732-panel coax: 47 against 64 us a stage at 256 lines, 21.4 against
     // 17.1 us at 16, 16.1 against 12.4 us at 3)
-    if (c->trace_mode == 0 && c->opt.precision == BEM_FP64 && c->opt.basis == BEM_BASIS_CONSTANT &&
+    if (c->trace_mode == 0 && (c->opt.precision == BEM_FP64 || c->opt.basis == BEM_BASIS_LINEAR) &&
         launch_trace_cluster(c, nrhs, sol, L, line_rhs, starts, tp, n_steps, stop_code, path, integral, exceeds))
         return;
     const int mode = c->trace_mode != 0 ? c->trace_mode : 1;

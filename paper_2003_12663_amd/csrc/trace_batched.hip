@@ -1092,7 +1092,10 @@ void launch_trace_nodal_cases(bem_ctx* c, int32_t nrhs, const double* sol, int64
         hipLaunchKernelGGL(k_gather_starts, dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, c->stream, m, didx, starts,
                            tst);
         BEM_CHECK_LAUNCH();
-        if (trace_fused_layout(c))
+        if (c->trace_mode == 0 &&
+            launch_trace_cluster(c, 1, sol + (int64_t)r * c->n, m, nullptr, tst, tp, tns, tsc, path ? tpath : nullptr,
+                                 integral ? tI : nullptr, exceeds ? tex : nullptr)) {
+        } else if (trace_fused_layout(c))
             launch_trace_fused(c, 1, sol + (int64_t)r * c->n, m, nullptr, tst, tp, tns, tsc, path ? tpath : nullptr,
                                integral ? tI : nullptr, exceeds ? tex : nullptr);
         else

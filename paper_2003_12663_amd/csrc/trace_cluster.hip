@@ -44,6 +44,7 @@
 
 #include "bem_device.h"
 #include "median_device.h"
+#include "nodal_device.h"
 #include "trace_device.h"
 
 #include <hip/hip_ext.h>
@@ -69,7 +70,9 @@ __device__ __forceinline__ bool lc_is_sent(double v) {
 
 struct LCArgs {
     const double* image;   // [B][P][LC_REC] panel records, panel j = i B + k at [k][i]
-    const double* sw;      // densities x w_1 area / 4 pi of several load cases, [rhs][B][P]; or nullptr
+    const double* sw;      // densities x w_1 area / 4 pi of several load cases, [rhs][B][P]; or, nodal
+                           // basis, the nodal density's three values a panel (k_lc_nodal); or nullptr
+    const int32_t* ntri;   // nodal basis: vertices of each triangle
     int64_t N, P;          // panels, panels per block at most
     const double* tri64;
     const int32_t* tri_body;
@@ -136,7 +139,8 @@ constexpr int QUAD_1 = 0xB1, QUAD_2 = 0x4E;   // quad_perm [1,0,3,2] and [2,3,0,
 struct LCPoint {
     double t0, t1, t2, T;
 };
-__device__ __forceinline__ LCPoint lc_point(const double (&v)[14], double p0, double p1, double p2) {
+template <int M>
+__device__ __forceinline__ LCPoint lc_point(const double (&v)[M], double p0, double p1, double p2) {
     LCPoint p{p0 - v[0], p1 - v[1], p2 - v[2], 0.0};
     p.T = __fma_rn(p.t0, p.t0, __fma_rn(p.t1, p.t1, p.t2 * p.t2));
     return p;
@@ -165,6 +169,32 @@ __device__ __forceinline__ void lc_pair(const double (&v)[14], const LCPoint& p,
     a0 = __fma_rn(sG, p.t0, __fma_rn(s0, v[3], __fma_rn(s1, v[6], a0)));
     a1 = __fma_rn(sG, p.t1, __fma_rn(s0, v[4], __fma_rn(s1, v[7], a1)));
     a2 = __fma_rn(sG, p.t2, __fma_rn(s0, v[5], __fma_rn(s1, v[8], a2)));
+}
+
+// The same for a nodal density: at the nodes c, c + m_i, c + rho m_i it is n0, n0 + d_i, n0 + rho d_i
+// (times w_1 area / 4 pi), with n0 its mean over the corners, d_i = s (u_i - mean), d_2 = -d_0 - d_1.
+__device__ __forceinline__ void lc_pair_nodal(const double (&v)[16], const LCPoint& p, bool on, const MedConst& kc,
+                                              double& a0, double& a1, double& a2) {
+    const double T = on ? p.T : 1.0e60;
+    const double n0 = on ? v[12] : 0.0, d0 = on ? v[14] : 0.0, d1 = on ? v[15] : 0.0;
+    const double d2 = -(d0 + d1);
+    const double pa = __fma_rn(p.t0, v[3], __fma_rn(p.t1, v[4], p.t2 * v[5]));
+    const double pb = __fma_rn(p.t0, v[6], __fma_rn(p.t1, v[7], p.t2 * v[8]));
+    const double pc = -(pa + pb);
+    const double g10 = (n0 + d0) * med_r3(__fma_rn(-2.0, pa, T + v[9]), kc);
+    const double g11 = (n0 + d1) * med_r3(__fma_rn(-2.0, pb, T + v[10]), kc);
+    const double g12 = (n0 + d2) * med_r3(__fma_rn(-2.0, pc, T + v[11]), kc);
+    const double g20 = __fma_rn(kc.rho, d0, n0) * med_r3(__fma_rn(kc.m2rho, pa, __fma_rn(kc.rho2, v[9], T)), kc);
+    const double g21 = __fma_rn(kc.rho, d1, n0) * med_r3(__fma_rn(kc.m2rho, pb, __fma_rn(kc.rho2, v[10], T)), kc);
+    const double g22 = __fma_rn(kc.rho, d2, n0) * med_r3(__fma_rn(kc.m2rho, pc, __fma_rn(kc.rho2, v[11], T)), kc);
+    const double g0 = n0 * med_r3(T, kc);
+    const double G = __fma_rn(kc.kap0, g0, __fma_rn(kc.kap, (g20 + g21) + g22, (g10 + g11) + g12));
+    const double h0 = __fma_rn(kc.kaprho, g20, g10), h1 = __fma_rn(kc.kaprho, g21, g11);
+    const double h2 = __fma_rn(kc.kaprho, g22, g12);
+    const double s0 = h2 - h0, s1 = h2 - h1;
+    a0 = __fma_rn(G, p.t0, __fma_rn(s0, v[3], __fma_rn(s1, v[6], a0)));
+    a1 = __fma_rn(G, p.t1, __fma_rn(s0, v[4], __fma_rn(s1, v[7], a1)));
+    a2 = __fma_rn(G, p.t2, __fma_rn(s0, v[5], __fma_rn(s1, v[8], a2)));
 }
 
 // Field of unit density on the flat triangle T at x by the closed form of flat_tri_SF, over four
@@ -223,9 +253,20 @@ __device__ __noinline__ LCVec3 lc_tri_F(const double* __restrict__ T, int e4, do
     return LCVec3{(F0 + sg * n0) * INV4PI, (F1 + sg * n1) * INV4PI, (F2 + sg * n2) * INV4PI};
 }
 
+// Field of the linear density with corner values u on the flat triangle T, one lane a pair (a call:
+// see lc_tri_F)
+__device__ __noinline__ LCVec3 lc_nodal_E(const double* __restrict__ T, double x0, double x1, double x2, double u0,
+                                          double u1, double u2) {
+    LCVec3 E{0.0, 0.0, 0.0};
+    double ph = 0.0;
+    nodal_tri_phiE(T, x0, x1, x2, u0, u1, u2, ph, E.x, E.y, E.z);
+    return E;
+}
+
 // W: waves of a block; B: blocks of a cluster; RES: the block's panels in LDS (else read from the image each turn);
-// SW: densities from the records (0), of several load cases from LDS (1) or from memory (2)
-template <int W, int B, bool RES, int SW>
+// SW: densities from the records (0), of several load cases from LDS (1) or from memory (2);
+// NODAL: the density is the nodal one (its three values a panel where SW 1, 2 read load cases')
+template <int W, int B, bool RES, int SW, bool NODAL>
 __global__ __launch_bounds__(64 * W) void k_lc_trace(LCArgs P) {
     constexpr int LC_W = W, LC_T = 64 * W;
     constexpr int LC_NE = LC_T / 4;   // near pairs evaluated at a time, four lanes each
@@ -341,12 +382,23 @@ __global__ __launch_bounds__(64 * W) void k_lc_trace(LCArgs P) {
             int qn = 0, mine = LC_NONE;   // pairs held by the wave; the last one held for this thread
             const double* recs = RES ? lrec : img;
             // what every pair reads of a record: centroid, medians, their squares, density, reach
-            auto fetch = [&](int i, double (&v)[14]) {
+            constexpr int NV = NODAL ? 16 : 14;
+            auto fetch = [&](int i, double (&v)[NV]) {
                 const double* r = recs + i * LC_REC;
 #pragma unroll
                 for (int c = 0; c < 12; ++c) v[c] = r[c];
                 v[12] = SW == 0 ? r[12] : (SW == 1 ? lsw[lo + i] : gsw[i]);
                 v[13] = r[13];
+                if constexpr (NODAL) {
+                    v[14] = SW == 1 ? lsw[P.P + i] : gsw[B * P.P + i];
+                    v[15] = SW == 1 ? lsw[2 * P.P + i] : gsw[2 * B * P.P + i];
+                }
+            };
+            auto pair = [&](const double (&v)[NV], const LCPoint& p, bool on, double& x, double& y, double& z) {
+                if constexpr (NODAL)
+                    lc_pair_nodal(v, p, on, kc, x, y, z);
+                else
+                    lc_pair(v, p, on, kc, x, y, z);
             };
             // regular or not (Sec. 4): |t|^2 above the record's reach settles it (the circumcentre's
             // distance is then certainly above eta R); below, the test itself.  A pair that is not
@@ -375,22 +427,22 @@ __global__ __launch_bounds__(64 * W) void k_lc_trace(LCArgs P) {
                 const int iA = base + pi, iB = iA + PB;
                 base += 2 * PB;
                 const bool okB = has && iB < Pk;
-                double vA[14], vB[14];
+                double vA[NV], vB[NV];
                 fetch(has ? iA : 0, vA);
                 fetch(okB ? iB : 0, vB);
                 const LCPoint pA = lc_point(vA, p0, p1, p2), pB = lc_point(vB, p0, p1, p2);
                 const bool onA = test(has, iA, pA, vA[13]), onB = test(okB, iB, pB, vB[13]);
-                lc_pair(vA, pA, onA, kc, a0, a1, a2);
-                lc_pair(vB, pB, onB, kc, b0, b1, b2);
+                pair(vA, pA, onA, a0, a1, a2);
+                pair(vB, pB, onB, b0, b1, b2);
             }
             if (base + PB >= Pk && base < Pk && qn <= LC_Q - 128) {   // a last single round
                 const int iA = base + pi;
                 base += PB;
                 const bool okA = has && iA < Pk;
-                double vA[14];
+                double vA[NV];
                 fetch(okA ? iA : 0, vA);
                 const LCPoint pA = lc_point(vA, p0, p1, p2);
-                lc_pair(vA, pA, test(okA, iA, pA, vA[13]), kc, a0, a1, a2);
+                pair(vA, pA, test(okA, iA, pA, vA[13]), a0, a1, a2);
             }
             if (lane == 0) {
                 nqc[wv] = qn;
@@ -424,13 +476,23 @@ __global__ __launch_bounds__(64 * W) void k_lc_trace(LCArgs P) {
                     ej = (int)(en & 0xffffu) * B + k;
                     const int es = slot_of[eli];
                     const double* Tj = P.tri64 + (int64_t)TRI_REC * ej;
-                    const double sg = P.sol[(int64_t)srhs[es] * P.n + ej];
                     const double y0 = sy[0][es], y1 = sy[1][es], y2 = sy[2][es];
-                    const LCVec3 f = lc_tri_F(Tj, tid & 3, y0, y1, y2);
-                    if ((tid & 3) == 0) {
-                        nres[0][tid >> 2] = sg * f.x;
-                        nres[1][tid >> 2] = sg * f.y;
-                        nres[2][tid >> 2] = sg * f.z;
+                    if constexpr (NODAL) {
+                        if ((tid & 3) == 0) {
+                            const int32_t* tv = P.ntri + 3 * (int64_t)ej;
+                            const LCVec3 f = lc_nodal_E(Tj, y0, y1, y2, P.sol[tv[0]], P.sol[tv[1]], P.sol[tv[2]]);
+                            nres[0][tid >> 2] = f.x;
+                            nres[1][tid >> 2] = f.y;
+                            nres[2][tid >> 2] = f.z;
+                        }
+                    } else {
+                        const double sg = P.sol[(int64_t)srhs[es] * P.n + ej];
+                        const LCVec3 f = lc_tri_F(Tj, tid & 3, y0, y1, y2);
+                        if ((tid & 3) == 0) {
+                            nres[0][tid >> 2] = sg * f.x;
+                            nres[1][tid >> 2] = sg * f.y;
+                            nres[2][tid >> 2] = sg * f.z;
+                        }
                     }
                     if (sphase[es] == 4 && (tid & 3) == 0) {
                         const double x0 = sx[0][es], x1 = sx[1][es], x2 = sx[2][es];
@@ -704,18 +766,36 @@ __global__ __launch_bounds__(256) void k_lc_density(int64_t N, int64_t P, int B,
     sw[(rhs * B + j % B) * P + j / B] = sol[rhs * n + j] * (MED_W1 * INV4PI * tri64[(int64_t)TRI_REC * j + TR_A]);
 }
 
+// The nodal density's values of each panel, times w_1 area / 4 pi: its mean, and s (u_i - mean) of
+// corners 0 and 1, as three "load cases" of k_lc_density's layout.
+__global__ __launch_bounds__(256) void k_lc_nodal(int64_t N, int64_t P, int B, const double* __restrict__ tri64,
+                                                  const int32_t* __restrict__ tri, const double* __restrict__ u,
+                                                  double* __restrict__ sw) {
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (j >= N) return;
+    const double w = MED_W1 * INV4PI * tri64[(int64_t)TRI_REC * j + TR_A];
+    const double u0 = u[tri[3 * j]], u1 = u[tri[3 * j + 1]], u2 = u[tri[3 * j + 2]];
+    const double mean = (u0 + u1 + u2) / 3.0;
+    double* o = sw + (j % B) * P + j / B;
+    o[0] = w * mean;
+    o[B * P] = w * (MED_SC * (u0 - mean));
+    o[2 * B * P] = w * (MED_SC * (u1 - mean));
+}
+
 // 8 and 16 blocks a cluster only with everything in LDS (launch_trace_cluster)
-template <int W>
+template <int W, bool ND>
 const void* lc_kernel_of(int B, bool res, int sw) {
-#define BEM_LC(BB, RES, SW) reinterpret_cast<const void*>(&k_lc_trace<W, BB, RES, SW>)
-    if (B == 8) return sw == 0 ? BEM_LC(8, true, 0) : BEM_LC(8, true, 1);
-    if (B == 16) return sw == 0 ? BEM_LC(16, true, 0) : BEM_LC(16, true, 1);
-    if (res) return sw == 0 ? BEM_LC(32, true, 0) : (sw == 1 ? BEM_LC(32, true, 1) : BEM_LC(32, true, 2));
-    return sw == 0 ? BEM_LC(32, false, 0) : BEM_LC(32, false, 2);
+#define BEM_LC(BB, RES, SW) reinterpret_cast<const void*>(&k_lc_trace<W, BB, RES, SW, ND>)
+    if constexpr (!ND) {
+        if (sw == 0) return B == 8 ? BEM_LC(8, true, 0) : (B == 16 ? BEM_LC(16, true, 0) : (res ? BEM_LC(32, true, 0) : BEM_LC(32, false, 0)));
+    }
+    if (sw == 1) return B == 8 ? BEM_LC(8, true, 1) : (B == 16 ? BEM_LC(16, true, 1) : BEM_LC(32, true, 1));
+    return res ? BEM_LC(32, true, 2) : BEM_LC(32, false, 2);
 #undef BEM_LC
 }
-const void* lc_kernel(int W, int B, bool res, int sw) {
-    return W == 8 ? lc_kernel_of<8>(B, res, sw) : lc_kernel_of<12>(B, res, sw);
+const void* lc_kernel(int W, int B, bool res, int sw, bool nodal) {
+    if (nodal) return lc_kernel_of<8, true>(B, res, sw);
+    return W == 8 ? lc_kernel_of<8, false>(B, res, sw) : lc_kernel_of<12, false>(B, res, sw);
 }
 
 }  // namespace
@@ -733,32 +813,39 @@ bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L
     if (c->coop_launch == 0 || cus < LC_XCD_CUS) return false;
     const int64_t N = c->N;
     if (!line_rhs) nrhs = 1;   // every line takes the first load case
+    // nodal basis (one load case; FP64 in either precision): three density values a panel
+    const bool nodal = c->opt.basis == BEM_BASIS_LINEAR;
+    if (nodal && nrhs > 1) return false;
+    const int nd = nodal ? 3 : nrhs;
     // blocks per cluster: as few as hold the panels (and the load cases' densities) in LDS.  Fewer
     // blocks exchange faster and leave more clusters to share the lines (us a turn, 1,280 panels,
     // 16 lines: 6.4 with 8 blocks, 7.7 with 32; 7,712 panels, 16 load cases x 64 lines: 187 ms a
     // run with 16, which hold the densities too, 204 with 8, 208 with 32).  Where 32 do not hold
     // them the densities, then the records, are read from memory each turn.
-    auto lds_room = [](int waves) {   // LDS of a CU less what the kernel itself takes
+    auto lds_room = [nodal](int waves) {   // LDS of a CU less what the kernel itself takes
         hipFuncAttributes fa;
-        BEM_HIP(hipFuncGetAttributes(&fa, lc_kernel(waves, 32, true, 0)));
+        BEM_HIP(hipFuncGetAttributes(&fa, lc_kernel(waves, 32, true, nodal ? 1 : 0, nodal)));
         return (size_t)160 * 1024 - fa.sharedSizeBytes - 16;
     };
     const size_t room = lds_room(8);
-    const size_t per_panel = sizeof(double) * LC_REC, per_dens = nrhs > 1 ? sizeof(double) * (size_t)nrhs : 0;
+    const size_t per_panel = sizeof(double) * LC_REC, per_dens = nd > 1 ? sizeof(double) * (size_t)nd : 0;
     int B = c->tune_trace_blocks > 0 ? c->tune_trace_blocks : 8;
     while (B < 32 && (per_panel + per_dens) * (size_t)ceil_div(N, B) > room) B *= 2;
     const int NC = cus / LC_XCD_CUS * (LC_XCD_CUS / B);
     const int64_t P = ceil_div(N, B);
     if (P > 65535) return false;   // a held pair carries its panel's index in 16 bits
     const bool res = per_panel * (size_t)P <= room;
-    const int sw = nrhs == 1 ? 0 : (res && (per_panel + per_dens) * (size_t)P <= room ? 1 : 2);
+    // nodal panels beyond LDS: their records and densities from memory each turn lose to the two-kernel
+    // layout where the pairs take the time (54,882 panels, 256 lines of 200 steps: 69.7 against 62.2 ms)
+    if (nodal && !res && L > (int64_t)NC * 8) return false;
+    const int sw = nd == 1 ? 0 : (res && (per_panel + per_dens) * (size_t)P <= room ? 1 : 2);
     const size_t dyn = res ? (per_panel + (sw == 1 ? per_dens : 0)) * (size_t)P : 0;
     // waves per block: 8 are the faster exchange and step (1 line, 19,732 panels: equal; 8 lines,
     // 2,192 panels: 19.0 against 20.8 ms a run), 12 fill the SIMDs better where the pairs take the
     // time (19,732 panels, 256 lines: 52.0 against 53.7 ms, 1024 lines: 181 against 192) and LDS has
     // room for their own arrays too
-    const int W = L > (int64_t)NC * 8 && dyn <= lds_room(12) ? 12 : 8;
-    const void* f = lc_kernel(W, B, res, sw);
+    const int W = !nodal && L > (int64_t)NC * 8 && dyn <= lds_room(12) ? 12 : 8;
+    const void* f = lc_kernel(W, B, res, sw, nodal);
     if (dyn > 0) BEM_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn));
     int per_cu = 0;
     BEM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, 64 * W, dyn));
@@ -768,17 +855,21 @@ bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L
     LCArgs A;
     const int64_t words = 3 * (int64_t)NC * LC_S * LC_WORDS * B;
     c->lc_buf.alloc(sizeof(double) * (size_t)(words + 8));
-    c->lc_image.alloc(sizeof(double) * (size_t)(B * P) * (LC_REC + (nrhs > 1 ? nrhs : 0)));
+    c->lc_image.alloc(sizeof(double) * (size_t)(B * P) * (LC_REC + (nd > 1 ? nd : 0)));
     A.image = c->lc_image.as<double>();
-    A.sw = nrhs > 1 ? c->lc_image.as<double>() + (size_t)(B * P) * LC_REC : nullptr;
+    A.sw = nd > 1 ? c->lc_image.as<double>() + (size_t)(B * P) * LC_REC : nullptr;
     A.buf = c->lc_buf.as<double>();
     A.counts = reinterpret_cast<unsigned long long*>(A.buf + words);
     A.err = reinterpret_cast<int32_t*>(A.counts + 2);
     hipLaunchKernelGGL(k_lc_fill, dim3(256), dim3(256), 0, c->stream, words,
                        reinterpret_cast<unsigned long long*>(A.buf), A.counts, A.err);
     BEM_CHECK_LAUNCH();
-    launch_median_records(c, nrhs > 1 ? nullptr : sol, c->lc_image, B, P);
-    if (nrhs > 1) {
+    launch_median_records(c, nd > 1 ? nullptr : sol, c->lc_image, B, P);
+    if (nodal) {
+        hipLaunchKernelGGL(k_lc_nodal, dim3((unsigned)ceil_div(N, 256)), dim3(256), 0, c->stream, N, P, B,
+                           c->tri64.as<double>(), c->tri.as<int32_t>(), sol, const_cast<double*>(A.sw));
+        BEM_CHECK_LAUNCH();
+    } else if (nrhs > 1) {
         hipLaunchKernelGGL(k_lc_density, dim3((unsigned)ceil_div(N, 256), (unsigned)nrhs), dim3(256), 0, c->stream, N,
                            P, B, c->tri64.as<double>(), sol, c->n, const_cast<double*>(A.sw));
         BEM_CHECK_LAUNCH();
@@ -794,7 +885,8 @@ bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L
     A.starts = starts;
     A.L = L;
     A.NC = NC;
-    A.nrhs = nrhs;
+    A.nrhs = nd;
+    A.ntri = c->tri.as<int32_t>();
     A.a.h = tp->h;
     A.a.e_min = tp->e_min;
     A.a.dir = tp->direction >= 0 ? 1.0 : -1.0;

@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 
 import oracle
-from workloads import coax_problem, electrode_line_starts, sphere_problem
+from workloads import coax_conductors_problem, coax_problem, electrode_line_starts, sphere_problem
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -34,6 +34,13 @@ def _density(p, nrhs, seed):
     k = rng.uniform(-1.0, 1.0, (nrhs, 3)) / np.abs(c).max()
     s = 60.0 * rng.uniform(0.8, 1.2, (nrhs, 1)) * (1.0 + 0.3 * np.sin(k @ c.T))
     return np.concatenate([s, np.zeros((nrhs, p.n_float))], axis=1)
+
+
+def _nodal_density(p, seed):
+    """A smooth positive nodal density and the potentials after it."""
+    rng = np.random.default_rng(seed)
+    k = rng.uniform(-1.0, 1.0, 3) / np.abs(p.vert).max()
+    return np.concatenate([60.0 * (1.0 + 0.3 * np.sin(p.vert @ k)), np.zeros(p.n_float)])
 
 
 def _check(bem, p, L, nrhs=1, h=1e-3, max_steps=12, seed=3, want_path=False, **tuning):
@@ -127,3 +134,34 @@ def test_line_groups_agree_with_single_lines(bem):
             I1, ns1, st1, _ = c.streamer_integral(x, starts[l:l + 1], tp)
             assert int(ns1[0]) == int(ns[l]) and int(st1[0]) == int(st[l])
             assert abs(float(I1[0] - I[l])) <= 1e-12 * abs(float(I[l]))
+
+
+@pytest.mark.parametrize("level,L,blocks", [(0, 5, 0), (1, 70, 16), (2, 1, 32), (3, 300, 0)])
+def test_nodal_density(bem, level, L, blocks):
+    """The nodal basis: three density values a panel, near pairs by the linear closed form."""
+    p = sphere_problem(level)
+    u = _nodal_density(p, 7)
+    starts, _, _ = electrode_line_starts(p, L, seed=7)
+    ns_o, st_o, I_o = oracle.Oracle(p, constraint_form=1).p1_trace(u, starts, oracle.trace_params(h=1e-3, max_steps=8))[:3]
+    with bem.Context.from_problem(p, basis=bem.BASIS_LINEAR, constraint_form=1) as c:
+        c.set_tuning("trace_blocks", blocks)
+        x = torch.tensor(u[None], device="cuda")
+        I, ns, st, _ = c.streamer_integral(x, starts, bem.trace_params(h=1e-3, max_steps=8))
+    assert np.array_equal(ns.cpu().numpy(), ns_o) and np.array_equal(st.cpu().numpy(), st_o)
+    assert np.abs(I.cpu().numpy() - I_o).max() <= 1e-10 * np.abs(I_o).max()
+
+
+@pytest.mark.parametrize("L", [3, 100])
+def test_nodal_density_beyond_lds(bem, L):
+    """The coaxial conductors at 32,000 panels: few lines read records and densities from
+    memory each turn; 100 run in the two-kernel layout."""
+    p = coax_conductors_problem(0.0026)
+    assert p.n_tri > 30000
+    u = _nodal_density(p, 8)
+    starts, _, _ = electrode_line_starts(p, L, seed=8)
+    ns_o, st_o, I_o = oracle.Oracle(p, constraint_form=1).p1_trace(u, starts, oracle.trace_params(h=1e-4, max_steps=2))[:3]
+    with bem.Context.from_problem(p, basis=bem.BASIS_LINEAR, constraint_form=1) as c:
+        x = torch.tensor(u[None], device="cuda")
+        I, ns, st, _ = c.streamer_integral(x, starts, bem.trace_params(h=1e-4, max_steps=2))
+    assert np.array_equal(ns.cpu().numpy(), ns_o) and np.array_equal(st.cpu().numpy(), st_o)
+    assert np.abs(I.cpu().numpy() - I_o).max() <= 1e-10 * np.abs(I_o).max()
