@@ -159,7 +159,7 @@ struct bem_ctx {
     // scratch
     bem::DBuf gm_V, gm_w, gm_z, gm_h, gm_part, gm_x, gm_r, gm_b, gm_misc;
     bem::HBuf host_stage;
-    bem::DBuf ev_part, ev_mask, ev_ptr, ev_col, ev_row, ev_tmp, tr_queue, lb_state, lb_part, lf_part, lf_loop, lf_cnt, lc_buf, lc_image;
+    bem::DBuf ev_rec, ev_part, ev_mask, ev_ptr, ev_col, ev_row, ev_tmp, tr_queue, lb_state, lb_part, lf_part, lf_loop, lf_cnt, lc_buf, lc_image;
 
     bem::DBuf bg_V, bg_W, bg_part, bg_small, bg_z, bg_B, bg_X, gemm_part, rows_part;   // batched GMRES
     bem::DBuf near_sf;   // S, F of the near list by the near-singular rule (near_rule 1)
@@ -304,10 +304,6 @@ void launch_eval(bem_ctx* c, const double* sigma, int64_t P, const double* pts, 
 // Sec. 4 classification of (point, panel) pairs as ballot masks mask[(j >> 6) * P + p] (bit j & 63 set:
 // not regular, or j == on_panel[p]); ceil(N / 64) * P words.
 void launch_point_mask(bem_ctx* c, int64_t P, const double* pts, const int32_t* on_panel, uint64_t* mask);
-// panel-range split of the field evaluation's far pass for P points (K ranges; span panels each)
-int64_t eval_split(const bem_ctx* c, int64_t P, int64_t* span);   // eval.hip
-void launch_eval_far(bem_ctx* c, const double* sigma, int64_t P, const double* pts, const int32_t* on_panel,
-                     double* part, int64_t KS, int64_t span);    // eval.hip: part[KS][P][4]
 void launch_trace(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const int32_t* line_rhs,
                   const double* starts, const bem_trace_params* tp, int32_t* n_steps, int32_t* stop_code,
                   double* path, double* integral, uint8_t* exceeds);   // trace.hip
