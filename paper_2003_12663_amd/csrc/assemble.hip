@@ -7,7 +7,8 @@
 // Near-singular and singular pairs are not integrated here: they are written
 // as zero by a select (the 7-point rule has a node at the centroid, so the
 // self pair would divide by zero) and recorded in a 64-bit ballot mask per
-// (row, 64-panel group) -- the "not processed" marks of Sec. 4.
+// (row, 64-panel group) -- the "not processed" marks of Sec. 4.  k_far64 does so for FP64
+// rows, k_far for FP32 ones.
 // Pass 2 compacts the masks into a CSR near list (count, scan, fill) and
 // k_near evaluates every near pair with the closed forms, one lane per pair,
 // so that the divergent work runs on its own (Sec. 4, deferred near pass).
@@ -16,6 +17,7 @@
 #include <algorithm>
 
 #include "bem_device.h"
+#include "median_device.h"
 
 namespace bem {
 namespace {
@@ -24,19 +26,101 @@ namespace {
 // MODE 0: potential rows S_ij = sum_q w_q / |x_i - y_q|
 // MODE 1: normal-derivative rows K'_ij = n_i . sum_q w_q (x_i - y_q) / |x_i - y_q|^3,
 //         multiplied by row_scale[r]
-template <int MODE, typename R>
-__global__ __launch_bounds__(256) void k_far(const double* __restrict__ far64, const R* __restrict__ farR, int64_t Np,
+// FP64: the rule about the centroid, a panel's record (density one) in its lane's registers; the
+// next row's point is requested before a row's arithmetic.  The reach test settles nearly every pair
+// without the circumcentre's distance.  Bound by FP64 issue: 16,656 potential rows of 19,732 panels
+// 1.22 ms (node by node 1.41), 3,076 derivative rows 0.25 ms (0.32).
+template <int MODE>
+__global__ __launch_bounds__(256) void k_far64(const double* __restrict__ rec, const double* __restrict__ tri64,
+                                               int64_t N, const int32_t* __restrict__ rows, int64_t n_rows,
+                                               const double* __restrict__ row_scale, double* __restrict__ out, int64_t ld,
+                                               int out_by_slot, uint64_t* __restrict__ mask, int rows_per_block) {
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t jw = (int64_t)blockIdx.x * 256 + (threadIdx.x & ~63u);
+    if (jw >= N) return;   // no barrier below
+    const bool valid = j < N;
+    double v[MED_REC];
+    const double* rj = rec + (int64_t)MED_REC * (valid ? j : N - 1);
+#pragma unroll
+    for (int c = 0; c < MED_REC; ++c) v[c] = rj[c];
+    const MedConst k = med_consts();
+    const double sw = v[MD_DENS];
+    const int64_t r0 = (int64_t)blockIdx.y * rows_per_block;
+    const int64_t r1 = r0 + rows_per_block < n_rows ? r0 + rows_per_block : n_rows;
+    auto point = [&](int64_t i, double (&x)[6]) {
+        const double* Ti = tri64 + (int64_t)TRI_REC * i;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) x[c] = Ti[TR_C + c];
+        if constexpr (MODE == 1)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) x[3 + c] = Ti[TR_N + c];
+    };
+    int64_t i = rows[r0], i1 = rows[r0 + 1 < r1 ? r0 + 1 : r0];
+    double x[6], xn[6];
+    point(i, x);
+    for (int64_t r = r0; r < r1; ++r) {
+        point(i1, xn);
+        const int64_t i2 = rows[r + 2 < r1 ? r + 2 : r1 - 1];
+        const double t0 = x[0] - v[0], t1 = x[1] - v[1], t2 = x[2] - v[2];
+        const double T = __fma_rn(t0, t0, __fma_rn(t1, t1, t2 * t2));
+        bool reg = T > v[MD_REACH];
+        if (!reg) reg = is_regular(x[0] - v[MD_CC], x[1] - v[MD_CC + 1], x[2] - v[MD_CC + 2], v[MD_RR]);
+        reg = reg && j != i;
+        const double pa = __fma_rn(t0, v[3], __fma_rn(t1, v[4], t2 * v[5]));
+        const double pb = __fma_rn(t0, v[6], __fma_rn(t1, v[7], t2 * v[8]));
+        const double pc = -(pa + pb);
+        const double r2[7] = {T,
+                              __fma_rn(-2.0, pa, T + v[9]),
+                              __fma_rn(-2.0, pb, T + v[10]),
+                              __fma_rn(-2.0, pc, T + v[11]),
+                              __fma_rn(k.m2rho, pa, __fma_rn(k.rho2, v[9], T)),
+                              __fma_rn(k.m2rho, pb, __fma_rn(k.rho2, v[10], T)),
+                              __fma_rn(k.m2rho, pc, __fma_rn(k.rho2, v[11], T))};
+        double acc;
+        if constexpr (MODE == 0) {
+            double ir[7];
+#pragma unroll
+            for (int q = 0; q < 7; ++q) ir[q] = rsqrt_pos(r2[q]);
+            acc = sw * __fma_rn(k.kap0, ir[0], __fma_rn(k.kap, (ir[4] + ir[5]) + ir[6], (ir[1] + ir[2]) + ir[3]));
+        } else {
+            double g[7];
+#pragma unroll
+            for (int q = 0; q < 7; ++q) g[q] = med_r3(r2[q], k);
+            const double G = __fma_rn(k.kap0, g[0], __fma_rn(k.kap, (g[4] + g[5]) + g[6], (g[1] + g[2]) + g[3]));
+            const double h0 = __fma_rn(k.kaprho, g[4], g[1]), h1 = __fma_rn(k.kaprho, g[5], g[2]);
+            const double h2 = __fma_rn(k.kaprho, g[6], g[3]);
+            const double s0 = h2 - h0, s1 = h2 - h1;
+            const double f0 = __fma_rn(G, t0, __fma_rn(s0, v[3], s1 * v[6]));
+            const double f1 = __fma_rn(G, t1, __fma_rn(s0, v[4], s1 * v[7]));
+            const double f2 = __fma_rn(G, t2, __fma_rn(s0, v[5], s1 * v[8]));
+            acc = sw * row_scale[r] * __fma_rn(x[3], f0, __fma_rn(x[4], f1, x[5] * f2));
+        }
+        if (valid) out[(out_by_slot ? r : i) * ld + j] = reg ? acc : 0.0;
+        if (mask) {
+            const uint64_t m = __ballot(valid && !reg);
+            if ((threadIdx.x & 63) == 0) mask[(jw >> 6) * N + i] = m;
+        }
+        i = i1;
+        i1 = i2;
+#pragma unroll
+        for (int c = 0; c < (MODE == 1 ? 6 : 3); ++c) x[c] = xn[c];
+    }
+}
+
+// FP32: node by node, classified in FP64 (template argument MODE as above)
+template <int MODE>
+__global__ __launch_bounds__(256) void k_far(const double* __restrict__ far64, const float* __restrict__ farR, int64_t Np,
                                              const double* __restrict__ tri64, int64_t N,
                                              const int32_t* __restrict__ rows, int64_t n_rows,
-                                             const double* __restrict__ row_scale, R* __restrict__ out, int64_t ld,
-                                             int out_by_slot, uint64_t* __restrict__ mask, int rows_per_block) {
+                                             const double* __restrict__ row_scale, float* __restrict__ out, int64_t ld,
+                                             uint64_t* __restrict__ mask, int rows_per_block) {
     const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;   // < Np always
     const bool valid = j < N;
     const double ccx = far64[(int64_t)(FR_CC + 0) * Np + j];
     const double ccy = far64[(int64_t)(FR_CC + 1) * Np + j];
     const double ccz = far64[(int64_t)(FR_CC + 2) * Np + j];
     const double rr = far64[(int64_t)FR_RR * Np + j];
-    R qx[7], qy[7], qz[7], qw[7];
+    float qx[7], qy[7], qz[7], qw[7];
 #pragma unroll
     for (int q = 0; q < 7; ++q) {
         qx[q] = farR[(int64_t)(FR_X + q) * Np + j];
@@ -52,39 +136,36 @@ __global__ __launch_bounds__(256) void k_far(const double* __restrict__ far64, c
         const double* Ti = tri64 + (int64_t)TRI_REC * i;
         const double xi0 = Ti[TR_C + 0], xi1 = Ti[TR_C + 1], xi2 = Ti[TR_C + 2];
         const bool regular = is_regular(xi0 - ccx, xi1 - ccy, xi2 - ccz, rr) && (j != i);
-        const R x0 = (R)xi0, x1 = (R)xi1, x2 = (R)xi2;
-        R acc;
+        const float x0 = (float)xi0, x1 = (float)xi1, x2 = (float)xi2;
+        float acc;
         if (MODE == 0) {
-            R s = (R)0;
+            float s = (float)0;
 #pragma unroll
             for (int q = 0; q < 7; ++q) {
-                const R dx = x0 - qx[q], dy = x1 - qy[q], dz = x2 - qz[q];
-                const R r2 = dx * dx + dy * dy + dz * dz;
+                const float dx = x0 - qx[q], dy = x1 - qy[q], dz = x2 - qz[q];
+                const float r2 = dx * dx + dy * dy + dz * dz;
                 s += qw[q] * rsqrt_pos(r2);
             }
             acc = s;
         } else {
-            R f0 = 0, f1 = 0, f2 = 0;
+            float f0 = 0, f1 = 0, f2 = 0;
 #pragma unroll
             for (int q = 0; q < 7; ++q) {
-                const R dx = x0 - qx[q], dy = x1 - qy[q], dz = x2 - qz[q];
-                const R r2 = dx * dx + dy * dy + dz * dz;
-                const R ir = rsqrt_pos(r2);
-                const R t = qw[q] * ir * ir * ir;
+                const float dx = x0 - qx[q], dy = x1 - qy[q], dz = x2 - qz[q];
+                const float r2 = dx * dx + dy * dy + dz * dz;
+                const float ir = rsqrt_pos(r2);
+                const float t = qw[q] * ir * ir * ir;
                 f0 += t * dx;
                 f1 += t * dy;
                 f2 += t * dz;
             }
-            const R n0 = (R)Ti[TR_N + 0], n1 = (R)Ti[TR_N + 1], n2 = (R)Ti[TR_N + 2];
-            acc = (n0 * f0 + n1 * f1 + n2 * f2) * (R)row_scale[r];
+            const float n0 = (float)Ti[TR_N + 0], n1 = (float)Ti[TR_N + 1], n2 = (float)Ti[TR_N + 2];
+            acc = (n0 * f0 + n1 * f1 + n2 * f2) * (float)row_scale[r];
         }
-        const R val = regular ? acc : (R)0;
-        const int64_t orow = out_by_slot ? r : i;
-        if (valid) out[orow * ld + j] = val;
-        if (mask) {
-            const uint64_t m = __ballot(valid && !regular);
-            if (wave_live && (threadIdx.x & 63) == 0) mask[(j >> 6) * N + i] = m;
-        }
+        const float val = regular ? acc : (float)0;
+        if (valid) out[i * ld + j] = val;
+        const uint64_t m = __ballot(valid && !regular);
+        if (wave_live && (threadIdx.x & 63) == 0) mask[(j >> 6) * N + i] = m;
     }
 }
 
@@ -310,31 +391,18 @@ void launch_far_assemble(bem_ctx* c) {
     const int64_t Np = padded_panels(c);
     const bool mixed = c->opt.precision == BEM_MIXED;
     uint64_t* mask = c->nearmask.as<uint64_t>();
-    auto launch = [&](int mode, const bem::DBuf& rows, int64_t nr, const double* scale, bool by_slot, bool with_mask,
-                      void* out, int64_t ld, bool fp32) {
-        if (nr == 0) return;
-        const int rpb = c->tune_far_rows;
-        dim3 grid((unsigned)(Np / 256), (unsigned)ceil_div(nr, rpb));
-        uint64_t* m = with_mask ? mask : nullptr;
-        if (!fp32) {
-            if (mode == 0)
-                hipLaunchKernelGGL((k_far<0, double>), grid, dim3(256), 0, c->stream, c->far64.as<double>(),
-                                   c->far64.as<double>(), Np, c->tri64.as<double>(), c->N, rows.as<int32_t>(), nr,
-                                   scale, (double*)out, ld, (int)by_slot, m, rpb);
-            else
-                hipLaunchKernelGGL((k_far<1, double>), grid, dim3(256), 0, c->stream, c->far64.as<double>(),
-                                   c->far64.as<double>(), Np, c->tri64.as<double>(), c->N, rows.as<int32_t>(), nr,
-                                   scale, (double*)out, ld, (int)by_slot, m, rpb);
-        } else {
-            if (mode == 0)
-                hipLaunchKernelGGL((k_far<0, float>), grid, dim3(256), 0, c->stream, c->far64.as<double>(),
-                                   c->far32.as<float>(), Np, c->tri64.as<double>(), c->N, rows.as<int32_t>(), nr,
-                                   scale, (float*)out, ld, (int)by_slot, m, rpb);
-            else
-                hipLaunchKernelGGL((k_far<1, float>), grid, dim3(256), 0, c->stream, c->far64.as<double>(),
-                                   c->far32.as<float>(), Np, c->tri64.as<double>(), c->N, rows.as<int32_t>(), nr,
-                                   scale, (float*)out, ld, (int)by_slot, m, rpb);
-        }
+    const int rpb = c->tune_far_rows;
+    auto launch64 = [&](auto kernel, const bem::DBuf& rows, int64_t nr, const double* scale, bool by_slot, uint64_t* m,
+                        void* out, int64_t ld) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(Np / 256), (unsigned)ceil_div(nr, rpb)), dim3(256), 0, c->stream,
+                           c->ev_rec.as<double>(), c->tri64.as<double>(), c->N, rows.as<int32_t>(), nr, scale,
+                           (double*)out, ld, (int)by_slot, m, rpb);
+        BEM_CHECK_LAUNCH();
+    };
+    auto launch32 = [&](auto kernel, const bem::DBuf& rows, int64_t nr, const double* scale, void* out) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(Np / 256), (unsigned)ceil_div(nr, rpb)), dim3(256), 0, c->stream,
+                           c->far64.as<double>(), c->far32.as<float>(), Np, c->tri64.as<double>(), c->N,
+                           rows.as<int32_t>(), nr, scale, (float*)out, c->ld, mask, rpb);
         BEM_CHECK_LAUNCH();
     };
     const int64_t npot = (int64_t)c->h_rows_pot.size(), nint = (int64_t)c->h_rows_int.size();
@@ -342,11 +410,18 @@ void launch_far_assemble(bem_ctx* c) {
     double* scale_int = c->gm_misc.as<double>();            // (eps+ - eps-) per interface row
     double* scale_one = scale_int + (nint > 0 ? nint : 1);  // 1 per floating row
     void* A = mixed ? c->A32.p : c->A64.p;
-    launch(0, c->rows_pot, npot, nullptr, false, true, A, c->ld, mixed);
-    launch(1, c->rows_int, nint, scale_int, false, true, A, c->ld, mixed);
     // K' block of floating rows (FP64 in both modes) for the constraint rows
-    if (nflt > 0 && (c->opt.constraint_form == 0 || c->has_sheet))
-        launch(1, c->rows_flt, nflt, scale_one, true, false, c->Kf.p, c->N, false);
+    const bool kf = nflt > 0 && (c->opt.constraint_form == 0 || c->has_sheet);
+    if (!mixed || kf) launch_median_records(c, nullptr, c->ev_rec);
+    if (npot > 0) {
+        if (mixed) launch32(k_far<0>, c->rows_pot, npot, nullptr, A);
+        else launch64(k_far64<0>, c->rows_pot, npot, nullptr, false, mask, A, c->ld);
+    }
+    if (nint > 0) {
+        if (mixed) launch32(k_far<1>, c->rows_int, nint, scale_int, A);
+        else launch64(k_far64<1>, c->rows_int, nint, scale_int, false, mask, A, c->ld);
+    }
+    if (kf) launch64(k_far64<1>, c->rows_flt, nflt, scale_one, true, nullptr, c->Kf.p, c->N);
 }
 
 void launch_near_csr(bem_ctx* c, const uint64_t* mask, int64_t T, DBuf& ptr, DBuf& row, DBuf& col, int64_t* nnz,

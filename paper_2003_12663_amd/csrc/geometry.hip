@@ -151,7 +151,8 @@ __global__ __launch_bounds__(256) void k_median_records(int64_t N, int64_t Np, i
 #pragma unroll
     for (int v = 0; v < 3; ++v) r[9 + v] = m[v][0] * m[v][0] + m[v][1] * m[v][1] + m[v][2] * m[v][2];
     const double rr = far64[(int64_t)FR_RR * Np + j];
-    r[MD_DENS] = sol ? sol[j] * (MED_W1 * INV4PI * T[TR_A]) : 0.0;
+    const double w = MED_W1 * INV4PI * T[TR_A];
+    r[MD_DENS] = sol ? sol[j] * w : w;
     const double reach = (sqrt(rr) + sqrt(off)) * (1.0 + 1e-6);   // far above the rounding of either distance
     r[MD_REACH] = reach * reach;
     r[MD_RR] = rr;
