@@ -128,8 +128,10 @@ __global__ __launch_bounds__(256) void k_ev_far(const double* __restrict__ rec, 
     double vA[MED_REC], vB[MED_REC];
     fetch(j0, vA);
     for (int j = j0; j < j1; j += 2) {
+        wait_scalar();
         fetch(j + 1, vB);
         panel(j, vA);
+        wait_scalar();
         fetch(j + 2, vA);
         if (j + 1 < j1) panel(j + 1, vB);
     }

@@ -34,6 +34,11 @@ __device__ __forceinline__ MedConst med_consts() {
     return k;
 }
 
+// Waits for this wave's scalar loads (and LDS operations) so far.  Scalar loads return out of order, so
+// a wait for one is a wait for all: a loop that requests the next record ahead has to wait for the
+// current one before that request, or it waits for both.
+__device__ __forceinline__ void wait_scalar() { __builtin_amdgcn_s_waitcnt(0xC07F); }   // lgkmcnt(0)
+
 // r^-3 from r^2: from the hardware estimate y of r^-1 (relative error about 2^-24), e = 1 - r^2 y^2
 // and y^3 (1 + 3/2 e + 15/8 e^2 + O(e^3)): truncation below 2^-68
 __device__ __forceinline__ double med_r3(double r2, const MedConst& k) {

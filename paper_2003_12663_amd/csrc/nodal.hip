@@ -22,28 +22,13 @@
 #include <cmath>
 
 #include "bem_device.h"
+#include "median_device.h"
 #include "nodal_device.h"
 
 namespace bem {
 namespace {
 
 constexpr int NODAL_COLS = 16;   // columns per wave
-
-// The rule's barycentric coordinate of local vertex c at node q (node order of
-// the panel records: centroid, then the orbits (a, a, 1 - 2a) for a = a1, a2
-// with the odd coordinate last, middle, first).
-struct NodeBary {
-    double b[7];
-    __device__ NodeBary(int c) {
-        const double s15 = sqrt(15.0);
-        const double a1 = (6.0 - s15) / 21.0, a2 = (6.0 + s15) / 21.0;
-        b[0] = 1.0 / 3.0;
-#pragma unroll
-        for (int q = 1; q <= 3; ++q) b[q] = (c == 3 - q) ? 1.0 - 2.0 * a1 : a1;
-#pragma unroll
-        for (int q = 4; q <= 6; ++q) b[q] = (c == 6 - q) ? 1.0 - 2.0 * a2 : a2;
-    }
-};
 
 // Closed form of int lambda_c(y) / (4 pi |x - y|) dS over the flat triangle T
 // (16-double exact-geometry record) for its local vertex c.  With rho the foot
@@ -157,6 +142,8 @@ __device__ __forceinline__ double hat_value(const double* __restrict__ T, int c,
     return (lam * I0 + (g0 * J0 + g1 * J1 + g2 * J2) / two_area) * INV4PI;
 }
 
+// Regular pairs of the vertex rows (KP false) or of the centroid rows below (KP true: x the centroid of
+// triangle trow[i], the kernel n . (x - y)/|x - y|^3 in place of 1/|x - y|).
 // One wave: rows i0 + lane, columns j0 .. j0 + 15 (column group cg).  The wave walks the
 // distinct triangles that hold a vertex of the group (ascending), evaluates the 7-point
 // rule once per triangle and adds each hat whose vertex is in the group into that column's
@@ -166,62 +153,117 @@ __device__ __forceinline__ double hat_value(const double* __restrict__ T, int c,
 // rows, n_cg a multiple of 8): blocks are dealt to the 8 XCDs in turn, so block b runs on
 // XCD b % 8, and each XCD sweeps all row tiles of one column group before the next,
 // keeping that group's records in its own L2.
-template <class T>   // stored type: double (FP64) or float (MIXED)
-__global__ __launch_bounds__(256) void k_nodal_assemble(int64_t nv, int64_t ld, int64_t n_rt,
-                                                        const double* __restrict__ vert,
-                                                        const int32_t* __restrict__ tri,
-                                                        const int32_t* __restrict__ grp_ptr,
-                                                        const int32_t* __restrict__ grp_tri,
-                                                        const uint32_t* __restrict__ grp_loc,
-                                                        const double* __restrict__ pan64, T* __restrict__ A) {
+// The rule is the form about the centroid (density one in the records).  Corner k's hat is 1/3 at the
+// centroid and 1/3 + s (delta_ik - 1/3) at the node on corner i's median (s the median's scale, s rho
+// on the second orbit), so with f_q the kernel at the nodes, U = sum w f and h_i = w_1 f_1i + rho w_2
+// f_2i its integral is U / 3 + s (h_k - (h_0 + h_1 + h_2) / 3).  A corner lies within reach of its
+// triangle, so corners are looked for only there.  Bound by FP64 issue; the next triangle's record is
+// requested before a triangle's arithmetic.
+template <class T, bool KP>   // T: stored type, double (FP64) or float (MIXED)
+__global__ __launch_bounds__(256) void k_nodal_regular(int64_t nr, int64_t nv, int64_t ld, int64_t n_rt,
+                                                       const double* __restrict__ vert,
+                                                       const int32_t* __restrict__ trow,
+                                                       const int32_t* __restrict__ tri,
+                                                       const int32_t* __restrict__ grp_ptr,
+                                                       const int32_t* __restrict__ grp_tri,
+                                                       const uint32_t* __restrict__ grp_loc,
+                                                       const double* __restrict__ rec,
+                                                       const double* __restrict__ tri64, T* __restrict__ A) {
+    constexpr int PF = MD_REACH + 1;             // the part of a record that every pair reads
     __shared__ double tile[4][NODAL_COLS][65];   // padded: the row-segment reads stride 65
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t b = blockIdx.x, xcd = b & 7, slot = b >> 3;
     const int64_t cg = (slot / n_rt) * 8 + xcd, rt = slot % n_rt;
     const int64_t i0 = (rt * 4 + wv) * 64;
     const int64_t i = i0 + lane;
-    const int64_t ic = i < nv ? i : nv - 1;
-    const double x0 = vert[3 * ic], x1 = vert[3 * ic + 1], x2 = vert[3 * ic + 2];
+    const int64_t ic = i < nr ? i : nr - 1;
+    const int64_t own = KP ? trow[ic] : -1;
+    const double* X = KP ? tri64 + (int64_t)TRI_REC * own : vert + 3 * ic;
+    const double x0 = X[KP ? TR_C : 0], x1 = X[KP ? TR_C + 1 : 1], x2 = X[KP ? TR_C + 2 : 2];
+    const double n0 = KP ? X[TR_N] : 0.0, n1 = KP ? X[TR_N + 1] : 0.0, n2 = KP ? X[TR_N + 2] : 0.0;
     const int64_t j0 = cg * NODAL_COLS;
 #pragma unroll
     for (int cc = 0; cc < NODAL_COLS; ++cc) tile[wv][cc][lane] = 0.0;
-    if (j0 < nv) {
-        const NodeBary nb0(0), nb1(1), nb2(2);
-        const int32_t e1 = grp_ptr[cg + 1];
-        for (int32_t e = grp_ptr[cg]; e < e1; ++e) {
-            const int64_t t = grp_tri[e];
-            const uint32_t loc = grp_loc[e];   // local column of corners 0, 1, 2 (0xff: not in the group)
-            const double* P = pan64 + (int64_t)FAR_REC * t;
-            const int32_t* tv = tri + 3 * t;
-            const bool vtx = (tv[0] == i) || (tv[1] == i) || (tv[2] == i);
-            // near and singular pairs are left to k_nodal_near (same predicate)
-            if (!vtx && is_regular(x0 - P[FR_CC], x1 - P[FR_CC + 1], x2 - P[FR_CC + 2], P[FR_RR])) {
-                double wr[7];
-#pragma unroll
-                for (int q = 0; q < 7; ++q) {
-                    const double d0 = x0 - P[FR_X + q], d1 = x1 - P[FR_Y + q], d2 = x2 - P[FR_Z + q];
-                    wr[q] = rsqrt_pos(d0 * d0 + d1 * d1 + d2 * d2);
-                }
-                const uint32_t l0 = loc & 0xffu, l1 = (loc >> 8) & 0xffu, l2 = (loc >> 16) & 0xffu;
-                if (l0 != 0xffu) {
-                    double s = 0.0;
-#pragma unroll
-                    for (int q = 0; q < 7; ++q) s += P[FR_W + q] * nb0.b[q] * wr[q];
-                    tile[wv][l0][lane] += s;
-                }
-                if (l1 != 0xffu) {
-                    double s = 0.0;
-#pragma unroll
-                    for (int q = 0; q < 7; ++q) s += P[FR_W + q] * nb1.b[q] * wr[q];
-                    tile[wv][l1][lane] += s;
-                }
-                if (l2 != 0xffu) {
-                    double s = 0.0;
-#pragma unroll
-                    for (int q = 0; q < 7; ++q) s += P[FR_W + q] * nb2.b[q] * wr[q];
-                    tile[wv][l2][lane] += s;
-                }
+    const int32_t e0 = j0 < nv ? grp_ptr[cg] : 0, e1 = j0 < nv ? grp_ptr[cg + 1] : 0;
+    MedConst k = med_consts();
+    // in vector registers: two records and the pointers fill the scalar ones
+    asm volatile("" : "+v"(k.m2rho), "+v"(k.rho2), "+v"(k.kap), "+v"(k.kap0), "+v"(k.kaprho), "+v"(k.c1875), "+v"(k.rho));
+    auto visit = [&](int64_t t, uint32_t loc, const double (&v)[PF]) {
+        const double t0 = x0 - v[0], t1 = x1 - v[1], t2 = x2 - v[2];
+        const double TT = __fma_rn(t0, t0, __fma_rn(t1, t1, t2 * t2));
+        bool reg = TT > v[MD_REACH];
+        if (!reg) {   // near and singular pairs are left to k_nodal_near (same predicate)
+            const double* r = rec + (int64_t)MED_REC * t;
+            reg = is_regular(x0 - r[MD_CC], x1 - r[MD_CC + 1], x2 - r[MD_CC + 2], r[MD_RR]);
+            if constexpr (KP) {
+                reg = reg && t != own;
+            } else {
+                const int32_t* tv = tri + 3 * t;
+                reg = reg && tv[0] != i && tv[1] != i && tv[2] != i;
             }
+        }
+        if (!reg) return;
+        const double pa = __fma_rn(t0, v[3], __fma_rn(t1, v[4], t2 * v[5]));
+        const double pb = __fma_rn(t0, v[6], __fma_rn(t1, v[7], t2 * v[8]));
+        const double pc = -(pa + pb);
+        const double r2[7] = {TT,
+                              __fma_rn(-2.0, pa, TT + v[9]),
+                              __fma_rn(-2.0, pb, TT + v[10]),
+                              __fma_rn(-2.0, pc, TT + v[11]),
+                              __fma_rn(k.m2rho, pa, __fma_rn(k.rho2, v[9], TT)),
+                              __fma_rn(k.m2rho, pb, __fma_rn(k.rho2, v[10], TT)),
+                              __fma_rn(k.m2rho, pc, __fma_rn(k.rho2, v[11], TT))};
+        double f[7];
+        if constexpr (KP) {
+            const double nt = __fma_rn(n0, t0, __fma_rn(n1, t1, n2 * t2));
+            const double na = __fma_rn(n0, v[3], __fma_rn(n1, v[4], n2 * v[5]));
+            const double nb = __fma_rn(n0, v[6], __fma_rn(n1, v[7], n2 * v[8]));
+            const double nc = -(na + nb);
+            f[0] = nt * med_r3(r2[0], k);
+            f[1] = (nt - na) * med_r3(r2[1], k);
+            f[2] = (nt - nb) * med_r3(r2[2], k);
+            f[3] = (nt - nc) * med_r3(r2[3], k);
+            f[4] = __fma_rn(-k.rho, na, nt) * med_r3(r2[4], k);
+            f[5] = __fma_rn(-k.rho, nb, nt) * med_r3(r2[5], k);
+            f[6] = __fma_rn(-k.rho, nc, nt) * med_r3(r2[6], k);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 7; ++q) f[q] = rsqrt_pos(r2[q]);
+        }
+        const double U = __fma_rn(k.kap0, f[0], __fma_rn(k.kap, (f[4] + f[5]) + f[6], (f[1] + f[2]) + f[3]));
+        const double h0 = __fma_rn(k.kaprho, f[4], f[1]), h1 = __fma_rn(k.kaprho, f[5], f[2]);
+        const double h2 = __fma_rn(k.kaprho, f[6], f[3]);
+        const double hs = v[MD_DENS] * MED_SC;
+        const double base = (v[MD_DENS] * (1.0 / 3.0)) * __fma_rn(-MED_SC, (h0 + h1) + h2, U);
+        const uint32_t l0 = loc & 0xffu, l1 = (loc >> 8) & 0xffu, l2 = (loc >> 16) & 0xffu;
+        if (l0 != 0xffu) tile[wv][l0][lane] += __fma_rn(hs, h0, base);
+        if (l1 != 0xffu) tile[wv][l1][lane] += __fma_rn(hs, h1, base);
+        if (l2 != 0xffu) tile[wv][l2][lane] += __fma_rn(hs, h2, base);
+    };
+    if (e0 < e1) {
+        auto fetch = [&](int64_t t, double (&v)[PF]) {
+            const double* r = rec + (int64_t)MED_REC * t;
+#pragma unroll
+            for (int c = 0; c < PF; ++c) v[c] = r[c];
+        };
+        auto at = [&](int32_t e) { return e < e1 ? e : e1 - 1; };
+        double vA[PF], vB[PF];
+        int32_t tA = grp_tri[e0], tB = grp_tri[at(e0 + 1)];
+        uint32_t lA = grp_loc[e0], lB = grp_loc[at(e0 + 1)];
+        fetch(tA, vA);
+        for (int32_t e = e0; e < e1; e += 2) {
+            wait_scalar();
+            const int32_t tC = grp_tri[at(e + 2)], tD = grp_tri[at(e + 3)];
+            const uint32_t lC = grp_loc[at(e + 2)], lD = grp_loc[at(e + 3)];
+            fetch(tB, vB);
+            visit(tA, lA, vA);
+            wait_scalar();
+            fetch(tC, vA);
+            if (e + 1 < e1) visit(tB, lB, vB);
+            tA = tC;
+            tB = tD;
+            lA = lC;
+            lB = lD;
         }
     }
     __syncthreads();
@@ -229,7 +271,7 @@ __global__ __launch_bounds__(256) void k_nodal_assemble(int64_t nv, int64_t ld, 
     for (int s = 0; s < 16; ++s) {
         const int r = (lane >> 4) + 4 * s, cc = lane & 15;
         const int64_t ii = i0 + r, jj = j0 + cc;
-        if (ii < nv && jj < nv) A[ii * ld + jj] = (T)tile[wv][cc][r];
+        if (ii < nr && jj < nv) A[ii * ld + jj] = (T)tile[wv][cc][r];
     }
 }
 
@@ -415,74 +457,6 @@ __global__ __launch_bounds__(64) void k_nodal_near(int64_t nr, int64_t ld, int64
 // triangle but T at x_T) for the centroid rows r (trow[r] = T), row stride ld.  T itself adds
 // nothing (in its plane the field of its own density has no normal component).
 
-// Regular pairs of the centroid rows: k_nodal_assemble's walk of column groups, with the
-// kernel n_T . w (x - y)/|x - y|^3 in place of w/|x - y|.  Kc is FP64.
-__global__ __launch_bounds__(256) void k_nodal_kp_assemble(int64_t nc, int64_t nv, int64_t ld, int64_t n_rt,
-                                                           const int32_t* __restrict__ trow,
-                                                           const int32_t* __restrict__ grp_ptr,
-                                                           const int32_t* __restrict__ grp_tri,
-                                                           const uint32_t* __restrict__ grp_loc,
-                                                           const double* __restrict__ pan64,
-                                                           const double* __restrict__ tri64, double* __restrict__ Kc) {
-    __shared__ double tile[4][NODAL_COLS][65];
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t b = blockIdx.x, xcd = b & 7, slot = b >> 3;
-    const int64_t cg = (slot / n_rt) * 8 + xcd, rt = slot % n_rt;
-    const int64_t r0 = (rt * 4 + wv) * 64;
-    const int64_t r = r0 + lane;
-    const int64_t T = trow[r < nc ? r : nc - 1];
-    const double* Tr = tri64 + (int64_t)TRI_REC * T;
-    const double x0 = Tr[TR_C], x1 = Tr[TR_C + 1], x2 = Tr[TR_C + 2];
-    const double m0 = Tr[TR_N], m1 = Tr[TR_N + 1], m2 = Tr[TR_N + 2];
-    const int64_t j0 = cg * NODAL_COLS;
-#pragma unroll
-    for (int cc = 0; cc < NODAL_COLS; ++cc) tile[wv][cc][lane] = 0.0;
-    if (j0 < nv) {
-        const NodeBary nb0(0), nb1(1), nb2(2);
-        const int32_t e1 = grp_ptr[cg + 1];
-        for (int32_t e = grp_ptr[cg]; e < e1; ++e) {
-            const int64_t t = grp_tri[e];
-            const uint32_t loc = grp_loc[e];
-            const double* P = pan64 + (int64_t)FAR_REC * t;
-            if (t != T && is_regular(x0 - P[FR_CC], x1 - P[FR_CC + 1], x2 - P[FR_CC + 2], P[FR_RR])) {
-                double kq[7];
-#pragma unroll
-                for (int q = 0; q < 7; ++q) {
-                    const double d0 = x0 - P[FR_X + q], d1 = x1 - P[FR_Y + q], d2 = x2 - P[FR_Z + q];
-                    const double ir = rsqrt_pos(d0 * d0 + d1 * d1 + d2 * d2);
-                    kq[q] = P[FR_W + q] * (d0 * m0 + d1 * m1 + d2 * m2) * (ir * ir * ir);
-                }
-                const uint32_t l0 = loc & 0xffu, l1 = (loc >> 8) & 0xffu, l2 = (loc >> 16) & 0xffu;
-                if (l0 != 0xffu) {
-                    double sacc = 0.0;
-#pragma unroll
-                    for (int q = 0; q < 7; ++q) sacc += kq[q] * nb0.b[q];
-                    tile[wv][l0][lane] += sacc;
-                }
-                if (l1 != 0xffu) {
-                    double sacc = 0.0;
-#pragma unroll
-                    for (int q = 0; q < 7; ++q) sacc += kq[q] * nb1.b[q];
-                    tile[wv][l1][lane] += sacc;
-                }
-                if (l2 != 0xffu) {
-                    double sacc = 0.0;
-#pragma unroll
-                    for (int q = 0; q < 7; ++q) sacc += kq[q] * nb2.b[q];
-                    tile[wv][l2][lane] += sacc;
-                }
-            }
-        }
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int sgm = 0; sgm < 16; ++sgm) {
-        const int rr = (lane >> 4) + 4 * sgm, cc = lane & 15;
-        const int64_t ii = r0 + rr, jj = j0 + cc;
-        if (ii < nc && jj < nv) Kc[ii * ld + jj] = tile[wv][cc][rr];
-    }
-}
-
 // Interface vertex rows (Eq. nonconductors at the vertex, taken as the hat-weighted mean over
 // the vertex's triangles T of the condition at x_T): one block per interface vertex i,
 //   A[i][k] = sum_{T in fan(i)} (a_T/3)/m_i [ (eps+ - eps-) Kc[crow(T)][k]
@@ -642,7 +616,7 @@ __global__ __launch_bounds__(256) void k_nodal_field(int64_t P, const double* __
         const double u0 = u[tv[0]], u1 = u[tv[1]], u2 = u[tv[2]];
         const double* Pr = pan64 + (int64_t)FAR_REC * t;
         if (is_regular(x0 - Pr[FR_CC], x1 - Pr[FR_CC + 1], x2 - Pr[FR_CC + 2], Pr[FR_RR])) {
-            // density at the nodes (same barycentrics as NodeBary)
+            // density at the nodes: centroid, then the orbits (a, a, 1 - 2a), odd coordinate last, middle, first
             const double sq[7] = {(u0 + u1 + u2) / 3.0,
                                   a1 * u0 + a1 * u1 + b1 * u2, a1 * u0 + b1 * u1 + a1 * u2, b1 * u0 + a1 * u1 + a1 * u2,
                                   a2 * u0 + a2 * u1 + b2 * u2, a2 * u0 + b2 * u1 + a2 * u2, b2 * u0 + a2 * u1 + a2 * u2};
@@ -734,9 +708,11 @@ static void nodal_assemble_t(bem_ctx* c, T* A, double* Atail, int64_t tail_row0)
     hipStream_t s = c->stream;
     const int64_t n_rt = ceil_div(nv, 256), n_cg = ceil_div(ceil_div(nv, NODAL_COLS), 8) * 8;
     if (n_rt * n_cg > ((int64_t)1 << 31) - 1) throw Error(BEM_ERR_INVALID, "too many vertices for the LINEAR basis");
-    hipLaunchKernelGGL(k_nodal_assemble<T>, dim3((unsigned)(n_rt * n_cg)), dim3(256), 0, s, nv, ld, n_rt,
-                       c->vert.as<double>(), c->tri.as<int32_t>(), c->grp_ptr.as<int32_t>(), c->grp_tri.as<int32_t>(),
-                       c->grp_loc.as<uint32_t>(), c->pan64.as<double>(), A);
+    launch_median_records(c, nullptr, c->ev_rec);
+    hipLaunchKernelGGL((k_nodal_regular<T, false>), dim3((unsigned)(n_rt * n_cg)), dim3(256), 0, s, nv, nv, ld, n_rt,
+                       c->vert.as<double>(), (const int32_t*)nullptr, c->tri.as<int32_t>(), c->grp_ptr.as<int32_t>(),
+                       c->grp_tri.as<int32_t>(), c->grp_loc.as<uint32_t>(), c->ev_rec.as<double>(),
+                       c->tri64.as<double>(), A);
     BEM_CHECK_LAUNCH();
     const int64_t Np = (int64_t)(c->far64.bytes / (sizeof(double) * FAR_REC));
     const int64_t nch = ceil_div(c->N, 64);
@@ -763,9 +739,10 @@ static void nodal_assemble_t(bem_ctx* c, T* A, double* Atail, int64_t tail_row0)
         double* Kc = c->nod_Kc.as<double>();
         const int64_t n_rtc = ceil_div(nc, 256);
         if (n_rtc * n_cg > ((int64_t)1 << 31) - 1) throw Error(BEM_ERR_INVALID, "too many centroid rows");
-        hipLaunchKernelGGL(k_nodal_kp_assemble, dim3((unsigned)(n_rtc * n_cg)), dim3(256), 0, s, nc, nv, ld, n_rtc,
-                           c->nod_trow.as<int32_t>(), c->grp_ptr.as<int32_t>(), c->grp_tri.as<int32_t>(),
-                           c->grp_loc.as<uint32_t>(), c->pan64.as<double>(), c->tri64.as<double>(), Kc);
+        hipLaunchKernelGGL((k_nodal_regular<double, true>), dim3((unsigned)(n_rtc * n_cg)), dim3(256), 0, s, nc, nv, ld,
+                           n_rtc, (const double*)nullptr, c->nod_trow.as<int32_t>(), c->tri.as<int32_t>(),
+                           c->grp_ptr.as<int32_t>(), c->grp_tri.as<int32_t>(), c->grp_loc.as<uint32_t>(),
+                           c->ev_rec.as<double>(), c->tri64.as<double>(), Kc);
         BEM_CHECK_LAUNCH();
         hipLaunchKernelGGL((k_nodal_near<double, true>), dim3((unsigned)(ceil_div(nc, 8) * 8)), dim3(64), 0, s, nc, ld,
                            c->N, Np, (const int32_t*)nullptr, (const double*)nullptr, c->nod_trow.as<int32_t>(),
