@@ -137,7 +137,7 @@ struct bem_ctx {
     bem::DBuf vert_body, fan_ptr, fan, nodal_mass, nodal_bounds, row_order;   // nodal basis only
     // per group of 16 consecutive vertex columns: the triangles holding one of its vertices
     // (ascending) and the local column of each corner (8 bits each, 0xff outside the group)
-    bem::DBuf grp_ptr, grp_tri, grp_loc;
+    bem::DBuf grp_col, grp_ptr, grp_tri, grp_loc;
     bem::DBuf nod_pan64, nod_far64, nod_ones;   // nodal density folded into the panel records (field lines)
     // nodal rows that need n . E, taken at triangle centroids: the centroid rows (triangles of
     // interface bodies, then of floating bodies whose row has a K' term, grouped by body), the
@@ -270,6 +270,7 @@ void launch_quad_pair_integrals(bem_ctx* c, int64_t P, const double* pts, const 
 // the Sec. 4 rule for the assembly's near list into sf[4 k .. 4 k + 3] (duffy.hip)
 void launch_near_duffy(bem_ctx* c, int64_t nnz, const int32_t* row, const int32_t* col, double* sf);
 // records of the 7-point rule about the centroid with the densities sol (or none), in B groups (geometry.hip)
+constexpr int NODAL_COLS = 16;   // columns of a group of the nodal basis's regular pass
 void launch_median_records(bem_ctx* c, const double* sol, DBuf& out, int B = 1, int64_t P = 0);
 void launch_panel_points(bem_ctx* c, int64_t L, const int32_t* panel, const double* bary, double offset,
                          double* out);                                // geometry.hip

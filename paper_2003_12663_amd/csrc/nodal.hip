@@ -28,8 +28,6 @@
 namespace bem {
 namespace {
 
-constexpr int NODAL_COLS = 16;   // columns per wave
-
 // Closed form of int lambda_c(y) / (4 pi |x - y|) dS over the flat triangle T
 // (16-double exact-geometry record) for its local vertex c.  With rho the foot
 // point of x on the plane and w the height,
@@ -144,15 +142,16 @@ __device__ __forceinline__ double hat_value(const double* __restrict__ T, int c,
 
 // Regular pairs of the vertex rows (KP false) or of the centroid rows below (KP true: x the centroid of
 // triangle trow[i], the kernel n . (x - y)/|x - y|^3 in place of 1/|x - y|).
-// One wave: rows i0 + lane, columns j0 .. j0 + 15 (column group cg).  The wave walks the
+// One wave: rows i0 + lane, the 16 columns of column group cg (neighbouring vertices).  The wave walks the
 // distinct triangles that hold a vertex of the group (ascending), evaluates the 7-point
 // rule once per triangle and adds each hat whose vertex is in the group into that column's
-// LDS slot, so a pair costs about two visits instead of one per vertex of the triangle.
+// LDS slot, so a pair costs about 1.7 visits instead of one per vertex of the triangle.
 // The four waves of a block take the same columns on four row tiles, so three of four
 // record loads hit the scalar cache.  1-D grid of n_rt x n_cg blocks (row tiles of 256
 // rows, n_cg a multiple of 8): blocks are dealt to the 8 XCDs in turn, so block b runs on
 // XCD b % 8, and each XCD sweeps all row tiles of one column group before the next,
-// keeping that group's records in its own L2.
+// keeping that group's records in its own L2; it takes consecutive groups, whose columns
+// share lines of the matrix.
 // The rule is the form about the centroid (density one in the records).  Corner k's hat is 1/3 at the
 // centroid and 1/3 + s (delta_ik - 1/3) at the node on corner i's median (s the median's scale, s rho
 // on the second orbit), so with f_q the kernel at the nodes, U = sum w f and h_i = w_1 f_1i + rho w_2
@@ -164,6 +163,7 @@ __global__ __launch_bounds__(256) void k_nodal_regular(int64_t nr, int64_t nv, i
                                                        const double* __restrict__ vert,
                                                        const int32_t* __restrict__ trow,
                                                        const int32_t* __restrict__ tri,
+                                                       const int32_t* __restrict__ grp_col,
                                                        const int32_t* __restrict__ grp_ptr,
                                                        const int32_t* __restrict__ grp_tri,
                                                        const uint32_t* __restrict__ grp_loc,
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256) void k_nodal_regular(int64_t nr, int64_t nv, i
     __shared__ double tile[4][NODAL_COLS][65];   // padded: the row-segment reads stride 65
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t b = blockIdx.x, xcd = b & 7, slot = b >> 3;
-    const int64_t cg = (slot / n_rt) * 8 + xcd, rt = slot % n_rt;
+    const int64_t cg = xcd * ((int64_t)gridDim.x / (8 * n_rt)) + slot / n_rt, rt = slot % n_rt;
     const int64_t i0 = (rt * 4 + wv) * 64;
     const int64_t i = i0 + lane;
     const int64_t ic = i < nr ? i : nr - 1;
@@ -267,11 +267,13 @@ __global__ __launch_bounds__(256) void k_nodal_regular(int64_t nr, int64_t nv, i
         }
     }
     __syncthreads();
+    const int cc = lane % NODAL_COLS;
+    if (j0 + cc >= nv) return;
+    const int64_t jj = grp_col[j0 + cc];
 #pragma unroll 4
-    for (int s = 0; s < 16; ++s) {
-        const int r = (lane >> 4) + 4 * s, cc = lane & 15;
-        const int64_t ii = i0 + r, jj = j0 + cc;
-        if (ii < nr && jj < nv) A[ii * ld + jj] = (T)tile[wv][cc][r];
+    for (int s = 0; s < NODAL_COLS; ++s) {
+        const int r = lane / NODAL_COLS + 64 / NODAL_COLS * s;
+        if (i0 + r < nr) A[(i0 + r) * ld + jj] = (T)tile[wv][cc][r];
     }
 }
 
@@ -279,30 +281,32 @@ __global__ __launch_bounds__(256) void k_nodal_regular(int64_t nr, int64_t nv, i
 // that every point within eta R of a circumcentre of the chunk lies in the ball
 // (radius = max |cc - centre| + eta R), so a ball of rows apart from it by more
 // than the two radii makes only regular pairs with the chunk.
+// One wave per chunk.
 __global__ __launch_bounds__(256) void k_nodal_chunk_bounds(int64_t N, int64_t Np, const double* __restrict__ far64,
                                                             double* __restrict__ cb) {
-    const int64_t ch = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t t0 = ch * 64;
-    if (t0 >= N) return;
-    const int64_t t1 = t0 + 64 < N ? t0 + 64 : N;
-    double m0 = 0.0, m1 = 0.0, m2 = 0.0;
-    for (int64_t t = t0; t < t1; ++t) {
-        m0 += far64[(int64_t)(FR_CC + 0) * Np + t];
-        m1 += far64[(int64_t)(FR_CC + 1) * Np + t];
-        m2 += far64[(int64_t)(FR_CC + 2) * Np + t];
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, ch = t >> 6;
+    if (ch * 64 >= N) return;   // whole waves
+    const bool live = t < N;
+    double c[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c[k] = live ? far64[(int64_t)(FR_CC + k) * Np + t] : 0.0;
+    const double inv = 1.0 / (double)(N - ch * 64 < 64 ? N - ch * 64 : 64);
+    double d2 = 0.0, m[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        m[k] = wave_sum(c[k]) * inv;
+        d2 += (c[k] - m[k]) * (c[k] - m[k]);
     }
-    const double inv = 1.0 / (double)(t1 - t0);
-    m0 *= inv; m1 *= inv; m2 *= inv;
-    double r = 0.0;
-    for (int64_t t = t0; t < t1; ++t) {
-        const double d0 = far64[(int64_t)(FR_CC + 0) * Np + t] - m0, d1 = far64[(int64_t)(FR_CC + 1) * Np + t] - m1;
-        const double d2 = far64[(int64_t)(FR_CC + 2) * Np + t] - m2;
-        const double e = sqrt(d0 * d0 + d1 * d1 + d2 * d2) + sqrt(far64[(int64_t)FR_RR * Np + t]);
-        r = e > r ? e : r;
+    double r = live ? sqrt(d2) + sqrt(far64[(int64_t)FR_RR * Np + t]) : 0.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const double v = __shfl_xor(r, o, 64);
+        r = v > r ? v : r;
     }
-    cb[4 * ch] = m0;
-    cb[4 * ch + 1] = m1;
-    cb[4 * ch + 2] = m2;
+    if ((threadIdx.x & 63) != 0) return;
+    cb[4 * ch] = m[0];
+    cb[4 * ch + 1] = m[1];
+    cb[4 * ch + 2] = m[2];
     cb[4 * ch + 3] = r;
 }
 
@@ -317,17 +321,18 @@ constexpr int NN_H = 256;   // slots of a wave's column table (192 columns at mo
 // the round's distinct columns go into a table in LDS, and each column's lane adds its hats in the
 // triangles' order, rounding to the stored type after each, as one lane walking the triangles would
 // (so FP32 rows hold the same bits).  One lane per row, the earlier form, ran each closed form for a
-// few lanes at a time and had 141 waves for 9,036 rows: 4.0 ms, where this takes 0.2.
+// few lanes at a time and had 141 waves for 9,036 rows: 4.0 ms, where this takes 0.24 (0.39 with 192
+// registers, two waves a SIMD, one chunk of triangles at a time and every column walking the whole round).
 template <class T, bool KP>
-__global__ __launch_bounds__(64) void k_nodal_near(int64_t nr, int64_t ld, int64_t N, int64_t Np,
+__global__ __launch_bounds__(64, 3) void k_nodal_near(int64_t nr, int64_t ld, int64_t N, int64_t Np,
                                                    const int32_t* __restrict__ row_order,
                                                    const double* __restrict__ vert, const int32_t* __restrict__ trow,
                                                    const int32_t* __restrict__ tri, const double* __restrict__ far64,
                                                    const double* __restrict__ cb, const double* __restrict__ tri64,
                                                    T* __restrict__ A) {
-    __shared__ int32_t lt[128];            // near triangles waiting, ascending
+    __shared__ int32_t lt[192];            // near triangles waiting, ascending
     __shared__ int32_t hkey[NN_H], used[192], s_used;
-    __shared__ double hval[NN_H];
+    __shared__ uint32_t hits[2][NN_H];     // a column's triangles of the round
     __shared__ uint32_t eslot[64];         // slots of a triangle's three columns, 8 bits each
     __shared__ double ev[3][64];
     const int lane = threadIdx.x;
@@ -343,8 +348,22 @@ __global__ __launch_bounds__(64) void k_nodal_near(int64_t nr, int64_t ld, int64
     T* row = A + i * ld;
     const int64_t nch = (N + 63) >> 6;
     int m = 0;             // triangles waiting
-    int64_t cbase = -64, t0 = 0;
+    int64_t cbase = -64;
     uint64_t todo = 0;     // chunks of [cbase, cbase + 64) within reach, not yet classified
+    auto near_of = [&](int64_t t) {   // t >= N: some triangle's answer
+        t = t < N ? t : N - 1;
+        const double c0 = far64[(int64_t)(FR_CC + 0) * Np + t], c1 = far64[(int64_t)(FR_CC + 1) * Np + t],
+                     c2 = far64[(int64_t)(FR_CC + 2) * Np + t], rr = far64[(int64_t)FR_RR * Np + t];
+        if constexpr (KP) {
+            return !is_regular(x0 - c0, x1 - c1, x2 - c2, rr) && t != own;
+        } else {
+            const int32_t v0 = tri[3 * t], v1 = tri[3 * t + 1], v2 = tri[3 * t + 2];
+            return !is_regular(x0 - c0, x1 - c1, x2 - c2, rr) || v0 == i || v1 == i || v2 == i;
+        }
+    };
+    auto below = [&](uint64_t w) {   // bits of w below this lane
+        return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(w >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)w, 0u));
+    };
     for (;;) {
         while (m < 64) {
             while (todo == 0 && cbase + 64 < nch) {
@@ -360,29 +379,29 @@ __global__ __launch_bounds__(64) void k_nodal_near(int64_t nr, int64_t ld, int64
                 todo = __ballot(in);
             }
             if (todo == 0) break;
-            t0 = (cbase + __builtin_ctzll(todo)) * 64;
+            // two chunks at a time, their loads in flight together
+            const int64_t ta = (cbase + __builtin_ctzll(todo)) * 64 + lane;
             todo &= todo - 1;
-            const int64_t t = t0 + lane;
-            bool near = false;
-            if (t < N) {
-                near = !is_regular(x0 - far64[(int64_t)(FR_CC + 0) * Np + t], x1 - far64[(int64_t)(FR_CC + 1) * Np + t],
-                                   x2 - far64[(int64_t)(FR_CC + 2) * Np + t], far64[(int64_t)FR_RR * Np + t]);
-                if (KP)
-                    near = near && t != own;
-                else
-                    near = near || tri[3 * t] == i || tri[3 * t + 1] == i || tri[3 * t + 2] == i;
-            }
-            const uint64_t nm = __ballot(near);
-            if (near)
-                lt[m + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(nm >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)nm, 0u))] = (int32_t)t;
-            m += __popcll(nm);
+            const int64_t tb = todo != 0 ? (cbase + __builtin_ctzll(todo)) * 64 + lane : N;
+            todo &= todo - 1;   // 0 stays 0
+            bool na = near_of(ta), nb = near_of(tb);
+            na = na && ta < N;
+            nb = nb && tb < N;
+            const uint64_t ma = __ballot(na), mb = __ballot(nb);
+            if (na) lt[m + below(ma)] = (int32_t)ta;
+            m += __popcll(ma);
+            if (nb) lt[m + below(mb)] = (int32_t)tb;
+            m += __popcll(mb);
         }
         if (m == 0) break;
         const int n = m < 64 ? m : 64;
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < NN_H / 64; ++k) hkey[lane + 64 * k] = -1;
+        for (int k = 0; k < NN_H / 64; ++k) {
+            hkey[lane + 64 * k] = -1;
+            hits[0][lane + 64 * k] = 0;
+            hits[1][lane + 64 * k] = 0;
+        }
         if (lane == 0) s_used = 0;
         __syncthreads();
         if (lane < n) {
@@ -395,13 +414,11 @@ __global__ __launch_bounds__(64) void k_nodal_near(int64_t nr, int64_t ld, int64
                 uint32_t h = ((uint32_t)col * 2654435761u) >> 24;
                 for (;;) {   // fewer columns than slots: a free or equal one is found
                     const int32_t k = atomicCAS(&hkey[h], -1, col);
-                    if (k == -1) {
-                        hval[h] = (double)row[col];
-                        used[atomicAdd(&s_used, 1)] = (int32_t)h;
-                    }
+                    if (k == -1) used[atomicAdd(&s_used, 1)] = (int32_t)h;
                     if (k == -1 || k == col) break;
                     h = (h + 1) & (NN_H - 1);
                 }
+                atomicOr(&hits[lane >> 5][h], 1u << (lane & 31));
                 slots |= h << (8 * c);
             }
             eslot[lane] = slots;
@@ -433,19 +450,23 @@ __global__ __launch_bounds__(64) void k_nodal_near(int64_t nr, int64_t ld, int64
         __syncthreads();
         for (int u = lane; u < s_used; u += 64) {
             const uint32_t h = (uint32_t)used[u];
-            double y = hval[h];
-            for (int e = 0; e < n; ++e) {
-                const uint32_t w = eslot[e];
-                if ((w & 0xffu) == h) y = (double)(T)(y + ev[0][e]);
-                else if (((w >> 8) & 0xffu) == h) y = (double)(T)(y + ev[1][e]);
-                else if (((w >> 16) & 0xffu) == h) y = (double)(T)(y + ev[2][e]);
+            T* out = row + hkey[h];
+            double y = (double)*out;
+            uint64_t w = (uint64_t)hits[1][h] << 32 | hits[0][h];
+            while (w) {
+                const int e = __builtin_ctzll(w);
+                w &= w - 1;
+                const uint32_t sl = eslot[e];
+                const int c = (sl & 0xffu) == h ? 0 : ((sl >> 8) & 0xffu) == h ? 1 : 2;
+                y = (double)(T)(y + ev[c][e]);
             }
-            row[hkey[h]] = (T)y;
+            *out = (T)y;
         }
         const int left = m - n;
-        const int32_t mv = lt[64 + lane];
+        const int32_t mv0 = lt[64 + lane], mv1 = lt[128 + lane];
         __syncthreads();   // and the row's entries are there for the next round's columns
-        if (lane < left) lt[lane] = mv;
+        if (lane < left) lt[lane] = mv0;
+        if (64 + lane < left) lt[64 + lane] = mv1;
         __syncthreads();
         m = left;
     }
@@ -710,14 +731,14 @@ static void nodal_assemble_t(bem_ctx* c, T* A, double* Atail, int64_t tail_row0)
     if (n_rt * n_cg > ((int64_t)1 << 31) - 1) throw Error(BEM_ERR_INVALID, "too many vertices for the LINEAR basis");
     launch_median_records(c, nullptr, c->ev_rec);
     hipLaunchKernelGGL((k_nodal_regular<T, false>), dim3((unsigned)(n_rt * n_cg)), dim3(256), 0, s, nv, nv, ld, n_rt,
-                       c->vert.as<double>(), (const int32_t*)nullptr, c->tri.as<int32_t>(), c->grp_ptr.as<int32_t>(),
-                       c->grp_tri.as<int32_t>(), c->grp_loc.as<uint32_t>(), c->ev_rec.as<double>(),
+                       c->vert.as<double>(), (const int32_t*)nullptr, c->tri.as<int32_t>(), c->grp_col.as<int32_t>(),
+                       c->grp_ptr.as<int32_t>(), c->grp_tri.as<int32_t>(), c->grp_loc.as<uint32_t>(), c->ev_rec.as<double>(),
                        c->tri64.as<double>(), A);
     BEM_CHECK_LAUNCH();
     const int64_t Np = (int64_t)(c->far64.bytes / (sizeof(double) * FAR_REC));
     const int64_t nch = ceil_div(c->N, 64);
     c->nodal_bounds.alloc(sizeof(double) * 4 * (size_t)nch);
-    hipLaunchKernelGGL(k_nodal_chunk_bounds, dim3((unsigned)ceil_div(nch, 256)), dim3(256), 0, s, c->N, Np,
+    hipLaunchKernelGGL(k_nodal_chunk_bounds, dim3((unsigned)ceil_div(c->N, 256)), dim3(256), 0, s, c->N, Np,
                        c->far64.as<double>(), c->nodal_bounds.as<double>());
     BEM_CHECK_LAUNCH();
     hipLaunchKernelGGL((k_nodal_near<T, false>), dim3((unsigned)(ceil_div(nv, 8) * 8)), dim3(64), 0, s, nv, ld, c->N, Np,
@@ -741,8 +762,8 @@ static void nodal_assemble_t(bem_ctx* c, T* A, double* Atail, int64_t tail_row0)
         if (n_rtc * n_cg > ((int64_t)1 << 31) - 1) throw Error(BEM_ERR_INVALID, "too many centroid rows");
         hipLaunchKernelGGL((k_nodal_regular<double, true>), dim3((unsigned)(n_rtc * n_cg)), dim3(256), 0, s, nc, nv, ld,
                            n_rtc, (const double*)nullptr, c->nod_trow.as<int32_t>(), c->tri.as<int32_t>(),
-                           c->grp_ptr.as<int32_t>(), c->grp_tri.as<int32_t>(), c->grp_loc.as<uint32_t>(),
-                           c->ev_rec.as<double>(), c->tri64.as<double>(), Kc);
+                           c->grp_col.as<int32_t>(), c->grp_ptr.as<int32_t>(), c->grp_tri.as<int32_t>(),
+                           c->grp_loc.as<uint32_t>(), c->ev_rec.as<double>(), c->tri64.as<double>(), Kc);
         BEM_CHECK_LAUNCH();
         hipLaunchKernelGGL((k_nodal_near<double, true>), dim3((unsigned)(ceil_div(nc, 8) * 8)), dim3(64), 0, s, nc, ld,
                            c->N, Np, (const int32_t*)nullptr, (const double*)nullptr, c->nod_trow.as<int32_t>(),
