@@ -132,82 +132,74 @@ __global__ __launch_bounds__(256) void k_gemm_f32_sum(const float* __restrict__ 
 // columns over one of GD_KS ranges of K.  Workgroups are dealt to the 8 XCDs round-robin, so with
 // the K range taken as blockIdx % GD_KS every block of one XCD works one K range: that range's
 // slice of Z (64 x K/8 doubles, 1.3 MB at 20k unknowns) stays in the XCD's L2 for all row blocks,
-// while each A entry is read from HBM once.  Per 32-wide k step the block stages a 64 x 32 tile of
-// A (FP32 entries widened) and a 64 x 32 tile of Z in LDS with row-contiguous loads (4 threads
-// cover a 256-byte row segment), the next step's tiles prefetched into registers; each wave then
-// runs 32 MFMAs with its operands read from LDS (a lane takes 4 consecutive k of its A row and of
-// 4 Z columns per 16 k).  The 64 x 64 partial tile is transposed through the same LDS and leaves
-// as column segments of 64 rows; k_gemm_f64_sum adds the K ranges in order.
-constexpr int GD_ROWS = 64, GD_KS = 8, GD_KC = 32, GD_PAD = 34;
+// while each A entry is read from HBM once.  A wave's rows are its own, so their entries (FP32 ones
+// widened) go from memory straight into its operand registers, a lane taking 4 consecutive k of its
+// row per 16 k (128-byte segments of a row), one 32-wide k step ahead; Z, which all waves share, is
+// staged in two 64 x 32 LDS tiles in turn, so a step has one barrier and runs 32 MFMAs a wave.
+// The partial tile is transposed through the same LDS and leaves as column segments of 64 rows;
+// k_gemm_f64_sum adds the K ranges in order.
+// Bound by the matrix cores: 7,713 x 7,744 FP64 entries times 64 vectors take 0.148 ms (51.6 TFLOP/s; 0.104 ms
+// at the rate of a large library product).  With A staged through LDS too, two barriers a step and
+// non-temporal loads it was 0.192 ms; non-temporal loads alone cost 6 % here, as a line is used by
+// two loads.  32 rows a wave (half the LDS reads, two waves a SIMD) take 0.153 ms.
+constexpr int GD_KS = 8, GD_KC = 32, GD_PAD = 34;
 
 template <typename TA>
-__global__ __launch_bounds__(256) void k_gemm_f64(const TA* __restrict__ A, int64_t lda, int64_t M, int64_t K,
-                                                  const double* __restrict__ Zt, int64_t ldz, int64_t kb_per, int KS,
-                                                  double* __restrict__ Ypart) {
-    // A and Z tiles, reused after the loop for the 64 x 65 output tile (4160 <= 4352 doubles)
+__global__ __launch_bounds__(256, 2) void k_gemm_f64(const TA* __restrict__ A, int64_t lda, int64_t M, int64_t K,
+                                                     const double* __restrict__ Zt, int64_t ldz, int64_t kb_per, int KS,
+                                                     double* __restrict__ Ypart) {
+    // the two Z tiles, reused after the loop for a 64 x 65 output tile (4160 <= 4352 doubles)
     __shared__ __attribute__((aligned(16))) double smem[2 * 64 * GD_PAD];
-    double(*As)[GD_PAD] = reinterpret_cast<double(*)[GD_PAD]>(smem);
-    double(*Bs)[GD_PAD] = reinterpret_cast<double(*)[GD_PAD]>(smem + 64 * GD_PAD);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int r = lane & 15, q4 = lane >> 4;   // row (A) / column (Z) within 16, k group 0..3
     const int64_t ks = blockIdx.x % KS, rb = blockIdx.x / KS;
-    const int64_t row0 = rb * GD_ROWS;
+    const int64_t row0 = rb * 64 + wv * 16;
     const int64_t kblocks = K / GD_KC;
     const int64_t kb0 = ks * kb_per, kb1 = kb0 + kb_per < kblocks ? kb0 + kb_per : kblocks;
-    // this thread's staging slot: A row / Z column sr, 8 doubles from sc
+    const int64_t ar = row0 + r < M ? row0 + r : M - 1;   // rows past M: read, never stored
+    const TA* __restrict__ Ap = A + ar * lda + 4 * q4;
+    // this thread's staging slot: Z column sr, 8 doubles from sc
     const int sr = tid >> 2, sc = 8 * (tid & 3);
-    const int64_t ar = row0 + sr < M ? row0 + sr : M - 1;   // rows past M: read, never stored
-    const TA* __restrict__ Ap = A + ar * lda + sc;
     const double* __restrict__ Zp = Zt + (int64_t)sr * ldz + sc;
-    double ra[8], rz[8];
-    auto load = [&](int64_t k) {
-        if (sizeof(TA) == 4) {
-            const f4v x0 = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(Ap + k));
-            const f4v x1 = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(Ap + k) + 1);
+    double a0[8], a1[8];
+    d2v rz[4];
+    auto load_a = [&](int64_t k, double (&x)[8]) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                ra[e] = x0[e];
-                ra[4 + e] = x1[e];
-            }
-        } else {
+        for (int u = 0; u < 2; ++u) {
+            if constexpr (sizeof(TA) == 4) {
+                const f4v v = *reinterpret_cast<const f4v*>(Ap + k + 16 * u);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const d2v x = __builtin_nontemporal_load(reinterpret_cast<const d2v*>(Ap + k) + e);
-                ra[2 * e] = x[0];
-                ra[2 * e + 1] = x[1];
+                for (int e = 0; e < 4; ++e) x[4 * u + e] = v[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const d2v v = reinterpret_cast<const d2v*>(Ap + k + 16 * u)[e];
+                    x[4 * u + 2 * e] = v[0];
+                    x[4 * u + 2 * e + 1] = v[1];
+                }
             }
         }
+    };
+    auto load_z = [&](int64_t k) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const d2v z = reinterpret_cast<const d2v*>(Zp + k)[e];
-            rz[2 * e] = z[0];
-            rz[2 * e + 1] = z[1];
-        }
+        for (int e = 0; e < 4; ++e) rz[e] = reinterpret_cast<const d2v*>(Zp + k)[e];
+    };
+    auto put_z = [&](int buf) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) *reinterpret_cast<d2v*>(&smem[(buf * 64 + sr) * GD_PAD + sc + 2 * e]) = rz[e];
     };
     d4v acc[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[c] = (d4v){0.0, 0.0, 0.0, 0.0};
-    if (kb0 < kb1) load(kb0 * GD_KC);
-    for (int64_t kb = kb0; kb < kb1; ++kb) {
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            *reinterpret_cast<d2v*>(&As[sr][sc + 2 * e]) = (d2v){ra[2 * e], ra[2 * e + 1]};
-            *reinterpret_cast<d2v*>(&Bs[sr][sc + 2 * e]) = (d2v){rz[2 * e], rz[2 * e + 1]};
-        }
-        __syncthreads();
-        if (kb + 1 < kb1) load((kb + 1) * GD_KC);
+    auto multiply = [&](int buf, const double (&x)[8]) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int kk = 16 * u + 4 * q4;
-            const d2v a0 = *reinterpret_cast<const d2v*>(&As[16 * wv + r][kk]);
-            const d2v a1 = *reinterpret_cast<const d2v*>(&As[16 * wv + r][kk + 2]);
-            const double a[4] = {a0[0], a0[1], a1[0], a1[1]};
             double b[4][4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const d2v b0 = *reinterpret_cast<const d2v*>(&Bs[16 * c + r][kk]);
-                const d2v b1 = *reinterpret_cast<const d2v*>(&Bs[16 * c + r][kk + 2]);
+                const d2v* z = reinterpret_cast<const d2v*>(&smem[(buf * 64 + 16 * c + r) * GD_PAD + kk]);
+                const d2v b0 = z[0], b1 = z[1];
                 b[c][0] = b0[0];
                 b[c][1] = b0[1];
                 b[c][2] = b1[0];
@@ -217,21 +209,42 @@ __global__ __launch_bounds__(256) void k_gemm_f64(const TA* __restrict__ A, int6
             for (int s4 = 0; s4 < 4; ++s4)
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s4], b[c][s4], acc[c], 0, 0, 0);
+                    acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[4 * u + s4], b[c][s4], acc[c], 0, 0, 0);
+        }
+    };
+    // step kb: Z of kb + 1 (in registers) goes to the other tile, Z of kb + 2 and A of kb + 1 are requested,
+    // then the step's products run; the barrier ends the step for both tiles
+    auto at = [&](int64_t kb) { return (kb < kb1 ? kb : kb1 - 1) * GD_KC; };
+    auto step = [&](int64_t kb, int buf, const double (&x)[8], double (&next)[8]) {
+        put_z(buf ^ 1);
+        load_z(at(kb + 2));
+        load_a(at(kb + 1), next);
+        multiply(buf, x);
+        __syncthreads();
+    };
+    if (kb0 < kb1) {
+        load_z(at(kb0));
+        load_a(at(kb0), a0);
+        put_z(0);
+        load_z(at(kb0 + 1));
+        __syncthreads();
+        for (int64_t kb = kb0; kb < kb1; kb += 2) {
+            step(kb, 0, a0, a1);
+            if (kb + 1 < kb1) step(kb + 1, 1, a1, a0);   // the same for the whole block
         }
     }
-    __syncthreads();   // every wave is done with the tiles before they are overwritten
-    double(*tile)[GD_ROWS + 1] = reinterpret_cast<double(*)[GD_ROWS + 1]>(smem);
+    __syncthreads();
+    double(*tile)[65] = reinterpret_cast<double(*)[65]>(smem);
+    double* out = Ypart + ks * 64 * M;
     // accumulator element v of lane (r, q4): row 4 v + q4 (+16 wv), column r (+16 c)
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int v = 0; v < 4; ++v) tile[16 * c + r][16 * wv + 4 * v + q4] = acc[c][v];
     __syncthreads();
-    double* out = Ypart + ks * 64 * M;
-    for (int e = threadIdx.x; e < 64 * GD_ROWS; e += 256) {
-        const int col = e / GD_ROWS, row = e % GD_ROWS;
-        const int64_t i = row0 + row;
+    for (int e = tid; e < 64 * 64; e += 256) {
+        const int col = e >> 6, row = e & 63;
+        const int64_t i = rb * 64 + row;
         if (i < M) out[(int64_t)col * M + i] = tile[col][row];
     }
 }
@@ -320,7 +333,7 @@ void launch_gemm_f64(bem_ctx* c, const void* A, bool a_is_f32, int64_t lda, int6
     if (M <= 0) return;
     if (K % GD_KC != 0 || ldz % 2 != 0 || lda % 4 != 0) throw Error(BEM_ERR_INVALID, "gemm_f64 shape not padded");
     KTimer t(c, "gemm_f64");
-    const int64_t rb = ceil_div(M, GD_ROWS);
+    const int64_t rb = ceil_div(M, 64);
     const int64_t kblocks = K / GD_KC;
     int64_t KS = std::min<int64_t>(GD_KS, kblocks);
     const int64_t kb_per = ceil_div(kblocks, KS);
@@ -329,13 +342,14 @@ void launch_gemm_f64(bem_ctx* c, const void* A, bool a_is_f32, int64_t lda, int6
     c->gemm_part.alloc(sizeof(double) * (size_t)KS * 64 * M);
     double* part = c->gemm_part.as<double>();
     const dim3 grid((unsigned)(rb * KS));
+    auto go = [&](auto kernel, auto* a) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, c->stream, a, lda, M, K, Zt, ldz, kb_per, (int)KS, part);
+        BEM_CHECK_LAUNCH();
+    };
     if (a_is_f32)
-        hipLaunchKernelGGL((k_gemm_f64<float>), grid, dim3(256), 0, c->stream, (const float*)A, lda, M, K, Zt, ldz,
-                           kb_per, (int)KS, part);
+        go(k_gemm_f64<float>, (const float*)A);
     else
-        hipLaunchKernelGGL((k_gemm_f64<double>), grid, dim3(256), 0, c->stream, (const double*)A, lda, M, K, Zt, ldz,
-                           kb_per, (int)KS, part);
-    BEM_CHECK_LAUNCH();
+        go(k_gemm_f64<double>, (const double*)A);
     hipLaunchKernelGGL(k_gemm_f64_sum, dim3((unsigned)ceil_div(M, 256), (unsigned)ncols), dim3(256), 0, c->stream,
                        part, (int)KS, M, ncols, Y, ldy, (int)accumulate, alpha);
     BEM_CHECK_LAUNCH();
