@@ -66,10 +66,10 @@ struct HBuf {
         p = nullptr;
         bytes = 0;
     }
-    void alloc(size_t b) {
+    void alloc(size_t b, unsigned flags = hipHostMallocDefault) {
         if (b <= bytes && p) return;
         release();
-        BEM_HIP(hipHostMalloc(&p, b, hipHostMallocDefault));
+        BEM_HIP(hipHostMalloc(&p, b, flags));
         bytes = b;
     }
     template <class T> T* as() const { return static_cast<T*>(p); }
@@ -157,6 +157,8 @@ struct bem_ctx {
     bool assembled = false;
 
     // scratch
+    bem::HBuf gm_host;                     // Hessenberg columns of the iterations in flight, with their numbers
+    uint64_t gm_seq = 0;                   // number of the last iteration queued
     bem::DBuf gm_V, gm_w, gm_z, gm_h, gm_part, gm_x, gm_r, gm_b, gm_misc;
     bem::HBuf host_stage;
     bem::DBuf ev_rec, ev_part, ev_mask, ev_ptr, ev_col, ev_row, ev_tmp, tr_queue, lb_state, lb_part, lf_part, lf_loop, lf_cnt, lc_buf, lc_image;

@@ -3,8 +3,21 @@
 // twice, Givens rotations and a zero initial guess.  The Krylov basis,
 // the dot products and the updates live on the device in FP64; the host
 // keeps the (m+1) x m Hessenberg matrix and the rotations and reads one
-// column (j + 2 doubles) per iteration.  The mixed mode wraps GMRES on the
-// mixed operator in FP64 iterative refinement.
+// column (j + 2 doubles) per iteration.  The last kernel of an iteration puts
+// the column and the iteration's number into coherent host memory, and the
+// next iteration is queued before the host waits for it, unless the residuals
+// so far say that this one ends the solve (an iteration queued in vain costs
+// a product).  The mixed mode wraps GMRES on the mixed operator in FP64
+// iterative refinement.
+//
+// An iteration at small n is bound by its launches (2-3 us of work in each,
+// 4-5 us to queue one), so up to GM_SUM vector blocks the sums over a dot
+// product's partials are taken by the kernels that use them and the second
+// dot products by the first update: 5 launches where separate sums take 9.
+// Above it every block would read as many partials as vector entries.  1,280
+// unknowns, 13 iterations, with assembly and evaluation: 1.05 -> 0.56 ms;
+// 19,733 unknowns, 61 iterations: 31.0 -> 29.8 ms, of which 27.8 in the products.
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -44,63 +57,105 @@ __global__ __launch_bounds__(64) void k_reduce_parts(const double* __restrict__ 
     if (Hcol) Hcol[k] = accumulate ? Hcol[k] + s : s;
 }
 
-// w -= sum_k h[k] V[k]
-__global__ __launch_bounds__(256) void k_orth_update(const double* __restrict__ V, int64_t vstride, int64_t n,
-                                                     int kcount, const double* __restrict__ h, double* __restrict__ w) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    double s = w[i];
-    for (int k = 0; k < kcount; ++k) s -= h[k] * V[k * vstride + i];
-    w[i] = s;
-}
+constexpr int64_t GM_SUM = 128;   // vector blocks of 256 (see the head of the file)
 
-// the second orthogonalisation pass with the block partials of |w|^2 of its output: one element
-// per thread and block b covering [256 b, 256 b + 256), the partition k_dots takes when its G
-// blocks cover n at one element per thread, so the norm is the same to the bit
-__global__ __launch_bounds__(256) void k_orth_update_norm(const double* __restrict__ V, int64_t vstride, int64_t n,
-                                                          int kcount, const double* __restrict__ h,
-                                                          double* __restrict__ w, double* __restrict__ part) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    double s = 0.0;
-    if (i < n) {
-        s = w[i];
-        for (int k = 0; k < kcount; ++k) s -= h[k] * V[k * vstride + i];
-        w[i] = s;
+// w -= sum_k h[k] V[k], 256 elements a block, the products of a block dealt to four groups of 256
+// threads (and its sums to 16 waves): a launch has few blocks, and their chains of loads are what
+// it takes.  SUM: h[k] is the sum of the partials src[k G ..], taken by every block in the same
+// order, and block 0 adds it to Hcol[k] (or sets it); else h = src.
+// dots: the partials of V[k] . w of the result, dots[k gridDim.x + block]; norm: those of |w|^2.
+template <bool SUM>
+__global__ __launch_bounds__(1024) void k_orth(const double* __restrict__ V, int64_t vstride, int64_t n, int kcount,
+                                               const double* __restrict__ src, int G, double* __restrict__ Hcol,
+                                               int accumulate, double* __restrict__ w, double* __restrict__ dots,
+                                               double* __restrict__ norm) {
+    __shared__ double hl[256], wl[256], red[3][256];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, e = tid & 255, q = tid >> 8;
+    const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + e;
+    double s = (q == 0 && i < n) ? w[i] : 0.0;
+    for (int k0 = 0; k0 < kcount; k0 += 256) {
+        const int nk = kcount - k0 < 256 ? kcount - k0 : 256;
+        if constexpr (SUM) {
+            for (int k = wv; k < nk; k += 16) {
+                double a = 0.0;
+                for (int b = lane; b < G; b += 64) a += src[(int64_t)(k0 + k) * G + b];
+                a = wave_sum(a);
+                if (lane == 0) {
+                    hl[k] = a;
+                    if (blockIdx.x == 0) Hcol[k0 + k] = accumulate ? Hcol[k0 + k] + a : a;
+                }
+            }
+        } else {
+            if (tid < nk) hl[tid] = src[k0 + tid];
+        }
+        __syncthreads();
+        if (i < n) {
+#pragma unroll 8
+            for (int k = q; k < nk; k += 4) s -= hl[k] * V[(int64_t)(k0 + k) * vstride + i];
+        }
+        __syncthreads();
     }
-    double q = fma(s, s, 0.0);
-    q = wave_sum(q);
-    __shared__ double red[4];
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = q;
+    if (q > 0) red[q - 1][e] = s;
     __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (q == 0) {
+        s = (s + red[0][e]) + (red[1][e] + red[2][e]);
+        if (i < n) w[i] = s;
+        wl[e] = s;   // 0 past the end
+    }
+    __syncthreads();
+    if (dots) {
+        for (int k = wv; k < kcount; k += 16) {
+            const double* v = V + (int64_t)k * vstride + i0;
+            double a = 0.0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (i0 + 64 * c + lane < n) a = fma(v[64 * c + lane], wl[64 * c + lane], a);
+            a = wave_sum(a);
+            if (lane == 0) dots[(int64_t)k * gridDim.x + blockIdx.x] = a;
+        }
+    }
+    if (norm && wv == 0) {
+        double a = 0.0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) a = fma(wl[64 * c + lane], wl[64 * c + lane], a);
+        a = wave_sum(a);
+        if (lane == 0) norm[blockIdx.x] = a;
+    }
 }
 
-// the next Krylov vector out = w / (*nrm) and the product's input z = out / d of the next
-// iteration (both left untouched if the norm is zero)
-__global__ __launch_bounds__(256) void k_scale_div(const double* __restrict__ w, const double* __restrict__ nrm,
-                                                   const double* __restrict__ d, int64_t n, double* __restrict__ out,
-                                                   double* __restrict__ z) {
+// The next Krylov vector out = w / |w| and the product's input z = out / d of the next iteration
+// (both left untouched if the norm is zero).  |w|: from the NP partials of its square, or *nrm (NP = 0).
+// host: block 0 hands the column Hcol[0..j], |w| and then `id` to the host.
+__global__ __launch_bounds__(256) void k_scale_div(const double* __restrict__ w, const double* __restrict__ parts, int NP,
+                                                   const double* __restrict__ nrm, const double* __restrict__ d,
+                                                   int64_t n, double* __restrict__ out, double* __restrict__ z,
+                                                   const double* __restrict__ Hcol, int j, double* __restrict__ host,
+                                                   uint64_t* flag, uint64_t id) {
+    __shared__ double vl;
+    if (threadIdx.x < 64) {
+        double a = 0.0;
+        if (NP > 0) {
+            for (int b = threadIdx.x; b < NP; b += 64) a += parts[b];
+            a = sqrt(wave_sum(a));
+        } else {
+            a = *nrm;
+        }
+        if (threadIdx.x == 0) vl = a;
+    }
+    __syncthreads();
+    const double v = vl;
+    if (host && blockIdx.x == 0) {
+        for (int k = threadIdx.x; k <= j; k += 256) host[k] = Hcol[k];
+        if (threadIdx.x == 0) host[j + 1] = v;
+        __threadfence_system();
+        __syncthreads();
+        if (threadIdx.x == 0) __hip_atomic_store(flag, id, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const double v = *nrm;
     if (i >= n || v == 0.0) return;
     const double o = w[i] / v;
     out[i] = o;
     z[i] = o / d[i];
-}
-
-// out = w / (*nrm) (left untouched if the norm is zero)
-__global__ __launch_bounds__(256) void k_scale_by_norm(const double* __restrict__ w, const double* __restrict__ nrm,
-                                                       int64_t n, double* __restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const double v = *nrm;
-    if (i >= n || v == 0.0) return;
-    out[i] = w[i] / v;
-}
-
-__global__ __launch_bounds__(256) void k_div_diag(const double* __restrict__ v, const double* __restrict__ d, int64_t n,
-                                                  double* __restrict__ z) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) z[i] = v[i] / d[i];
 }
 
 // r = b - Ax
@@ -140,8 +195,10 @@ struct Work {
     bem_ctx* c;
     int64_t n, vs;   // length and padded stride of Krylov vectors
     int m, G;
-    double *V, *w, *z, *h, *part, *Hcol, *misc;
+    double *V, *w, *z, *h, *part, *part2, *Hcol, *misc;
     double* host;    // pinned host staging
+    double* col;     // two columns in coherent host memory,
+    uint64_t* flag;  // and the numbers of the iterations that filled them
     hipStream_t s;
     bool transpose = false;   // solve with A^T (same Jacobi diagonal)
     dim3 g1() const { return dim3((unsigned)ceil_div(n, 256)); }
@@ -160,6 +217,68 @@ double host_norm(Work& W, const double* v) {
     BEM_HIP(hipMemcpyAsync(W.host, W.misc, sizeof(double), hipMemcpyDeviceToHost, W.s));
     BEM_HIP(hipStreamSynchronize(W.s));
     return W.host[0];
+}
+
+// Queue iteration j: w = A z, orthogonalised twice against V[0..j], V[j + 1] and the next z from it, its
+// column to the host.  Returns the iteration's number.
+uint64_t queue_iteration(Work& W, int j) {
+    bem_ctx* c = W.c;
+    const int64_t n = W.n;
+    const int GB = (int)ceil_div(n, 256);
+    const int kc = j + 1;
+    KTimer tj(c, "gmres_iter");
+    if (W.transpose)
+        launch_matvec_t(c, W.z, W.w, W.s);
+    else
+        launch_matvec(c, W.z, W.w, W.s);
+    KTimer to(c, "gmres_ortho");
+    const bool sum = GB <= GM_SUM;
+    // blocks per dot product: one element per thread, fewer where there are many products
+    const int G = std::min(W.G, std::max(8, 1024 / kc));
+    hipLaunchKernelGGL(k_dots, dim3(G, kc), dim3(256), 0, W.s, W.V, W.vs, n, W.w, W.part, G);
+    BEM_CHECK_LAUNCH();
+    double* none = nullptr;
+    if (sum) {
+        hipLaunchKernelGGL(k_orth<true>, dim3(GB), dim3(1024), 0, W.s, W.V, W.vs, n, kc, W.part, G, W.Hcol, 0, W.w,
+                           W.part2, none);
+        BEM_CHECK_LAUNCH();
+        hipLaunchKernelGGL(k_orth<true>, dim3(GB), dim3(1024), 0, W.s, W.V, W.vs, n, kc, W.part2, GB, W.Hcol, 1, W.w,
+                           none, W.part);
+        BEM_CHECK_LAUNCH();
+    } else {
+        for (int pass = 0; pass < 2; ++pass) {
+            if (pass == 1) {
+                hipLaunchKernelGGL(k_dots, dim3(G, kc), dim3(256), 0, W.s, W.V, W.vs, n, W.w, W.part, G);
+                BEM_CHECK_LAUNCH();
+            }
+            hipLaunchKernelGGL(k_reduce_parts, dim3((unsigned)kc), dim3(64), 0, W.s, W.part, G, kc, W.h, W.Hcol, pass, 0);
+            BEM_CHECK_LAUNCH();
+            hipLaunchKernelGGL(k_orth<false>, dim3(GB), dim3(1024), 0, W.s, W.V, W.vs, n, kc, W.h, 0, W.Hcol, 0, W.w,
+                               none, pass == 1 ? W.part2 : none);
+            BEM_CHECK_LAUNCH();
+        }
+        hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(64), 0, W.s, W.part2, GB, 1, W.Hcol + kc, none, 0, 1);
+        BEM_CHECK_LAUNCH();
+    }
+    const uint64_t id = ++c->gm_seq;
+    hipLaunchKernelGGL(k_scale_div, dim3(GB), dim3(256), 0, W.s, W.w, W.part, sum ? GB : 0, W.Hcol + kc, c->diag.as<double>(),
+                       n, W.V + (int64_t)kc * W.vs, W.z, W.Hcol, j, W.col + (j & 1) * (W.m + 2), W.flag + (j & 1), id);
+    BEM_CHECK_LAUNCH();
+    return id;
+}
+
+// Waits until iteration `id` (with column slot) has handed its column over; errors of the stream are raised.
+void wait_iteration(Work& W, int slot, uint64_t id) {
+    for (int64_t spin = 1;; ++spin) {
+        if (__atomic_load_n(W.flag + slot, __ATOMIC_ACQUIRE) >= id) return;
+        if ((spin & 0xffff) == 0) {
+            const hipError_t e = hipStreamQuery(W.s);
+            if (e == hipErrorNotReady) continue;
+            BEM_HIP(e);
+            if (__atomic_load_n(W.flag + slot, __ATOMIC_ACQUIRE) >= id) return;
+            throw Error(BEM_ERR_HIP, "GMRES iteration ended without its column");
+        }
+    }
 }
 
 // One GMRES solve of A x = b (x overwritten; zero initial guess unless keep_x).
@@ -200,60 +319,23 @@ int gmres_core(Work& W, const double* b, double* x, double tol, int max_iter, in
             break;
         }
         if (iters >= max_iter) break;
-        hipLaunchKernelGGL(k_scale_by_norm, W.g1(), dim3(256), 0, W.s, W.V, W.misc, n, W.V);
+        hipLaunchKernelGGL(k_scale_div, W.g1(), dim3(256), 0, W.s, W.V, W.misc, 0, W.misc, d, n, W.V, W.z, W.Hcol, 0,
+                           (double*)nullptr, (uint64_t*)nullptr, (uint64_t)0);
         BEM_CHECK_LAUNCH();
         std::fill(g.begin(), g.end(), 0.0);
         std::fill(H.begin(), H.end(), 0.0);
         g[0] = beta;
         int jend = 0;
-        // the norm's block partials from the second orthogonalisation pass and the next product's
-        // input from the scaling, when the dot products' blocks cover w at one element per thread
-        const bool fused = W.G == ceil_div(n, 256);
+        uint64_t id = queue_iteration(W, 0), id_next = 0;
+        double r_last = relres, r_prev = relres;
         for (int j = 0; j < m; ++j) {
-            KTimer tj(c, "gmres_iter");
-            double* Vj = W.V + (int64_t)j * W.vs;
-            if (j == 0 || !fused) {   // else the scaling that made V[j] also wrote z
-                hipLaunchKernelGGL(k_div_diag, W.g1(), dim3(256), 0, W.s, Vj, d, n, W.z);
-                BEM_CHECK_LAUNCH();
-            }
-            if (W.transpose)
-                launch_matvec_t(c, W.z, W.w, W.s);
-            else
-                launch_matvec(c, W.z, W.w, W.s);
-            {
-                KTimer to(c, "gmres_ortho");
-                for (int pass = 0; pass < 2; ++pass) {
-                    hipLaunchKernelGGL(k_dots, dim3(W.G, j + 1), dim3(256), 0, W.s, W.V, W.vs, n, W.w, W.part, W.G);
-                    BEM_CHECK_LAUNCH();
-                    hipLaunchKernelGGL(k_reduce_parts, dim3((unsigned)(j + 1)), dim3(64), 0, W.s, W.part,
-                                       W.G, j + 1, W.h, W.Hcol, pass, 0);
-                    BEM_CHECK_LAUNCH();
-                    if (fused && pass == 1)
-                        hipLaunchKernelGGL(k_orth_update_norm, W.g1(), dim3(256), 0, W.s, W.V, W.vs, n, j + 1, W.h,
-                                           W.w, W.part);
-                    else
-                        hipLaunchKernelGGL(k_orth_update, W.g1(), dim3(256), 0, W.s, W.V, W.vs, n, j + 1, W.h, W.w);
-                    BEM_CHECK_LAUNCH();
-                }
-                if (fused) {
-                    hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(64), 0, W.s, W.part, W.G, 1, W.Hcol + j + 1,
-                                       (double*)nullptr, 0, 1);
-                    BEM_CHECK_LAUNCH();
-                } else {
-                    device_norm(W, W.w, W.Hcol + j + 1);
-                }
-                if (fused && j + 1 < m)
-                    hipLaunchKernelGGL(k_scale_div, W.g1(), dim3(256), 0, W.s, W.w, W.Hcol + j + 1, d, n,
-                                       W.V + (int64_t)(j + 1) * W.vs, W.z);
-                else
-                    hipLaunchKernelGGL(k_scale_by_norm, W.g1(), dim3(256), 0, W.s, W.w, W.Hcol + j + 1, n,
-                                       W.V + (int64_t)(j + 1) * W.vs);
-                BEM_CHECK_LAUNCH();
-            }
-            BEM_HIP(hipMemcpyAsync(W.host, W.Hcol, sizeof(double) * (j + 2), hipMemcpyDeviceToHost, W.s));
-            BEM_HIP(hipStreamSynchronize(W.s));
-            for (int k = 0; k <= j + 1; ++k) H[(size_t)k * m + j] = W.host[k];
-            const double hn = W.host[j + 1];
+            // the residual this iteration leads to if it falls by the last one's factor
+            const bool more = j + 1 < m && iters + 1 < max_iter, ahead = more && r_last * (r_last / r_prev) > tol;
+            if (ahead) id_next = queue_iteration(W, j + 1);
+            wait_iteration(W, j & 1, id);
+            const double* col = W.col + (j & 1) * (W.m + 2);
+            for (int k = 0; k <= j + 1; ++k) H[(size_t)k * m + j] = col[k];
+            const double hn = col[j + 1];
             for (int k = 0; k < j; ++k) {
                 const double a = H[(size_t)k * m + j], bb = H[(size_t)(k + 1) * m + j];
                 H[(size_t)k * m + j] = cs[k] * a + sn[k] * bb;
@@ -269,7 +351,10 @@ int gmres_core(Work& W, const double* b, double* x, double tol, int max_iter, in
             g[j] = cs[j] * g[j];
             ++iters;
             jend = j + 1;
-            if (std::fabs(g[j + 1]) / bnorm <= tol || iters >= max_iter || hn == 0.0) break;
+            r_prev = r_last;
+            r_last = std::fabs(g[j + 1]) / bnorm;
+            if (r_last <= tol || iters >= max_iter || hn == 0.0) break;
+            id = ahead || !more ? id_next : queue_iteration(W, j + 1);
         }
         for (int k = jend - 1; k >= 0; --k) {
             double sacc = g[k];
@@ -301,7 +386,9 @@ static void setup_work(bem_ctx* c, Work& W) {
     c->gm_w.alloc(sizeof(double) * W.vs);
     c->gm_z.alloc(sizeof(double) * W.vs);
     c->gm_h.alloc(sizeof(double) * (W.m + 2) * 2);
-    c->gm_part.alloc(sizeof(double) * (size_t)W.G * (W.m + 1));
+    // dot partials; those of the second products (GB <= GM_SUM) or the norm's GB
+    const int64_t GB = ceil_div(c->n, 256), p1 = (int64_t)W.G * (W.m + 1);
+    c->gm_part.alloc(sizeof(double) * (size_t)(p1 + std::max(GB, std::min(GB, GM_SUM) * (W.m + 1))));
     c->gm_r.alloc(sizeof(double) * W.vs * 3);
     W.V = c->gm_V.as<double>();
     W.w = c->gm_w.as<double>();
@@ -309,8 +396,17 @@ static void setup_work(bem_ctx* c, Work& W) {
     W.h = c->gm_h.as<double>();
     W.Hcol = W.h + (W.m + 2);
     W.part = c->gm_part.as<double>();
+    W.part2 = W.part + p1;
     W.misc = c->gm_r.as<double>() + 2 * W.vs;
     W.host = c->host_stage.as<double>();
+    // coherent, so that the host sees a column while later kernels run; iteration numbers only grow
+    const size_t cols = 2 * (size_t)(W.m + 2);
+    if (c->gm_host.bytes < sizeof(double) * (cols + 2)) {
+        c->gm_host.alloc(sizeof(double) * (cols + 2), hipHostMallocCoherent);
+        std::fill_n(c->gm_host.as<uint64_t>(), cols + 2, (uint64_t)0);
+    }
+    W.flag = c->gm_host.as<uint64_t>();
+    W.col = c->gm_host.as<double>() + 2;
 }
 
 // A^T x = b (FP64 operator only): the adjoint solve of the gradient.
