@@ -141,6 +141,22 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// Hand-off to the host through coherent host memory while the kernel runs on: every thread's host_put()s,
+// host_done() by all of them, a barrier, then one thread's host_flag().  The stores are system-scope ones,
+// so waiting for them orders them before the flag; a system-scope fence would also write back the
+// L2's dirty lines, which the host does not read (10 us more where each of 64 blocks does it).
+__device__ __forceinline__ void host_put(double* p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void host_done() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void host_flag(uint64_t* p, uint64_t id) {
+    __hip_atomic_store(p, id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
 }  // namespace bem

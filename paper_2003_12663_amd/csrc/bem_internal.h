@@ -273,6 +273,7 @@ void launch_quad_pair_integrals(bem_ctx* c, int64_t P, const double* pts, const 
 void launch_near_duffy(bem_ctx* c, int64_t nnz, const int32_t* row, const int32_t* col, double* sf);
 // records of the 7-point rule about the centroid with the densities sol (or none), in B groups (geometry.hip)
 constexpr int NODAL_COLS = 16;   // columns of a group of the nodal basis's regular pass
+void gmres_host(bem_ctx* c, size_t words);
 void launch_median_records(bem_ctx* c, const double* sol, DBuf& out, int B = 1, int64_t P = 0);
 void launch_panel_points(bem_ctx* c, int64_t L, const int32_t* panel, const double* bary, double offset,
                          double* out);                                // geometry.hip

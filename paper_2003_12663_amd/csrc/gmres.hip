@@ -145,11 +145,11 @@ __global__ __launch_bounds__(256) void k_scale_div(const double* __restrict__ w,
     __syncthreads();
     const double v = vl;
     if (host && blockIdx.x == 0) {
-        for (int k = threadIdx.x; k <= j; k += 256) host[k] = Hcol[k];
-        if (threadIdx.x == 0) host[j + 1] = v;
-        __threadfence_system();
+        for (int k = threadIdx.x; k <= j; k += 256) host_put(host + k, Hcol[k]);
+        if (threadIdx.x == 0) host_put(host + j + 1, v);
+        host_done();
         __syncthreads();
-        if (threadIdx.x == 0) __hip_atomic_store(flag, id, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (threadIdx.x == 0) host_flag(flag, id);
     }
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n || v == 0.0) return;
@@ -375,6 +375,13 @@ int gmres_core(Work& W, const double* b, double* x, double tol, int max_iter, in
 
 }  // namespace
 
+// Coherent host memory of at least `words` 64-bit words: the host sees what a kernel stores there while
+// later kernels run.  Its first words hold iteration numbers, which only grow, and start at 0.
+void gmres_host(bem_ctx* c, size_t words) {
+    c->gm_host.alloc(sizeof(uint64_t) * words, hipHostMallocCoherent);
+    std::fill_n(c->gm_host.as<uint64_t>(), c->gm_host.bytes / sizeof(uint64_t), (uint64_t)0);
+}
+
 static void setup_work(bem_ctx* c, Work& W) {
     W.c = c;
     W.n = c->n;
@@ -399,12 +406,7 @@ static void setup_work(bem_ctx* c, Work& W) {
     W.part2 = W.part + p1;
     W.misc = c->gm_r.as<double>() + 2 * W.vs;
     W.host = c->host_stage.as<double>();
-    // coherent, so that the host sees a column while later kernels run; iteration numbers only grow
-    const size_t cols = 2 * (size_t)(W.m + 2);
-    if (c->gm_host.bytes < sizeof(double) * (cols + 2)) {
-        c->gm_host.alloc(sizeof(double) * (cols + 2), hipHostMallocCoherent);
-        std::fill_n(c->gm_host.as<uint64_t>(), cols + 2, (uint64_t)0);
-    }
+    gmres_host(c, 2 + 2 * (size_t)(W.m + 2));
     W.flag = c->gm_host.as<uint64_t>();
     W.col = c->gm_host.as<double>() + 2;
 }

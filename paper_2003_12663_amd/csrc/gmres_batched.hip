@@ -34,18 +34,15 @@ namespace {
 
 constexpr int BR = 64;   // right-hand sides per batch
 
-// Zt32/Zt64[r][i] and Zn64[i][r] from src[r * sstride + i] (divided by d[i] if given); zero padding
+// Zt32/Zt64[r][i] and Zn64[i][r] from src[r * sstride + i]; zero padding
 __global__ __launch_bounds__(256) void k_b_prep(const double* __restrict__ src, int64_t sstride, int nr, int64_t n,
-                                                int64_t ld, const double* __restrict__ d, float* __restrict__ zt32,
+                                                int64_t ld, float* __restrict__ zt32,
                                                 double* __restrict__ zt64, double* __restrict__ zn64) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int r = blockIdx.y;
     if (i >= ld) return;
     double v = 0.0;
-    if (r < nr && i < n) {
-        v = src[(int64_t)r * sstride + i];
-        if (d) v /= d[i];
-    }
+    if (r < nr && i < n) v = src[(int64_t)r * sstride + i];
     if (zt32) zt32[(int64_t)r * ld + i] = (float)v;
     if (zt64) zt64[(int64_t)r * ld + i] = v;
     if (zn64) zn64[i * BR + r] = v;
@@ -64,54 +61,137 @@ __global__ __launch_bounds__(256) void k_b_near(const int64_t* __restrict__ nptr
     if (r < nr) W[(int64_t)r * ld + i] += s;
 }
 
-// part[(r * m1 + k) * G + b] = sum over block b's slice of V[(r * m1 + k) * ld + i] * W[r * ld + i]
+// part[(r * m1 + k) * G + b] = sum over block b's slice of V[(r * m1 + k) * ld + i] * W[r * ld + i].
+// A block takes up to four k, so that W is read once for them and four loads of V are in flight
+// (one k a block: 26 us for 27 x 64 vectors of 7,713).
+constexpr int DOT_K = 4;
+
 __global__ __launch_bounds__(256) void k_b_dots(const double* __restrict__ V, int m1, int64_t ld, int64_t n,
-                                                const double* __restrict__ W, double* __restrict__ part, int G) {
-    const int k = blockIdx.y, r = blockIdx.z;
-    const double* v = V + ((int64_t)r * m1 + k) * ld;
+                                                int kcount, const double* __restrict__ W, double* __restrict__ part,
+                                                int G) {
+    const int k0 = blockIdx.y * DOT_K, r = blockIdx.z;
     const double* w = W + (int64_t)r * ld;
-    double s = 0.0;
-    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < n; t += (int64_t)G * 256) s = fma(v[t], w[t], s);
-    s = wave_sum(s);
-    __shared__ double red[4];
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    const double* v[DOT_K];
+    double s[DOT_K];
+#pragma unroll
+    for (int q = 0; q < DOT_K; ++q) {
+        v[q] = V + ((int64_t)r * m1 + (k0 + q < kcount ? k0 + q : k0)) * ld;
+        s[q] = 0.0;
+    }
+    if (k0 + 1 == kcount) {
+        for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < n; t += (int64_t)G * 256) s[0] = fma(v[0][t], w[t], s[0]);
+    } else {
+        for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < n; t += (int64_t)G * 256) {
+            const double x = w[t];
+#pragma unroll
+            for (int q = 0; q < DOT_K; ++q) s[q] = fma(v[q][t], x, s[q]);
+        }
+    }
+    __shared__ double red[DOT_K][4];
+#pragma unroll
+    for (int q = 0; q < DOT_K; ++q) {
+        s[q] = wave_sum(s[q]);
+        if ((threadIdx.x & 63) == 0) red[q][threadIdx.x >> 6] = s[q];
+    }
     __syncthreads();
-    if (threadIdx.x == 0) part[((int64_t)r * m1 + k) * G + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+    const int q = threadIdx.x;
+    if (q < DOT_K && k0 + q < kcount)
+        part[((int64_t)r * m1 + k0 + q) * G + blockIdx.x] = (red[q][0] + red[q][1]) + (red[q][2] + red[q][3]);
 }
 
-// h[r][k] = sum_b part; Hcol[r][k] (+)= h[r][k]; optional sqrt (norms)
-__global__ void k_b_reduce(const double* __restrict__ part, int G, int m1, int kcount, int nr, double* __restrict__ h,
-                           int hstride, double* __restrict__ Hcol, int accumulate, int take_sqrt) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= kcount * nr) return;
-    const int r = t / kcount, k = t % kcount;
+// nrm[r * nstride] = sqrt(sum_b part), one wave per vector
+__global__ __launch_bounds__(64) void k_b_norm(const double* __restrict__ part, int G, double* __restrict__ nrm,
+                                               int nstride) {
     double s = 0.0;
-    for (int b = 0; b < G; ++b) s += part[((int64_t)r * m1 + k) * G + b];
-    if (take_sqrt) s = sqrt(s);
-    h[r * hstride + k] = s;
-    if (Hcol) Hcol[r * hstride + k] = accumulate ? Hcol[r * hstride + k] + s : s;
+    for (int b = threadIdx.x; b < G; b += 64) s += part[(int64_t)blockIdx.x * G + b];
+    s = wave_sum(s);
+    if (threadIdx.x == 0) nrm[(int64_t)blockIdx.x * nstride] = sqrt(s);
 }
 
-// W[r] -= sum_k h[r][k] V[r][k]
+// W[r] -= sum_k h[r][k] V[r][k] with h[r][k] the sum of the G partials of k_b_dots, taken by every block in
+// the same order; block 0 of a vector sets Hcol[r][k] to it or adds it.  norm: also the partials of
+// |W[r]|^2 of the result, norm[r gridDim.x + block].  (A launch of its own for the sums took 5.7 us,
+// three times an iteration.)
 __global__ __launch_bounds__(256) void k_b_orth(const double* __restrict__ V, int m1, int64_t ld, int64_t n, int kcount,
-                                                const double* __restrict__ h, int hstride, double* __restrict__ W) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int r = blockIdx.y;
-    if (i >= n) return;
-    double s = W[(int64_t)r * ld + i];
-    for (int k = 0; k < kcount; ++k) s -= h[r * hstride + k] * V[((int64_t)r * m1 + k) * ld + i];
-    W[(int64_t)r * ld + i] = s;
+                                                const double* __restrict__ part, int G, double* __restrict__ Hcol,
+                                                int hstride, int accumulate, double* __restrict__ W,
+                                                double* __restrict__ norm) {
+    __shared__ double hl[256], red[4];
+    const int tid = threadIdx.x, r = blockIdx.y;
+    const int64_t i = (int64_t)blockIdx.x * 256 + tid;
+    double* w = W + (int64_t)r * ld;
+    double s = i < n ? w[i] : 0.0;
+    for (int k0 = 0; k0 < kcount; k0 += 256) {
+        const int nk = kcount - k0 < 256 ? kcount - k0 : 256;
+        for (int k = tid >> 3; k < ((nk + 31) & ~31); k += 32) {   // 8 lanes a sum
+            double a = 0.0;
+            if (k < nk)
+                for (int b = tid & 7; b < G; b += 8) a += part[((int64_t)r * m1 + k0 + k) * G + b];
+#pragma unroll
+            for (int o = 4; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+            if (k < nk && (tid & 7) == 0) {
+                hl[k] = a;
+                double* H = Hcol + (int64_t)r * hstride + k0 + k;
+                if (blockIdx.x == 0) *H = accumulate ? *H + a : a;
+            }
+        }
+        __syncthreads();
+        if (i < n) {
+            const double* v = V + ((int64_t)r * m1 + k0) * ld + i;
+#pragma unroll 8
+            for (int k = 0; k < nk; ++k) s -= hl[k] * v[(int64_t)k * ld];
+        }
+        __syncthreads();
+    }
+    if (i < n) w[i] = s;
+    if (!norm) return;
+    const double q = wave_sum(s * s);
+    if ((tid & 63) == 0) red[tid >> 6] = q;
+    __syncthreads();
+    if (tid == 0) norm[(int64_t)r * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// out[r] = W[r] / nrm[r * nstride] (untouched where the norm is zero)
-__global__ __launch_bounds__(256) void k_b_scale(const double* __restrict__ W, int64_t wstride,
-                                                 const double* __restrict__ nrm, int nstride, int64_t n,
-                                                 double* __restrict__ out, int64_t ostride) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// The next basis vectors out[r] = W[r] / |W[r]| and the next product's inputs out / d in the layouts asked for
+// (see k_b_prep; rows past nr and entries past n stay zero).  |W[r]|: from the NP partials of its square, or
+// nrm[r nstride] (NP = 0); where it is zero out[r] is left as it is.  col: block 0 of a vector hands its
+// column Hcol[r][0..j], |W[r]| and then `id` to the host.
+__global__ __launch_bounds__(256) void k_b_next(const double* __restrict__ W, int64_t ld, const double* __restrict__ parts,
+                                                int NP, const double* __restrict__ nrm, int nstride, int64_t n,
+                                                const double* __restrict__ d, double* __restrict__ out,
+                                                int64_t ostride, float* __restrict__ zt32, double* __restrict__ zt64,
+                                                double* __restrict__ zn64, const double* __restrict__ Hcol, int j,
+                                                double* __restrict__ col, uint64_t* flag, uint64_t id) {
+    __shared__ double vl;
     const int r = blockIdx.y;
-    const double v = nrm[r * nstride];
-    if (i >= n || v == 0.0) return;
-    out[(int64_t)r * ostride + i] = W[(int64_t)r * wstride + i] / v;
+    if (threadIdx.x < 64) {
+        double a = 0.0;
+        if (NP > 0) {
+            for (int b = threadIdx.x; b < NP; b += 64) a += parts[(int64_t)r * NP + b];
+            a = sqrt(wave_sum(a));
+        } else {
+            a = nrm[(int64_t)r * nstride];
+        }
+        if (threadIdx.x == 0) vl = a;
+    }
+    __syncthreads();
+    const double v = vl;
+    if (col && blockIdx.x == 0) {
+        double* c = col + (int64_t)r * nstride;
+        for (int k = threadIdx.x; k <= j; k += 256) host_put(c + k, Hcol[(int64_t)r * nstride + k]);
+        if (threadIdx.x == 0) host_put(c + j + 1, v);
+        host_done();
+        __syncthreads();
+        if (threadIdx.x == 0) host_flag(flag + r, id);
+    }
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    double* op = out + (int64_t)r * ostride + i;
+    const double o = v != 0.0 ? W[(int64_t)r * ld + i] / v : *op;
+    if (v != 0.0) *op = o;
+    const double z = o / d[i];
+    if (zt32) zt32[(int64_t)r * ld + i] = (float)z;
+    if (zt64) zt64[(int64_t)r * ld + i] = z;
+    if (zn64) zn64[i * BR + r] = z;
 }
 
 // R[r] = B[r] - W[r]
@@ -153,23 +233,29 @@ struct BW {
     int32_t* jend;
     float* zt32;
     double *zt64, *zn64;
-    double* host;   // pinned
+    double* host;     // pinned
+    double* col;      // a column per vector in coherent host memory,
+    uint64_t* flag;   // and the number of the iteration that filled it
     dim3 gv() const { return dim3((unsigned)ceil_div(n, 256), (unsigned)nr); }
 };
 
-// W = A * (src / d) for the nr vectors (stride sstride), inner (mixed: FP32 cores) or exact
-void apply(BW& w, const double* src, int64_t sstride, const double* d, bool exact) {
+// the input layouts that product() reads: inner FP32 vectors, FP64 ones, and FP64 ones interleaved for the
+// near remainders and the constraint rows of the mixed operator
+float* in32(const BW& w, bool exact) { return w.c->opt.precision == BEM_MIXED && !exact ? w.zt32 : nullptr; }
+double* in64(const BW& w, bool exact) { return in32(w, exact) ? nullptr : w.zt64; }
+double* in_rows(const BW& w, bool exact) {
+    return w.c->opt.precision == BEM_MIXED && (exact || w.n > w.N) ? w.zn64 : nullptr;
+}
+
+// W = A z for the vectors in the input layouts, inner (mixed: FP32 cores) or exact
+void product(BW& w, bool exact) {
     bem_ctx* c = w.c;
     const bool mixed = c->opt.precision == BEM_MIXED;
-    const bool f32 = mixed && !exact;
-    hipLaunchKernelGGL(k_b_prep, dim3((unsigned)ceil_div(w.ld, 256), BR), dim3(256), 0, w.s, src, sstride, w.nr, w.n,
-                       w.ld, d, f32 ? w.zt32 : nullptr, f32 ? nullptr : w.zt64, (mixed && !f32) ? w.zn64 : nullptr);
-    BEM_CHECK_LAUNCH();
     if (!mixed) {
         launch_gemm_f64(c, c->A64.p, false, w.ld, w.n, w.ld, w.zt64, w.ld, w.nr, w.W, w.ld, false, 1.0);
         return;
     }
-    if (f32) {
+    if (!exact) {
         launch_gemm_f32(c, c->A32.as<float>(), w.ld, w.N, w.ld, w.zt32, w.ld, w.nr, w.W, w.ld, false);
     } else {
         launch_gemm_f64(c, c->A32.p, true, w.ld, w.N, w.ld, w.zt64, w.ld, w.nr, w.W, w.ld, false, 1.0);
@@ -178,15 +264,16 @@ void apply(BW& w, const double* src, int64_t sstride, const double* d, bool exac
                            c->near_col.as<int32_t>(), c->near_val.as<double>(), w.N, w.zn64, w.nr, w.W, w.ld);
         BEM_CHECK_LAUNCH();
     }
-    if (w.n > w.N) {
-        // constraint rows (FP64, a few) need the FP64 vectors, vector-interleaved for the K-split row product
-        if (f32) {
-            hipLaunchKernelGGL(k_b_prep, dim3((unsigned)ceil_div(w.ld, 256), BR), dim3(256), 0, w.s, src, sstride,
-                               w.nr, w.n, w.ld, d, (float*)nullptr, (double*)nullptr, w.zn64);
-            BEM_CHECK_LAUNCH();
-        }
+    if (w.n > w.N)   // constraint rows (FP64, a few)
         launch_gemm_rows(c, c->A64.as<double>(), w.ld, w.n - w.N, w.ld, w.zn64, w.nr, w.W + w.N, w.ld, false, 1.0);
-    }
+}
+
+// W = A * src for the nr vectors (stride sstride)
+void apply(BW& w, const double* src, int64_t sstride, bool exact) {
+    hipLaunchKernelGGL(k_b_prep, dim3((unsigned)ceil_div(w.ld, 256), BR), dim3(256), 0, w.s, src, sstride, w.nr, w.n,
+                       w.ld, in32(w, exact), in64(w, exact), in_rows(w, exact));
+    BEM_CHECK_LAUNCH();
+    product(w, exact);
 }
 
 // blocks per dot product: about 2048 blocks per launch in total, each at least a few waves of work
@@ -195,21 +282,30 @@ int dot_split(const BW& w, int ndots) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(g, w.G));
 }
 
-// norms of the nr vectors v[r * ld] into dst[r * dstride] (device); with `out`, also to the host
-void norms(BW& w, const double* v, double* dst, int dstride, std::vector<double>* out) {
-    const int G = dot_split(w, w.nr);
-    hipLaunchKernelGGL(k_b_dots, dim3(G, 1, w.nr), dim3(256), 0, w.s, v, 1, w.ld, w.n, v, w.part, G);
+// norms of the nr vectors v[r * ld] into w.h[r * hs] and to the host
+void norms(BW& w, const double* v, std::vector<double>& out) {
+    const int G = dot_split(w, w.nr), hs = w.m + 2;
+    hipLaunchKernelGGL(k_b_dots, dim3(G, 1, w.nr), dim3(256), 0, w.s, v, 1, w.ld, w.n, 1, v, w.part, G);
     BEM_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_b_reduce, dim3((unsigned)ceil_div(w.nr, 64)), dim3(64), 0, w.s, w.part, G, 1, 1, w.nr, dst,
-                       dstride, (double*)nullptr, 0, 1);
+    hipLaunchKernelGGL(k_b_norm, dim3((unsigned)w.nr), dim3(64), 0, w.s, w.part, G, w.h, hs);
     BEM_CHECK_LAUNCH();
-    if (out) {
-        if (dst != w.h) throw Error(BEM_ERR_INVALID, "norms to host need the h block");
-        BEM_HIP(hipMemcpyAsync(w.host, w.h, sizeof(double) * w.nr * dstride, hipMemcpyDeviceToHost, w.s));
-        BEM_HIP(hipStreamSynchronize(w.s));
-        out->resize(w.nr);
-        for (int r = 0; r < w.nr; ++r) (*out)[r] = w.host[r * dstride];
-    }
+    BEM_HIP(hipMemcpyAsync(w.host, w.h, sizeof(double) * w.nr * hs, hipMemcpyDeviceToHost, w.s));
+    BEM_HIP(hipStreamSynchronize(w.s));
+    out.resize(w.nr);
+    for (int r = 0; r < w.nr; ++r) out[r] = w.host[r * hs];
+}
+
+// waits until every vector's column of iteration `id` is with the host; errors of the stream are raised
+void wait_columns(const BW& w, uint64_t id) {
+    for (int r = 0; r < w.nr; ++r)
+        for (int64_t spin = 1; __atomic_load_n(w.flag + r, __ATOMIC_ACQUIRE) < id; ++spin) {
+            if ((spin & 0xffff) != 0) continue;
+            const hipError_t e = hipStreamQuery(w.s);
+            if (e == hipErrorNotReady) continue;
+            BEM_HIP(e);
+            if (__atomic_load_n(w.flag + r, __ATOMIC_ACQUIRE) < id)
+                throw Error(BEM_ERR_HIP, "GMRES iteration ended without its columns");
+        }
 }
 
 // Batched GMRES on A x_r = b_r (x updated in place; initial guess as given).
@@ -226,10 +322,10 @@ int bgmres(BW& w, const double* B, double* X, double tol, int max_iter, bool exa
     std::vector<double> beta(nr);
     for (;;) {
         // W = B - A X, its norms, then V[r][0] = W[r] / beta[r]
-        apply(w, X, w.ld, nullptr, exact_apply);
+        apply(w, X, w.ld, exact_apply);
         hipLaunchKernelGGL(k_b_residual, w.gv(), dim3(256), 0, w.s, B, w.W, w.ld, w.n, w.W);
         BEM_CHECK_LAUNCH();
-        norms(w, w.W, w.h, hs, &beta);
+        norms(w, w.W, beta);
         bool all_done = true;
         for (int r = 0; r < nr; ++r) {
             rel[r] = bnorm[r] > 0.0 ? beta[r] / bnorm[r] : 0.0;
@@ -237,8 +333,11 @@ int bgmres(BW& w, const double* B, double* X, double tol, int max_iter, bool exa
             if (!done[r]) all_done = false;
         }
         if (all_done || iters >= max_iter) break;
-        hipLaunchKernelGGL(k_b_scale, w.gv(), dim3(256), 0, w.s, w.W, w.ld, w.h, hs, w.n, w.V, (int64_t)m1 * w.ld);
+        hipLaunchKernelGGL(k_b_next, w.gv(), dim3(256), 0, w.s, w.W, w.ld, w.h, 0, w.h, hs, w.n, d, w.V,
+                           (int64_t)m1 * w.ld, in32(w, exact_apply), in64(w, exact_apply), in_rows(w, exact_apply),
+                           w.Hcol, 0, (double*)nullptr, (uint64_t*)nullptr, (uint64_t)0);
         BEM_CHECK_LAUNCH();
+        product(w, exact_apply);
         std::fill(H.begin(), H.end(), 0.0);
         std::fill(g.begin(), g.end(), 0.0);
         for (int r = 0; r < nr; ++r) {
@@ -246,27 +345,31 @@ int bgmres(BW& w, const double* B, double* X, double tol, int max_iter, bool exa
             jend[r] = 0;
             stopped[r] = done[r];
         }
+        double r_last = 1.0, r_prev = 1.0;
+        for (int r = 0; r < nr; ++r) r_last = r_prev = std::max(r == 0 ? 0.0 : r_last, rel[r]);
         for (int j = 0; j < m; ++j) {
             KTimer tj(c, "bgmres_iter");
-            // W = A (V[:, j] / d)
-            apply(w, w.V + (int64_t)j * w.ld, (int64_t)m1 * w.ld, d, exact_apply);
-            const int G = dot_split(w, (j + 1) * nr);
+            // W = A (V[:, j] / d) is on its way
+            const int G = dot_split(w, (int)ceil_div(j + 1, DOT_K) * nr), GB = (int)ceil_div(w.n, 256);
+            double* norm = w.part + (size_t)nr * m1 * w.G;
             for (int pass = 0; pass < 2; ++pass) {
-                hipLaunchKernelGGL(k_b_dots, dim3(G, j + 1, nr), dim3(256), 0, w.s, w.V, m1, w.ld, w.n, w.W, w.part,
-                                   G);
+                hipLaunchKernelGGL(k_b_dots, dim3(G, ceil_div(j + 1, DOT_K), nr), dim3(256), 0, w.s, w.V, m1, w.ld,
+                                   w.n, j + 1, w.W, w.part, G);
                 BEM_CHECK_LAUNCH();
-                hipLaunchKernelGGL(k_b_reduce, dim3((unsigned)ceil_div((j + 1) * nr, 64)), dim3(64), 0, w.s, w.part,
-                                   G, m1, j + 1, nr, w.h, hs, w.Hcol, pass, 0);
-                BEM_CHECK_LAUNCH();
-                hipLaunchKernelGGL(k_b_orth, w.gv(), dim3(256), 0, w.s, w.V, m1, w.ld, w.n, j + 1, w.h, hs, w.W);
+                hipLaunchKernelGGL(k_b_orth, w.gv(), dim3(256), 0, w.s, w.V, m1, w.ld, w.n, j + 1, w.part, G, w.Hcol,
+                                   hs, pass, w.W, pass == 1 ? norm : (double*)nullptr);
                 BEM_CHECK_LAUNCH();
             }
-            norms(w, w.W, w.Hcol + j + 1, hs, nullptr);
-            hipLaunchKernelGGL(k_b_scale, w.gv(), dim3(256), 0, w.s, w.W, w.ld, w.Hcol + j + 1, hs, w.n,
-                               w.V + (int64_t)(j + 1) * w.ld, (int64_t)m1 * w.ld);
+            const uint64_t id = ++c->gm_seq;
+            hipLaunchKernelGGL(k_b_next, w.gv(), dim3(256), 0, w.s, w.W, w.ld, norm, GB, w.Hcol, hs, w.n, d,
+                               w.V + (int64_t)(j + 1) * w.ld, (int64_t)m1 * w.ld, in32(w, exact_apply),
+                               in64(w, exact_apply), in_rows(w, exact_apply), w.Hcol, j, w.col, w.flag, id);
             BEM_CHECK_LAUNCH();
-            BEM_HIP(hipMemcpyAsync(w.host, w.Hcol, sizeof(double) * nr * hs, hipMemcpyDeviceToHost, w.s));
-            BEM_HIP(hipStreamSynchronize(w.s));
+            // the next product runs while the host reads the columns, unless the residuals so far say that
+            // this iteration ends the solve (a product in vain costs more than the wait)
+            const bool more = j + 1 < m && iters + 1 < max_iter, ahead = more && r_last * (r_last / r_prev) > tol;
+            if (ahead) product(w, exact_apply);
+            wait_columns(w, id);
             ++iters;
             bool all_stopped = true;
             for (int r = 0; r < nr; ++r) {
@@ -275,8 +378,8 @@ int bgmres(BW& w, const double* B, double* X, double tol, int max_iter, bool exa
                 double* cr = cs.data() + (size_t)r * m;
                 double* sr = sn.data() + (size_t)r * m;
                 double* gr = g.data() + (size_t)r * (m + 1);
-                for (int k = 0; k <= j + 1; ++k) Hr[(size_t)k * m + j] = w.host[r * hs + k];
-                const double hn = w.host[r * hs + j + 1];
+                for (int k = 0; k <= j + 1; ++k) Hr[(size_t)k * m + j] = w.col[r * hs + k];
+                const double hn = w.col[r * hs + j + 1];
                 for (int k = 0; k < j; ++k) {
                     const double a = Hr[(size_t)k * m + j], b = Hr[(size_t)(k + 1) * m + j];
                     Hr[(size_t)k * m + j] = cr[k] * a + sr[k] * b;
@@ -295,6 +398,11 @@ int bgmres(BW& w, const double* B, double* X, double tol, int max_iter, bool exa
                 if (!stopped[r]) all_stopped = false;
             }
             if (all_stopped || iters >= max_iter) break;
+            r_prev = r_last;
+            r_last = 0.0;   // the largest residual still above the tolerance
+            for (int r = 0; r < nr; ++r)
+                if (!stopped[r]) r_last = std::max(r_last, std::fabs(g[(size_t)r * (m + 1) + j + 1]) / bnorm[r]);
+            if (!ahead && more) product(w, exact_apply);
         }
         // y_r from the triangular systems, then X_r += V_r y_r / d
         for (int r = 0; r < nr; ++r) {
@@ -336,7 +444,7 @@ void batched_apply_exact(bem_ctx* c, int nr, const double* X, double* Y) {
     w.zt32 = c->bg_z.as<float>();
     w.zt64 = reinterpret_cast<double*>(w.zt32 + BR * ld);
     w.zn64 = w.zt64 + BR * ld;
-    apply(w, X, w.n, nullptr, true);
+    apply(w, X, w.n, true);
     for (int r = 0; r < nr; ++r)
         BEM_HIP(hipMemcpyAsync(Y + (int64_t)r * w.n, w.W + (int64_t)r * w.ld, sizeof(double) * w.n,
                                hipMemcpyDeviceToDevice, w.s));
@@ -358,7 +466,7 @@ int gmres_solve_batched(bem_ctx* c, int nr, const double* B, double* X, double t
     const size_t ld = (size_t)w.ld;
     c->bg_V.alloc(sizeof(double) * nr * w.m1 * ld);
     c->bg_W.alloc(sizeof(double) * nr * ld * 3);
-    c->bg_part.alloc(sizeof(double) * nr * w.m1 * w.G);
+    c->bg_part.alloc(sizeof(double) * nr * ((size_t)w.m1 * w.G + (size_t)ceil_div(w.n, 256)));   // and the norms'
     c->bg_small.alloc(sizeof(double) * (size_t)nr * (w.m + 2) * 3 + sizeof(int32_t) * 64);
     c->bg_z.alloc(sizeof(float) * BR * ld + sizeof(double) * BR * ld * 2);
     c->host_stage.alloc(sizeof(double) * std::max<size_t>(4096, (size_t)nr * (w.m + 2) + 64));
@@ -375,12 +483,16 @@ int gmres_solve_batched(bem_ctx* c, int nr, const double* B, double* X, double t
     w.zt64 = reinterpret_cast<double*>(w.zt32 + BR * ld);
     w.zn64 = w.zt64 + BR * ld;
     w.host = c->host_stage.as<double>();
+    const size_t cols = (size_t)nr * (w.m + 2);
+    gmres_host(c, BR + cols);
+    w.flag = c->gm_host.as<uint64_t>();
+    w.col = c->gm_host.as<double>() + BR;
     // zero the Z buffers once: rows >= nr stay zero
     hipLaunchKernelGGL(k_b_fill, dim3((unsigned)ceil_div((int64_t)BR * ld * 2, 256)), dim3(256), 0, w.s, w.zt64,
                        (int64_t)BR * ld * 2, 0.0);
     BEM_CHECK_LAUNCH();
     std::vector<double> bnorm(nr), rel(nr);
-    norms(w, B, w.h, w.m + 2, &bnorm);
+    norms(w, B, bnorm);
     const int64_t total = (int64_t)nr * w.ld;
     hipLaunchKernelGGL(k_b_fill, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, w.s, X, total, 0.0);
     BEM_CHECK_LAUNCH();
@@ -392,11 +504,11 @@ int gmres_solve_batched(bem_ctx* c, int nr, const double* B, double* X, double t
     } else {
         // FP64 iterative refinement around the FP32-core inner solves
         for (;;) {
-            apply(w, X, w.ld, nullptr, true);
+            apply(w, X, w.ld, true);
             hipLaunchKernelGGL(k_b_residual, w.gv(), dim3(256), 0, w.s, B, w.W, w.ld, w.n, R);
             BEM_CHECK_LAUNCH();
             std::vector<double> rn;
-            norms(w, R, w.h, w.m + 2, &rn);
+            norms(w, R, rn);
             double worst = 0.0;
             for (int r = 0; r < nr; ++r) {
                 rel[r] = bnorm[r] > 0.0 ? rn[r] / bnorm[r] : 0.0;

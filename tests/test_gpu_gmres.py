@@ -54,3 +54,25 @@ def test_gmres_iteration_limit(bem, limit):
         sol, info = c.solve(p.body_V, tol=1e-10, max_iter=limit, raise_on_noconv=False)
         assert not info["converged"] and info["iters"] == limit
         assert abs(_residual(c, p, sol) - info["rel_residual"]) <= 1e-12
+
+
+@pytest.mark.parametrize("nrhs,restart", [(2, 100), (5, 4), (63, 20), (64, 100), (70, 100)])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_gmres_batched_residual(bem, nrhs, restart, mixed):
+    """Load cases solved together, one of them zero: residuals from the single-vector product.  MIXED
+    solves to 1e-8 (its workload's bar)."""
+    p = sphere_problem(2) if restart < 20 else coax_problem(0.012)
+    print(f"[gpu-gmres] batched {p.name} rhs={nrhs} restart={restart} mixed={mixed}", flush=True)
+    rng = np.random.default_rng(nrhs)
+    V = rng.uniform(-1.0, 1.0, (nrhs, len(p.body_V)))
+    V[1] = 0.0
+    tol = 1e-8 if mixed else 1e-10
+    with bem.Context.from_problem(p, restart=restart, precision=bem.MIXED if mixed else bem.FP64) as c:
+        c.assemble()
+        sol, info = c.solve(V, tol=tol, max_iter=3000)
+        b = c.rhs(V).reshape(nrhs, -1)
+        assert info["converged"]
+        for r in range(nrhs):
+            res = (b[r] - c.matvec(sol[r:r + 1]).reshape(-1)).norm().item()
+            assert res <= tol * b[r].norm().item() + 1e-13 * b.norm(dim=1).max().item()
+        assert torch.equal(sol[1], torch.zeros_like(sol[1]))
