@@ -613,7 +613,7 @@ bem_status bem_rhs(bem_ctx* c, int32_t nrhs, const double* body_V, double* b) {
     for (int64_t k = 0; k < (int64_t)nrhs * c->n_body; ++k)
         if (!std::isfinite(body_V[k])) throw bem::Error(BEM_ERR_INVALID, "non-finite body potential");
     upload(c->gm_b, body_V, (size_t)nrhs * c->n_body, c->stream);
-    bem::launch_rhs(c, nrhs, c->gm_b.as<double>(), b);
+    bem::launch_rhs(c, nrhs, c->gm_b.as<double>(), b, c->n);
     BEM_HIP(hipStreamSynchronize(c->stream));   // body_V staging buffer is reused
     return BEM_OK;
     API_CATCH
@@ -687,14 +687,12 @@ bem_status bem_solve_gmres(bem_ctx* c, int32_t nrhs, const double* body_V, doubl
             c->bg_X.alloc(sizeof(double) * 64 * ld);
             double* B = c->bg_B.as<double>();
             double* X = c->bg_X.as<double>();
-            for (int r = 0; r < nr; ++r)
-                bem::launch_rhs(c, 1, dV + (int64_t)(r0 + r) * c->n_body, B + (int64_t)r * ld);
+            bem::launch_rhs(c, nr, dV + (int64_t)r0 * c->n_body, B, ld);
             int it = 0, ref = 0;
             double rr = 0.0;
             const int rc = bem::gmres_solve_batched(c, nr, B, X, tol, max_iter, &it, &rr, &ref);
-            for (int r = 0; r < nr; ++r)
-                BEM_HIP(hipMemcpyAsync(sol + (int64_t)(r0 + r) * n, X + (int64_t)r * ld, sizeof(double) * n,
-                                       hipMemcpyDeviceToDevice, c->stream));
+            BEM_HIP(hipMemcpy2DAsync(sol + (int64_t)r0 * n, sizeof(double) * n, X, sizeof(double) * ld,
+                                     sizeof(double) * n, nr, hipMemcpyDeviceToDevice, c->stream));
             total_it += it;
             total_ref += ref;
             worst = std::max(worst, rr);
@@ -702,7 +700,7 @@ bem_status bem_solve_gmres(bem_ctx* c, int32_t nrhs, const double* body_V, doubl
         }
     } else {
         for (int32_t r = 0; r < nrhs; ++r) {
-            bem::launch_rhs(c, 1, dV + (int64_t)r * c->n_body, bvec);
+            bem::launch_rhs(c, 1, dV + (int64_t)r * c->n_body, bvec, ld);
             int it = 0, ref = 0;
             double rr = 0.0;
             const int rc = bem::gmres_solve(c, bvec, xvec, tol, max_iter, &it, &rr, &ref);

@@ -283,7 +283,7 @@ void launch_near_csr(bem_ctx* c, const uint64_t* mask, int64_t n_targets, DBuf& 
 void launch_near_assemble(bem_ctx* c);                             // assemble.hip
 void launch_finalize(bem_ctx* c);                                  // assemble.hip
 void launch_copy_rows(bem_ctx* c, int64_t row0, int64_t n_rows, double* out);
-void launch_rhs(bem_ctx* c, int32_t nrhs, const double* d_bodyV, double* b);
+void launch_rhs(bem_ctx* c, int32_t nrhs, const double* d_bodyV, double* b, int64_t ldb);   // b[r ldb + i]
 void launch_nodal_assemble(bem_ctx* c);                                          // nodal.hip
 void launch_nodal_records(bem_ctx* c, const double* u);                          // nodal.hip
 void launch_nodal_field(bem_ctx* c, int32_t nrhs, const double* sol, int64_t P, const double* pts, double* phi,
