@@ -126,9 +126,9 @@ __global__ __launch_bounds__(1024) void k_orth(const double* __restrict__ V, int
 // The next Krylov vector out = w / |w| and the product's input z = out / d of the next iteration
 // (both left untouched if the norm is zero).  |w|: from the NP partials of its square, or *nrm (NP = 0).
 // host: block 0 hands the column Hcol[0..j], |w| and then `id` to the host.
-__global__ __launch_bounds__(256) void k_scale_div(const double* __restrict__ w, const double* __restrict__ parts, int NP,
+__global__ __launch_bounds__(256) void k_scale_div(const double* w, const double* __restrict__ parts, int NP,
                                                    const double* __restrict__ nrm, const double* __restrict__ d,
-                                                   int64_t n, double* __restrict__ out, double* __restrict__ z,
+                                                   int64_t n, double* out, double* __restrict__ z,   // out may be w
                                                    const double* __restrict__ Hcol, int j, double* __restrict__ host,
                                                    uint64_t* flag, uint64_t id) {
     __shared__ double vl;
@@ -281,45 +281,45 @@ void wait_iteration(Work& W, int slot, uint64_t id) {
     }
 }
 
-// One GMRES solve of A x = b (x overwritten; zero initial guess unless keep_x).
-int gmres_core(Work& W, const double* b, double* x, double tol, int max_iter, int* iters_out, double* relres_out,
-               bool keep_x) {
+// One GMRES solve of A x = b (x overwritten; zero initial guess).
+int gmres_core(Work& W, const double* b, double* x, double tol, int max_iter, int* iters_out, double* relres_out) {
     bem_ctx* c = W.c;
     const int64_t n = W.n;
     const int m = W.m;
     const double* d = c->diag.as<double>();
-    if (!keep_x) {
-        hipLaunchKernelGGL(k_fill, W.g1(), dim3(256), 0, W.s, x, n, 0.0);
-        BEM_CHECK_LAUNCH();
-    }
+    hipLaunchKernelGGL(k_fill, W.g1(), dim3(256), 0, W.s, x, n, 0.0);
+    BEM_CHECK_LAUNCH();
     const double bnorm = host_norm(W, b);
     std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m + 1);
     int iters = 0;
     double relres = 0.0;
     bool converged = false;
     if (bnorm == 0.0) {
-        hipLaunchKernelGGL(k_fill, W.g1(), dim3(256), 0, W.s, x, n, 0.0);
-        BEM_CHECK_LAUNCH();
         *iters_out = 0;
         *relres_out = 0.0;
         return 0;
     }
     for (;;) {
-        // r = b - A x into V[0]
-        if (W.transpose)
-            launch_matvec_t(c, x, W.w, W.s);
-        else
-            launch_matvec(c, x, W.w, W.s);
-        hipLaunchKernelGGL(k_residual, W.g1(), dim3(256), 0, W.s, b, W.w, n, W.V);
-        BEM_CHECK_LAUNCH();
-        const double beta = host_norm(W, W.V);
+        // r = b - A x and its norm; b itself for the zero guess, no product needed
+        const double* r = b;
+        double beta = bnorm;
+        if (iters > 0) {
+            if (W.transpose)
+                launch_matvec_t(c, x, W.w, W.s);
+            else
+                launch_matvec(c, x, W.w, W.s);
+            hipLaunchKernelGGL(k_residual, W.g1(), dim3(256), 0, W.s, b, W.w, n, W.V);
+            BEM_CHECK_LAUNCH();
+            r = W.V;
+            beta = host_norm(W, r);
+        }
         relres = beta / bnorm;
         if (relres <= tol) {
             converged = true;
             break;
         }
         if (iters >= max_iter) break;
-        hipLaunchKernelGGL(k_scale_div, W.g1(), dim3(256), 0, W.s, W.V, W.misc, 0, W.misc, d, n, W.V, W.z, W.Hcol, 0,
+        hipLaunchKernelGGL(k_scale_div, W.g1(), dim3(256), 0, W.s, r, W.misc, 0, W.misc, d, n, W.V, W.z, W.Hcol, 0,
                            (double*)nullptr, (uint64_t*)nullptr, (uint64_t)0);
         BEM_CHECK_LAUNCH();
         std::fill(g.begin(), g.end(), 0.0);
@@ -417,7 +417,7 @@ int gmres_solve_t(bem_ctx* c, const double* b, double* x, double tol, int max_it
     Work W;
     setup_work(c, W);
     W.transpose = true;
-    return gmres_core(W, b, x, tol, max_iter, iters, relres, false);
+    return gmres_core(W, b, x, tol, max_iter, iters, relres);
 }
 
 int gmres_solve(bem_ctx* c, const double* b, double* x, double tol, int max_iter, int* iters, double* relres,
@@ -425,7 +425,7 @@ int gmres_solve(bem_ctx* c, const double* b, double* x, double tol, int max_iter
     *refinements_out = 0;
     Work W;
     setup_work(c, W);
-    if (c->opt.precision == BEM_FP64) return gmres_core(W, b, x, tol, max_iter, iters, relres, false);
+    if (c->opt.precision == BEM_FP64) return gmres_core(W, b, x, tol, max_iter, iters, relres);
 
     // Mixed mode: FP64 iterative refinement around GMRES on the mixed operator.
     double* r = c->gm_r.as<double>();
@@ -448,7 +448,7 @@ int gmres_solve(bem_ctx* c, const double* b, double* x, double tol, int max_iter
         int it = 0;
         double rr = 0.0;
         const double inner = std::max(1e-4, 0.5 * tol / rel);
-        gmres_core(W, r, dx, inner, max_iter - total, &it, &rr, false);
+        gmres_core(W, r, dx, inner, max_iter - total, &it, &rr);
         total += it;
         ++refinements;
         hipLaunchKernelGGL(k_axpy, W.g1(), dim3(256), 0, W.s, x, dx, W.n);

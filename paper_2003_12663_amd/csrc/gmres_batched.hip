@@ -308,7 +308,7 @@ void wait_columns(const BW& w, uint64_t id) {
         }
 }
 
-// Batched GMRES on A x_r = b_r (x updated in place; initial guess as given).
+// Batched GMRES on A x_r = b_r: x is zero on entry, and w.h holds the norms of b (also in bnorm).
 // Returns the number of iterations; rel[r] gets the final relative residual.
 int bgmres(BW& w, const double* B, double* X, double tol, int max_iter, bool exact_apply, std::vector<double>& rel,
            std::vector<double>& bnorm) {
@@ -321,11 +321,17 @@ int bgmres(BW& w, const double* B, double* X, double tol, int max_iter, bool exa
     int iters = 0;
     std::vector<double> beta(nr);
     for (;;) {
-        // W = B - A X, its norms, then V[r][0] = W[r] / beta[r]
-        apply(w, X, w.ld, exact_apply);
-        hipLaunchKernelGGL(k_b_residual, w.gv(), dim3(256), 0, w.s, B, w.W, w.ld, w.n, w.W);
-        BEM_CHECK_LAUNCH();
-        norms(w, w.W, beta);
+        // residuals B - A X and their norms, then V[r][0] = residual / beta[r]; for the zero guess they are
+        // B and bnorm, which the caller has just taken (w.h)
+        const double* res = B;
+        beta = bnorm;
+        if (iters > 0) {
+            apply(w, X, w.ld, exact_apply);
+            hipLaunchKernelGGL(k_b_residual, w.gv(), dim3(256), 0, w.s, B, w.W, w.ld, w.n, w.W);
+            BEM_CHECK_LAUNCH();
+            res = w.W;
+            norms(w, res, beta);
+        }
         bool all_done = true;
         for (int r = 0; r < nr; ++r) {
             rel[r] = bnorm[r] > 0.0 ? beta[r] / bnorm[r] : 0.0;
@@ -333,7 +339,7 @@ int bgmres(BW& w, const double* B, double* X, double tol, int max_iter, bool exa
             if (!done[r]) all_done = false;
         }
         if (all_done || iters >= max_iter) break;
-        hipLaunchKernelGGL(k_b_next, w.gv(), dim3(256), 0, w.s, w.W, w.ld, w.h, 0, w.h, hs, w.n, d, w.V,
+        hipLaunchKernelGGL(k_b_next, w.gv(), dim3(256), 0, w.s, res, w.ld, w.h, 0, w.h, hs, w.n, d, w.V,
                            (int64_t)m1 * w.ld, in32(w, exact_apply), in64(w, exact_apply), in_rows(w, exact_apply),
                            w.Hcol, 0, (double*)nullptr, (uint64_t*)nullptr, (uint64_t)0);
         BEM_CHECK_LAUNCH();
@@ -487,9 +493,10 @@ int gmres_solve_batched(bem_ctx* c, int nr, const double* B, double* X, double t
     gmres_host(c, BR + cols);
     w.flag = c->gm_host.as<uint64_t>();
     w.col = c->gm_host.as<double>() + BR;
-    // zero the Z buffers once: rows >= nr stay zero
-    hipLaunchKernelGGL(k_b_fill, dim3((unsigned)ceil_div((int64_t)BR * ld * 2, 256)), dim3(256), 0, w.s, w.zt64,
-                       (int64_t)BR * ld * 2, 0.0);
+    // zero the Z buffers once: rows >= nr and entries past n stay zero
+    const int64_t zwords = (int64_t)BR * ld / 2 * 5;
+    hipLaunchKernelGGL(k_b_fill, dim3((unsigned)ceil_div(zwords, 256)), dim3(256), 0, w.s,
+                       reinterpret_cast<double*>(w.zt32), zwords, 0.0);
     BEM_CHECK_LAUNCH();
     std::vector<double> bnorm(nr), rel(nr);
     norms(w, B, bnorm);
