@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "adjoint_device.h"
+#include "median_device.h"
 
 namespace bem {
 
@@ -38,20 +39,7 @@ namespace {
 
 constexpr int PA_TILE = 64;    // points per LDS tile in k_pan_far_adj
 constexpr int PA_ACC = 11;     // per-panel accumulators: T_far, T_near, 9 corner components
-
-__device__ __forceinline__ void quad7_bary(int q, double& b0, double& b1, double& b2) {
-    const double s15 = sqrt(15.0);
-    const double a1 = (6.0 - s15) / 21.0, a2 = (6.0 + s15) / 21.0;
-    if (q == 0) {
-        b0 = b1 = b2 = 1.0 / 3.0;
-        return;
-    }
-    const double a = q < 4 ? a1 : a2;
-    const int r = (q - 1) % 3;   // position of 1 - 2a
-    b0 = (r == 2) ? 1.0 - 2.0 * a : a;
-    b1 = (r == 1) ? 1.0 - 2.0 * a : a;
-    b2 = (r == 0) ? 1.0 - 2.0 * a : a;
-}
+constexpr int PA_SEG = 64;     // near points of a panel that a wave of k_pan_near_adj takes
 
 // ---- panel-major near lists from (panel group, point) ballot masks --------------------
 // mask[(j >> 6) * P + p] bit (j & 63) marks the pair (p, j) as not regular.
@@ -65,73 +53,100 @@ __global__ __launch_bounds__(64) void k_pm_count(const uint64_t* __restrict__ ma
     if (j < N) cnt[pb * N + j] = c;
 }
 
-// ptr[0] = 0, ptr[j + 1] = ptr[j] + sum_pb cnt[pb][j]; one block.
-__global__ __launch_bounds__(1024) void k_pm_scan(const int32_t* __restrict__ cnt, int64_t N, int PB,
-                                                  int64_t* __restrict__ ptr) {
-    __shared__ int64_t part[1024];
-    const int64_t per = (N + 1023) / 1024;
-    const int64_t j0 = threadIdx.x * per, j1 = std::min<int64_t>(N, j0 + per);
-    int64_t s = 0;
-    for (int64_t j = j0; j < j1; ++j)
-        for (int pb = 0; pb < PB; ++pb) s += cnt[(int64_t)pb * N + j];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t run = 0;
-        for (int t = 0; t < 1024; ++t) {
-            const int64_t v = part[t];
-            part[t] = run;
-            run += v;
+// cnt[pb][j]: counts in, offsets within panel j out; tot[j] their sum
+__global__ __launch_bounds__(64) void k_pm_rows(int32_t* __restrict__ cnt, int64_t N, int PB, int32_t* __restrict__ tot) {
+    const int64_t j = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    if (j >= N) return;
+    int32_t run = 0;
+    for (int b0 = 0; b0 < PB; b0 += 16) {
+        int32_t v[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v[q] = cnt[(int64_t)(b0 + q) * N + j];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            cnt[(int64_t)(b0 + q) * N + j] = run;
+            run += v[q];
         }
-        ptr[0] = 0;
     }
-    __syncthreads();
-    int64_t run = part[threadIdx.x];
+    tot[j] = run;
+}
+
+// ptr[0] = 0, ptr[j + 1] = ptr[j] + tot[j], and likewise seg for the number of pieces of PA_SEG points;
+// one block.
+__global__ __launch_bounds__(1024) void k_pm_scan(const int32_t* __restrict__ tot, int64_t N, int64_t* __restrict__ ptr,
+                                                  int64_t* __restrict__ seg) {
+    __shared__ int64_t part[1024], spart[1024];
+    const int tid = threadIdx.x;
+    const int64_t per = (N + 1023) / 1024;
+    const int64_t j0 = std::min<int64_t>(N, tid * per), j1 = std::min<int64_t>(N, j0 + per);
+    int64_t s = 0, g = 0;
     for (int64_t j = j0; j < j1; ++j) {
-        for (int pb = 0; pb < PB; ++pb) run += cnt[(int64_t)pb * N + j];
+        s += tot[j];
+        g += (tot[j] + PA_SEG - 1) / PA_SEG;
+    }
+    part[tid] = s;
+    spart[tid] = g;
+    __syncthreads();
+    for (int d = 1; d < 1024; d <<= 1) {
+        const int64_t v = tid >= d ? part[tid - d] : 0, w = tid >= d ? spart[tid - d] : 0;
+        __syncthreads();
+        part[tid] += v;
+        spart[tid] += w;
+        __syncthreads();
+    }
+    int64_t run = tid > 0 ? part[tid - 1] : 0, srun = tid > 0 ? spart[tid - 1] : 0;
+    if (tid == 0) ptr[0] = seg[0] = 0;
+    for (int64_t j = j0; j < j1; ++j) {
+        run += tot[j];
+        srun += (tot[j] + PA_SEG - 1) / PA_SEG;
         ptr[j + 1] = run;
+        seg[j + 1] = srun;
     }
 }
 
+// list: the near points of each panel, ascending; owner[s]: the panel of piece s
 __global__ __launch_bounds__(64) void k_pm_fill(const uint64_t* __restrict__ mask, int64_t P, int64_t N, int64_t chunk,
                                                 const int32_t* __restrict__ cnt, const int64_t* __restrict__ ptr,
-                                                int32_t* __restrict__ list) {
+                                                const int64_t* __restrict__ seg, int32_t* __restrict__ list,
+                                                int32_t* __restrict__ owner) {
     const int64_t g = blockIdx.x, pb = blockIdx.y;
     const int64_t j = g * 64 + threadIdx.x;
     if (j >= N) return;
-    int64_t pos = ptr[j];
-    for (int64_t b = 0; b < pb; ++b) pos += cnt[b * N + j];
+    if (pb == 0)
+        for (int64_t s = seg[j]; s < seg[j + 1]; ++s) owner[s] = (int32_t)j;
+    int64_t pos = ptr[j] + cnt[pb * N + j];
     const int64_t p0 = pb * chunk, p1 = std::min<int64_t>(P, p0 + chunk);
     for (int64_t p = p0; p < p1; ++p)
         if ((mask[g * P + p] >> threadIdx.x) & 1ull) list[pos++] = (int32_t)p;
 }
 
 // ---- panel side, regular pairs ------------------------------------------------------
-// For panel j (one per lane) and the points of this block's range: with the pair value
-// G = a_p S_j(x_p) + c_p . F_j(x_p) (7-point rule), accumulates T = sum G and the
-// derivatives of sum G with respect to the three vertices at fixed area (node positions
-// y_q = sum_k beta_qk v_k); the area part is added when folding (G is linear in the area).
-__global__ __launch_bounds__(256) void k_pan_far_adj(const double* __restrict__ far64, int64_t Np, int64_t N,
-                                                     int64_t P, int64_t span, const double* __restrict__ pts,
+// For panel j (one per lane, its record of density one in registers) and the points of this block's
+// range: with the pair value G = a_p S_j(x_p) + c_p . F_j(x_p) (7-point rule about the centroid),
+// accumulates T = sum G and the derivatives of sum G with respect to the three vertices at fixed
+// area; the area part is added when folding (G is linear in the area).  With w the node weights, d = t
+// - r m_i from node to point, g = |d|^-3, u = |d|^-5 and alpha = a g + 3 (c . d) u a node's derivative is
+// w (alpha d - g c); summed over the nodes it moves the centroid, over r times those of median i it
+// moves m_i.  The parts along the medians gather as scalars (s1, s2) and are applied at the end.
+// The pairs that are not regular (and a centroid's own panel, self_mode) are marked in
+// mask[(j >> 6) P + p], bit j & 63.  Bound by FP64 issue: 4.5 ms a batch of 131,072 points on 7,712 panels,
+// where the node-by-node form took 5.4 and a pass of its own for the marks 0.6.
+__global__ __launch_bounds__(256) void k_pan_far_adj(const double* __restrict__ rec, int64_t N, int64_t P,
+                                                     int64_t span, const double* __restrict__ pts,
                                                      const double* __restrict__ aw, const double* __restrict__ cw,
-                                                     int self_mode, int64_t p_off, double* __restrict__ part) {
+                                                     int self_mode, int64_t p_off, double* __restrict__ part,
+                                                     uint64_t* __restrict__ mask) {
     __shared__ double tp[PA_TILE][7];
     const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const bool valid = j < N;
-    const int64_t jj = valid ? j : N - 1;
-    double yq[7][3], wq[7];
+    double v[MED_REC];
+    const double* rj = rec + (int64_t)MED_REC * (valid ? j : N - 1);
 #pragma unroll
-    for (int q = 0; q < 7; ++q) {
-        yq[q][0] = far64[(int64_t)(FR_X + q) * Np + jj];
-        yq[q][1] = far64[(int64_t)(FR_Y + q) * Np + jj];
-        yq[q][2] = far64[(int64_t)(FR_Z + q) * Np + jj];
-        wq[q] = far64[(int64_t)(FR_W + q) * Np + jj];
-    }
-    const double cc0 = far64[(int64_t)(FR_CC + 0) * Np + jj], cc1 = far64[(int64_t)(FR_CC + 1) * Np + jj];
-    const double cc2 = far64[(int64_t)(FR_CC + 2) * Np + jj], rr = far64[(int64_t)FR_RR * Np + jj];
-    double T = 0.0, G[7][3];
+    for (int c = 0; c < MED_REC; ++c) v[c] = rj[c];
+    const MedConst k = med_consts();
+    double T = 0.0, gc[3] = {0.0, 0.0, 0.0}, gm[3][3], s1[3] = {0.0, 0.0, 0.0}, s2[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-    for (int q = 0; q < 7; ++q) G[q][0] = G[q][1] = G[q][2] = 0.0;
+    for (int i = 0; i < 3; ++i) gm[i][0] = gm[i][1] = gm[i][2] = 0.0;
     const int64_t p_beg = (int64_t)blockIdx.y * span;
     const int64_t p_end = std::min<int64_t>(P, p_beg + span);
     for (int64_t t0 = p_beg; t0 < p_end; t0 += PA_TILE) {
@@ -139,60 +154,90 @@ __global__ __launch_bounds__(256) void k_pan_far_adj(const double* __restrict__ 
         for (int e = threadIdx.x; e < PA_TILE * 7; e += 256) {
             const int pi = e / 7, comp = e % 7;
             const int64_t p = t0 + pi;
-            double v = 0.0;
+            double x = 0.0;
             if (p < p_end) {
                 if (comp < 3)
-                    v = pts[3 * p + comp];
+                    x = pts[3 * p + comp];
                 else if (comp == 3)
-                    v = aw ? aw[p] : 0.0;
+                    x = aw ? aw[p] : 0.0;
                 else
-                    v = cw[3 * p + comp - 4];
+                    x = cw[3 * p + comp - 4];
             }
-            tp[pi][comp] = v;
+            tp[pi][comp] = x;
         }
         __syncthreads();
         const int cnt = (int)std::min<int64_t>(PA_TILE, p_end - t0);
-        if (!valid) continue;
         for (int pi = 0; pi < cnt; ++pi) {
             const double x0 = tp[pi][0], x1 = tp[pi][1], x2 = tp[pi][2];
-            if (self_mode && t0 + pi + p_off == j) continue;
-            if (!is_regular(x0 - cc0, x1 - cc1, x2 - cc2, rr)) continue;
+            const double t[3] = {x0 - v[0], x1 - v[1], x2 - v[2]};
+            const double R = __fma_rn(t[0], t[0], __fma_rn(t[1], t[1], t[2] * t[2]));
+            bool reg = R > v[MD_REACH];
+            if (!reg) reg = is_regular(x0 - v[MD_CC], x1 - v[MD_CC + 1], x2 - v[MD_CC + 2], v[MD_RR]);
+            reg = reg && !(self_mode && t0 + pi + p_off == j);
+            const uint64_t m = __ballot(valid && !reg);
+            if ((threadIdx.x & 63) == 0 && valid) mask[(j >> 6) * P + t0 + pi] = m;
+            if (!reg) continue;
             const double a = tp[pi][3], c0 = tp[pi][4], c1 = tp[pi][5], c2 = tp[pi][6];
+            const double pa = __fma_rn(t[0], v[3], __fma_rn(t[1], v[4], t[2] * v[5]));
+            const double pb = __fma_rn(t[0], v[6], __fma_rn(t[1], v[7], t[2] * v[8]));
+            const double pc = -(pa + pb);
+            const double ct = __fma_rn(c0, t[0], __fma_rn(c1, t[1], c2 * t[2]));
+            const double ca = __fma_rn(c0, v[3], __fma_rn(c1, v[4], c2 * v[5]));
+            const double cb = __fma_rn(c0, v[6], __fma_rn(c1, v[7], c2 * v[8]));
+            const double cc = -(ca + cb);
+            const double r2[7] = {R,
+                                  __fma_rn(-2.0, pa, R + v[9]),
+                                  __fma_rn(-2.0, pb, R + v[10]),
+                                  __fma_rn(-2.0, pc, R + v[11]),
+                                  __fma_rn(k.m2rho, pa, __fma_rn(k.rho2, v[9], R)),
+                                  __fma_rn(k.m2rho, pb, __fma_rn(k.rho2, v[10], R)),
+                                  __fma_rn(k.m2rho, pc, __fma_rn(k.rho2, v[11], R))};
+            const double cd[7] = {ct, ct - ca, ct - cb, ct - cc, __fma_rn(-k.rho, ca, ct), __fma_rn(-k.rho, cb, ct),
+                                  __fma_rn(-k.rho, cc, ct)};
+            double ir[7], g[7], gd[7], al[7];
 #pragma unroll
             for (int q = 0; q < 7; ++q) {
-                const double dx = x0 - yq[q][0], dy = x1 - yq[q][1], dz = x2 - yq[q][2];
-                const double r2 = dx * dx + dy * dy + dz * dz;
-                const double ir = rsqrt_pos(r2);
-                const double ir2 = ir * ir;
-                const double t1 = wq[q] * ir;        // w / r
-                const double t3 = t1 * ir2;          // w / r^3
-                const double cd = c0 * dx + c1 * dy + c2 * dz;
-                T += a * t1 + t3 * cd;
-                // dG/dy_q = (a w / r^3 + 3 w (c.d) / r^5) d - (w / r^3) c
-                const double coef = t3 * (a + 3.0 * cd * ir2);
-                G[q][0] += coef * dx - t3 * c0;
-                G[q][1] += coef * dy - t3 * c1;
-                G[q][2] += coef * dz - t3 * c2;
+                ir[q] = rsqrt_pos(r2[q]);
+                const double ir2 = ir[q] * ir[q];
+                g[q] = ir[q] * ir2;
+                gd[q] = g[q] * cd[q];
+                al[q] = __fma_rn(3.0, gd[q] * ir2, a * g[q]);
+            }
+            auto sum = [&](const double (&f)[7]) {
+                return __fma_rn(k.kap0, f[0], __fma_rn(k.kap, (f[4] + f[5]) + f[6], (f[1] + f[2]) + f[3]));
+            };
+            T += __fma_rn(a, sum(ir), sum(gd));
+            const double A = sum(al), G = sum(g);
+            const double c[3] = {c0, c1, c2};
+#pragma unroll
+            for (int e = 0; e < 3; ++e) gc[e] = __fma_rn(A, t[e], __fma_rn(-G, c[e], gc[e]));
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const double Ai = __fma_rn(k.kaprho, al[4 + i], al[1 + i]), Gi = __fma_rn(k.kaprho, g[4 + i], g[1 + i]);
+                s1[i] += Ai;
+                s2[i] += __fma_rn(k.kaprho2, al[4 + i], al[1 + i]);
+#pragma unroll
+                for (int e = 0; e < 3; ++e) gm[i][e] = __fma_rn(Ai, t[e], __fma_rn(-Gi, c[e], gm[i][e]));
             }
         }
     }
     if (!valid) return;
     double* o = part + ((int64_t)blockIdx.y * N + j) * 10;
-    o[0] = T;
+    const double w = v[MD_DENS];
+    o[0] = w * T;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        double g0 = 0.0, g1 = 0.0, g2 = 0.0;
+    for (int e = 0; e < 3; ++e) {
+        const double m[3] = {v[3 + e], v[6 + e], -(v[3 + e] + v[6 + e])};
+        double C = gc[e], M[3];
 #pragma unroll
-        for (int q = 0; q < 7; ++q) {
-            double b[3];
-            quad7_bary(q, b[0], b[1], b[2]);
-            g0 += b[k] * G[q][0];
-            g1 += b[k] * G[q][1];
-            g2 += b[k] * G[q][2];
+        for (int i = 0; i < 3; ++i) {
+            C -= s1[i] * m[i];
+            M[i] = gm[i][e] - s2[i] * m[i];
         }
-        o[1 + 3 * k] = g0;
-        o[2 + 3 * k] = g1;
-        o[3 + 3 * k] = g2;
+        // y = c + r m_i, m_i = s (v_i - c): corner k moves it by 1/3 + r s (delta_ik - 1/3)
+        const double base = (C - MED_SC * ((M[0] + M[1]) + M[2])) / 3.0;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) o[1 + 3 * q + e] = w * (base + MED_SC * M[q]);
     }
 }
 
@@ -213,15 +258,21 @@ __global__ __launch_bounds__(256) void k_pan_reduce(const double* __restrict__ p
     for (int c = 1; c < 10; ++c) a[1 + c] += s[c];
 }
 
-// ---- panel side, near pairs: one wave per panel over its near points -----------------
+// ---- panel side, near pairs: one wave per piece of a panel's near points ------------------
+// (One wave per panel: the panels along a line have many times the points of the others, and half of
+// the CUs waited for them; 3.4 -> 1.7 ms a batch of 131,072 points on 7,712 panels.)  The dual numbers
+// take all 512 registers: held to 256 they spill, 5.6 ms.  out[piece]: T and the nine corner derivatives.
 __global__ __launch_bounds__(256) void k_pan_near_adj(const int64_t* __restrict__ ptr, const int32_t* __restrict__ list,
-                                                      int64_t N, const double* __restrict__ tri64,
+                                                      const int64_t* __restrict__ seg,
+                                                      const int32_t* __restrict__ owner, int64_t S,
+                                                      const double* __restrict__ tri64,
                                                       const double* __restrict__ pts, const double* __restrict__ aw,
                                                       const double* __restrict__ cw, int self_mode, int64_t p_off,
-                                                      double* __restrict__ acc) {
-    const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                      double* __restrict__ out) {
+    const int64_t s = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (j >= N) return;
+    if (s >= S) return;
+    const int64_t j = owner[s];
     const double* Tj = tri64 + (int64_t)TRI_REC * j;
     double vv[3][3];
 #pragma unroll
@@ -231,7 +282,8 @@ __global__ __launch_bounds__(256) void k_pan_near_adj(const int64_t* __restrict_
     double T = 0.0, g[9];
 #pragma unroll
     for (int c = 0; c < 9; ++c) g[c] = 0.0;
-    for (int64_t e = ptr[j] + lane; e < ptr[j + 1]; e += 64) {
+    const int64_t e = ptr[j] + (s - seg[j]) * PA_SEG + lane;
+    if (e < ptr[j + 1]) {
         const int64_t p = list[e];
         const bool self = self_mode && p + p_off == j;
         const double a = aw ? aw[p] : 0.0;
@@ -259,11 +311,21 @@ __global__ __launch_bounds__(256) void k_pan_near_adj(const int64_t* __restrict_
 #pragma unroll
     for (int c = 0; c < 9; ++c) g[c] = wave_sum(g[c]);
     if (lane == 0) {
-        double* o = acc + j * PA_ACC;
-        o[1] += T;
+        double* o = out + s * 10;
+        o[0] = T;
 #pragma unroll
-        for (int c = 0; c < 9; ++c) o[2 + c] += g[c];
+        for (int c = 0; c < 9; ++c) o[1 + c] = g[c];
     }
+}
+
+// acc[j] += the panel's pieces, in order
+__global__ __launch_bounds__(256) void k_pan_near_sum(const int64_t* __restrict__ seg, int64_t N,
+                                                      const double* __restrict__ piece, double* __restrict__ acc) {
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x, j = e / 10, c = e % 10;
+    if (j >= N) return;
+    double v = 0.0;
+    for (int64_t s = seg[j]; s < seg[j + 1]; ++s) v += piece[s * 10 + c];
+    acc[j * PA_ACC + 1 + c] += v;
 }
 
 // GV[j][k] += sgn sigma_j (corner_k + (da/dv_k / a) T_far); sigbar[j] = T_far + T_near; acc cleared
@@ -504,16 +566,17 @@ void zero(bem_ctx* c, double* p, int64_t n) {
 void panel_side(bem_ctx* c, int64_t P, const double* pts, const double* aw, const double* cw, bool self_mode,
                 double* acc) {
     const int64_t N = c->N;
-    const int64_t Np = (int64_t)(c->far64.bytes / (sizeof(double) * FAR_REC));
     const int64_t nblk = ceil_div(N, 64);
     const int64_t B = std::min<int64_t>(P, c->grad_batch);   // points per batch
     c->ad_mask.alloc(sizeof(uint64_t) * (size_t)nblk * B);
-    const int PB = 32;
-    c->ad_cnt.alloc(sizeof(int32_t) * (size_t)PB * N + sizeof(int64_t) * (N + 2));   // + alignment pad
-    int32_t* cnt = c->ad_cnt.as<int32_t>();
-    int64_t* ptr = reinterpret_cast<int64_t*>(cnt + (size_t)PB * N + (N & 1));
-    c->ad_self.alloc(sizeof(int32_t) * (size_t)B);
-    int32_t* host32 = c->host_stage.as<int32_t>();
+    const int PB = 128;   // ranges of points per panel group while counting and listing
+    c->ad_cnt.alloc(sizeof(int64_t) * (size_t)(2 * (N + 1)) + sizeof(int32_t) * (size_t)(PB + 1) * N);
+    int64_t* ptr = c->ad_cnt.as<int64_t>();
+    int64_t* seg = ptr + (N + 1);
+    int32_t* cnt = reinterpret_cast<int32_t*>(seg + (N + 1));
+    int32_t* tot = cnt + (size_t)PB * N;
+    int64_t* host = c->host_stage.as<int64_t>();
+    launch_median_records(c, nullptr, c->ev_rec);
     for (int64_t b0 = 0; b0 < P; b0 += B) {
         const int64_t nb = std::min<int64_t>(B, P - b0);
         const double* bp = pts + 3 * b0;
@@ -529,8 +592,8 @@ void panel_side(bem_ctx* c, int64_t P, const double* pts, const double* aw, cons
             KS = ceil_div(nb, span);
             c->ad_ppart.alloc(sizeof(double) * 10 * (size_t)KS * N);
             hipLaunchKernelGGL(k_pan_far_adj, dim3((unsigned)pb, (unsigned)KS), dim3(256), 0, c->stream,
-                               c->far64.as<double>(), Np, N, nb, span, bp, ba, bc, (int)self_mode, b0,
-                               c->ad_ppart.as<double>());
+                               c->ev_rec.as<double>(), N, nb, span, bp, ba, bc, (int)self_mode, b0,
+                               c->ad_ppart.as<double>(), c->ad_mask.as<uint64_t>());
             BEM_CHECK_LAUNCH();
             hipLaunchKernelGGL(k_pan_reduce, dim3((unsigned)pb), dim3(256), 0, c->stream, c->ad_ppart.as<double>(), KS,
                                N, acc);
@@ -539,33 +602,33 @@ void panel_side(bem_ctx* c, int64_t P, const double* pts, const double* aw, cons
         // near pairs: masks -> panel-major lists -> closed forms in dual numbers
         {
             KTimer t(c, "grad_panel_near");
-            const int32_t* op = nullptr;
-            if (self_mode) {
-                std::vector<int32_t> iota(nb);   // point i of the batch is the centroid of panel b0 + i
-                for (int64_t i = 0; i < nb; ++i) iota[i] = (int32_t)(b0 + i);
-                BEM_HIP(hipMemcpyAsync(c->ad_self.p, iota.data(), sizeof(int32_t) * nb, hipMemcpyHostToDevice,
-                                       c->stream));
-                BEM_HIP(hipStreamSynchronize(c->stream));
-                op = c->ad_self.as<int32_t>();
-            }
-            launch_point_mask(c, nb, bp, op, c->ad_mask.as<uint64_t>());
             const int64_t chunk = ceil_div(nb, PB);
             hipLaunchKernelGGL(k_pm_count, dim3((unsigned)nblk, PB), dim3(64), 0, c->stream, c->ad_mask.as<uint64_t>(),
                                nb, N, chunk, cnt);
             BEM_CHECK_LAUNCH();
-            hipLaunchKernelGGL(k_pm_scan, dim3(1), dim3(1024), 0, c->stream, cnt, N, PB, ptr);
+            hipLaunchKernelGGL(k_pm_rows, dim3((unsigned)nblk), dim3(64), 0, c->stream, cnt, N, PB, tot);
             BEM_CHECK_LAUNCH();
-            int64_t nnz = 0;
-            BEM_HIP(hipMemcpyAsync(host32, ptr + N, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
+            hipLaunchKernelGGL(k_pm_scan, dim3(1), dim3(1024), 0, c->stream, tot, N, ptr, seg);
+            BEM_CHECK_LAUNCH();
+            BEM_HIP(hipMemcpyAsync(host, ptr + N, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
+            BEM_HIP(hipMemcpyAsync(host + 1, seg + N, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
             BEM_HIP(hipStreamSynchronize(c->stream));
-            std::memcpy(&nnz, host32, sizeof(int64_t));
+            const int64_t nnz = host[0], S = host[1];
             if (nnz >= ((int64_t)1 << 31)) throw Error(BEM_ERR_INVALID, "gradient near list exceeds 2^31 pairs");
-            c->ad_list.alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1));
+            if (S == 0) continue;
+            // the pieces' sums, their panels and the list
+            c->ad_list.alloc(sizeof(double) * 10 * (size_t)S + sizeof(int32_t) * (size_t)(S + nnz));
+            double* piece = c->ad_list.as<double>();
+            int32_t* owner = reinterpret_cast<int32_t*>(piece + 10 * S);
+            int32_t* list = owner + S;
             hipLaunchKernelGGL(k_pm_fill, dim3((unsigned)nblk, PB), dim3(64), 0, c->stream, c->ad_mask.as<uint64_t>(),
-                               nb, N, chunk, cnt, ptr, c->ad_list.as<int32_t>());
+                               nb, N, chunk, cnt, ptr, seg, list, owner);
             BEM_CHECK_LAUNCH();
-            hipLaunchKernelGGL(k_pan_near_adj, dim3((unsigned)ceil_div(N, 4)), dim3(256), 0, c->stream, ptr,
-                               c->ad_list.as<int32_t>(), N, c->tri64.as<double>(), bp, ba, bc, (int)self_mode, b0, acc);
+            hipLaunchKernelGGL(k_pan_near_adj, dim3((unsigned)ceil_div(S, 4)), dim3(256), 0, c->stream, ptr, list, seg,
+                               owner, S, c->tri64.as<double>(), bp, ba, bc, (int)self_mode, b0, piece);
+            BEM_CHECK_LAUNCH();
+            hipLaunchKernelGGL(k_pan_near_sum, dim3((unsigned)ceil_div(10 * N, 256)), dim3(256), 0, c->stream, seg, N,
+                               piece, acc);
             BEM_CHECK_LAUNCH();
         }
     }

@@ -168,7 +168,7 @@ struct bem_ctx {
     bem::HMatrix* hm = nullptr;   // compressed operator in use (bem_compress), else the dense matrix
 
     // gradient of the streamer integrals
-    bem::DBuf ad_state, ad_part, ad_rec, ad_order, ad_mask, ad_cnt, ad_self, ad_ppart, ad_list, ad_path, ad_stage, ad_geo, ad_seg,
+    bem::DBuf ad_state, ad_part, ad_rec, ad_order, ad_mask, ad_cnt, ad_ppart, ad_list, ad_path, ad_stage, ad_geo, ad_seg,
         ad_vptr, ad_vcorner;
 
     // kernel-side launch timing (profiling mode 2): KCLK_SUB word pairs per launch slot, the
