@@ -157,6 +157,7 @@ struct bem_ctx {
     bool assembled = false;
 
     // scratch
+    bem::HBuf check_host;                  // answers of the argument checks (coherent)
     bem::HBuf gm_host;                     // Hessenberg columns of the iterations in flight, with their numbers
     uint64_t gm_seq = 0;                   // number of the last iteration queued
     bem::DBuf gm_V, gm_w, gm_z, gm_h, gm_part, gm_x, gm_r, gm_b, gm_misc;
@@ -273,6 +274,7 @@ void launch_quad_pair_integrals(bem_ctx* c, int64_t P, const double* pts, const 
 void launch_near_duffy(bem_ctx* c, int64_t nnz, const int32_t* row, const int32_t* col, double* sf);
 // records of the 7-point rule about the centroid with the densities sol (or none), in B groups (geometry.hip)
 constexpr int NODAL_COLS = 16;   // columns of a group of the nodal basis's regular pass
+void launch_check_points(bem_ctx* c, int64_t P, const double* pts, const int32_t* on_panel, int32_t* bad);
 void gmres_host(bem_ctx* c, size_t words);
 void launch_median_records(bem_ctx* c, const double* sol, DBuf& out, int B = 1, int64_t P = 0);
 void launch_panel_points(bem_ctx* c, int64_t L, const int32_t* panel, const double* bary, double offset,

@@ -48,6 +48,19 @@ __global__ __launch_bounds__(256) void k_eval_mask(const double* __restrict__ fa
     }
 }
 
+// bad[0]: a coordinate of the P points is not finite; bad[1]: an on_panel entry is outside [-1, N).
+// (bad: coherent host memory, zero on entry.)
+__global__ __launch_bounds__(256) void k_check_points(int64_t P, int64_t N, const double* __restrict__ pts,
+                                                      const int32_t* __restrict__ on_panel, int32_t* bad) {
+    bool b0 = false, b1 = false;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < 3 * P; i += (int64_t)gridDim.x * 256) {
+        b0 = b0 || !isfinite(pts[i]);
+        if (on_panel && i < P) b1 = b1 || on_panel[i] < -1 || on_panel[i] >= N;
+    }
+    if (b0) __hip_atomic_store(bad, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (b1) __hip_atomic_store(bad + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 constexpr int EV_C = 32;    // panels per mask word of k_ev_far
 constexpr int EV_Q = 128;   // near pairs per round of a wave in k_ev_near
 
@@ -384,6 +397,12 @@ static void launch_eval64(bem_ctx* c, const double* sigma, int64_t P, const doub
             BEM_CHECK_LAUNCH();
         }
     }
+}
+
+void launch_check_points(bem_ctx* c, int64_t P, const double* pts, const int32_t* on_panel, int32_t* bad) {
+    hipLaunchKernelGGL(k_check_points, dim3((unsigned)std::min<int64_t>(ceil_div(3 * P, 256), 1024)), dim3(256), 0,
+                       c->stream, P, c->N, pts, on_panel, bad);
+    BEM_CHECK_LAUNCH();
 }
 
 void launch_eval(bem_ctx* c, const double* sigma, int64_t P, const double* pts, const int32_t* on_panel, double* phi,

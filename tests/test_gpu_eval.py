@@ -54,3 +54,25 @@ def test_field_at_split_edges(bem, make, P, blocks, eta):
             for got, want in ((phi[0], po), (E[0], Eo), (E2[0], Eo)):
                 d = np.abs(got.cpu().numpy() - want)
                 assert d.max() <= 1e-10 * np.abs(want).max()
+
+
+def test_refused_points(bem):
+    """A non-finite coordinate or a panel out of range anywhere in the list is refused before anything runs."""
+    p = sphere_problem(2)
+    print("[gpu-eval] refused points", flush=True)
+    cen = np.tile(p.vert[p.tri].mean(axis=1), (2, 1))
+    on = np.tile(np.arange(p.n_tri, dtype=np.int32), 2)
+    with bem.Context.from_problem(p) as c:
+        sol = torch.ones(p.n_tri, dtype=torch.float64, device="cuda")
+        c.eval_field(sol, cen, on_panel=on)
+        for row, value in ((0, np.nan), (len(cen) - 1, np.inf), (300, -np.inf)):
+            bad = cen.copy()
+            bad[row, row % 3] = value
+            with pytest.raises(bem.BemError, match="non-finite point coordinate"):
+                c.eval_field(sol, bad, on_panel=on)
+        for row, value in ((0, -2), (len(on) - 1, p.n_tri), (300, 2**31 - 1)):
+            bad = on.copy()
+            bad[row] = value
+            with pytest.raises(bem.BemError, match="on_panel entry out of range"):
+                c.eval_field(sol, cen, on_panel=bad)
+        c.eval_field(sol, cen, on_panel=on)
