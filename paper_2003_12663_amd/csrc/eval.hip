@@ -61,12 +61,13 @@ __global__ __launch_bounds__(256) void k_check_points(int64_t P, int64_t N, cons
     if (b1) __hip_atomic_store(bad + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-constexpr int EV_C = 32;    // panels per mask word of k_ev_far
+constexpr int EV_C = 32;    // panels per mask word
+constexpr int EV_H = 16;    // panels per half word: what a range of k_ev_far is a multiple of
 constexpr int EV_Q = 128;   // near pairs per round of a wave in k_ev_near
 
 // Up to 256 points (one per lane) against the panels [span y, span (y + 1)) of the records `rec`
 // (densities in them): part[y][p] = (phi, E), and the bit masks of the pairs that are not regular,
-// mask[p][word].  on_panel: the point's own panel counts as not regular.  PHI false: no potential.
+// mask[p][half word].  on_panel: the point's own panel counts as not regular.  PHI false: no potential.
 // Bound by FP64 issue; the next panel's record is requested before a panel's arithmetic.  E at 19,732
 // centroids: 1.71 ms and 0.14 ms of k_ev_near; node by node over LDS tiles it took 2.30 ms, and 0.35 ms
 // more for a mask pass of its own and the near list with its wait of the host.  1000 points against
@@ -75,7 +76,7 @@ template <bool PHI>
 __global__ __launch_bounds__(256) void k_ev_far(const double* __restrict__ rec, int64_t N, int64_t P, int64_t span,
                                                 int64_t KS, const double* __restrict__ pts,
                                                 const int32_t* __restrict__ on_panel, double* __restrict__ part,
-                                                uint32_t* __restrict__ mask) {
+                                                uint16_t* __restrict__ mask) {
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const bool live = p < P;
     const int64_t pc = live ? p : P - 1;
@@ -131,10 +132,12 @@ __global__ __launch_bounds__(256) void k_ev_far(const double* __restrict__ rec, 
             e1 = __fma_rn(sG, t1, __fma_rn(s0, v[4], __fma_rn(s1, v[7], e1)));
             e2 = __fma_rn(sG, t2, __fma_rn(s0, v[5], __fma_rn(s1, v[8], e2)));
         } else {
-            word |= 1u << (j & (EV_C - 1));
+            word |= 1u << (j & (EV_H - 1));
         }
-        if ((j & (EV_C - 1)) == EV_C - 1 || j == j1 - 1) {   // j0 is a multiple of EV_C
-            if (live) mask[p * KS + j / EV_C] = word;
+        if ((j & (EV_H - 1)) == EV_H - 1 || j == j1 - 1) {   // j0 is a multiple of EV_H
+            uint16_t* h = mask + 2 * p * KS + j / EV_H;
+            if (live) h[0] = (uint16_t)word;
+            if (live && j == (int)N - 1 && (j & (EV_C - 1)) < EV_H) h[1] = 0;   // the last word's other half
             word = 0;
         }
     };
@@ -373,7 +376,7 @@ static void launch_eval64(bem_ctx* c, const double* sigma, int64_t P, const doub
     for (int64_t p0 = 0; p0 < P; p0 += B) {
         const int64_t nb = std::min<int64_t>(B, P - p0);
         int64_t span = 0;
-        const int64_t K = eval_split(c, nb, EV_C, &span);
+        const int64_t K = eval_split(c, nb, EV_H, &span);
         c->ev_part.alloc(sizeof(double) * 4 * (size_t)(K * nb));
         c->ev_mask.alloc(sizeof(uint32_t) * (size_t)(W * nb));
         const double* bp = pts + 3 * p0;
@@ -383,10 +386,10 @@ static void launch_eval64(bem_ctx* c, const double* sigma, int64_t P, const doub
             const dim3 grid((unsigned)ceil_div(nb, 256), (unsigned)K);
             if (phi)
                 hipLaunchKernelGGL(k_ev_far<true>, grid, dim3(256), 0, c->stream, c->ev_rec.as<double>(), N, nb, span, W,
-                                   bp, bo, c->ev_part.as<double>(), c->ev_mask.as<uint32_t>());
+                                   bp, bo, c->ev_part.as<double>(), c->ev_mask.as<uint16_t>());
             else
                 hipLaunchKernelGGL(k_ev_far<false>, grid, dim3(256), 0, c->stream, c->ev_rec.as<double>(), N, nb, span, W,
-                                   bp, bo, c->ev_part.as<double>(), c->ev_mask.as<uint32_t>());
+                                   bp, bo, c->ev_part.as<double>(), c->ev_mask.as<uint16_t>());
             BEM_CHECK_LAUNCH();
         }
         {
