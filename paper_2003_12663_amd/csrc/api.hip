@@ -476,6 +476,10 @@ bem_status bem_create(int64_t n_vert, const double* vert, int64_t n_tri, const i
     upload(c->rows_pot, c->h_rows_pot.data(), c->h_rows_pot.size(), s);
     upload(c->rows_int, c->h_rows_int.data(), c->h_rows_int.size(), s);
     upload(c->rows_flt, c->h_rows_flt.data(), c->h_rows_flt.size(), s);
+    std::vector<int32_t> rows_dir;   // potential rows that are not a floating body's
+    for (int32_t i : c->h_rows_pot)
+        if (slot[i] < 0) rows_dir.push_back(i);
+    upload(c->rows_dir, rows_dir.data(), rows_dir.size(), s);
     upload(c->row_slot, slot.data(), slot.size(), s);
     // interface-row scales (eps+ - eps-) followed by ones for the K' rows of floating bodies
     std::vector<double> scales;

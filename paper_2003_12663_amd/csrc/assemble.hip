@@ -26,6 +26,7 @@ namespace {
 // MODE 0: potential rows S_ij = sum_q w_q / |x_i - y_q|
 // MODE 1: normal-derivative rows K'_ij = n_i . sum_q w_q (x_i - y_q) / |x_i - y_q|^3,
 //         multiplied by row_scale[r]
+// MODE 2: both of a floating body's rows: S_ij to `out` and K'_ij to kout[r] (row stride N)
 // FP64: the rule about the centroid, a panel's record (density one) in its lane's registers; the
 // next row's point is requested before a row's arithmetic.  The reach test settles nearly every pair
 // without the circumcentre's distance.  Bound by FP64 issue: 16,656 potential rows of 19,732 panels
@@ -34,7 +35,8 @@ template <int MODE>
 __global__ __launch_bounds__(256) void k_far64(const double* __restrict__ rec, const double* __restrict__ tri64,
                                                int64_t N, const int32_t* __restrict__ rows, int64_t n_rows,
                                                const double* __restrict__ row_scale, double* __restrict__ out, int64_t ld,
-                                               int out_by_slot, uint64_t* __restrict__ mask, int rows_per_block) {
+                                               int out_by_slot, uint64_t* __restrict__ mask, int rows_per_block,
+                                               double* __restrict__ kout) {
     const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t jw = (int64_t)blockIdx.x * 256 + (threadIdx.x & ~63u);
     if (jw >= N) return;   // no barrier below
@@ -51,7 +53,7 @@ __global__ __launch_bounds__(256) void k_far64(const double* __restrict__ rec, c
         const double* Ti = tri64 + (int64_t)TRI_REC * i;
 #pragma unroll
         for (int c = 0; c < 3; ++c) x[c] = Ti[TR_C + c];
-        if constexpr (MODE == 1)
+        if constexpr (MODE > 0)
 #pragma unroll
             for (int c = 0; c < 3; ++c) x[3 + c] = Ti[TR_N + c];
     };
@@ -76,16 +78,17 @@ __global__ __launch_bounds__(256) void k_far64(const double* __restrict__ rec, c
                               __fma_rn(k.m2rho, pa, __fma_rn(k.rho2, v[9], T)),
                               __fma_rn(k.m2rho, pb, __fma_rn(k.rho2, v[10], T)),
                               __fma_rn(k.m2rho, pc, __fma_rn(k.rho2, v[11], T))};
-        double acc;
-        if constexpr (MODE == 0) {
-            double ir[7];
+        double acc, kp = 0.0, ir[7], g[7];
 #pragma unroll
-            for (int q = 0; q < 7; ++q) ir[q] = rsqrt_pos(r2[q]);
-            acc = sw * __fma_rn(k.kap0, ir[0], __fma_rn(k.kap, (ir[4] + ir[5]) + ir[6], (ir[1] + ir[2]) + ir[3]));
-        } else {
-            double g[7];
-#pragma unroll
-            for (int q = 0; q < 7; ++q) g[q] = med_r3(r2[q], k);
+        for (int q = 0; q < 7; ++q) {
+            if constexpr (MODE == 1) {
+                g[q] = med_r3(r2[q], k);
+            } else {
+                ir[q] = rsqrt_pos(r2[q]);
+                g[q] = ir[q] * (ir[q] * ir[q]);   // MODE 2
+            }
+        }
+        if constexpr (MODE > 0) {
             const double G = __fma_rn(k.kap0, g[0], __fma_rn(k.kap, (g[4] + g[5]) + g[6], (g[1] + g[2]) + g[3]));
             const double h0 = __fma_rn(k.kaprho, g[4], g[1]), h1 = __fma_rn(k.kaprho, g[5], g[2]);
             const double h2 = __fma_rn(k.kaprho, g[6], g[3]);
@@ -93,8 +96,14 @@ __global__ __launch_bounds__(256) void k_far64(const double* __restrict__ rec, c
             const double f0 = __fma_rn(G, t0, __fma_rn(s0, v[3], s1 * v[6]));
             const double f1 = __fma_rn(G, t1, __fma_rn(s0, v[4], s1 * v[7]));
             const double f2 = __fma_rn(G, t2, __fma_rn(s0, v[5], s1 * v[8]));
-            acc = sw * row_scale[r] * __fma_rn(x[3], f0, __fma_rn(x[4], f1, x[5] * f2));
+            kp = sw * row_scale[r] * __fma_rn(x[3], f0, __fma_rn(x[4], f1, x[5] * f2));
         }
+        if constexpr (MODE == 1)
+            acc = kp;
+        else
+            acc = sw * __fma_rn(k.kap0, ir[0], __fma_rn(k.kap, (ir[4] + ir[5]) + ir[6], (ir[1] + ir[2]) + ir[3]));
+        if constexpr (MODE == 2)
+            if (valid) kout[r * N + j] = reg ? kp : 0.0;
         if (valid) out[(out_by_slot ? r : i) * ld + j] = reg ? acc : 0.0;
         if (mask) {
             const uint64_t m = __ballot(valid && !reg);
@@ -103,7 +112,7 @@ __global__ __launch_bounds__(256) void k_far64(const double* __restrict__ rec, c
         i = i1;
         i1 = i2;
 #pragma unroll
-        for (int c = 0; c < (MODE == 1 ? 6 : 3); ++c) x[c] = xn[c];
+        for (int c = 0; c < (MODE > 0 ? 6 : 3); ++c) x[c] = xn[c];
     }
 }
 
@@ -485,7 +494,7 @@ void launch_far_assemble(bem_ctx* c) {
                         void* out, int64_t ld) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(Np / 256), (unsigned)ceil_div(nr, rpb)), dim3(256), 0, c->stream,
                            c->ev_rec.as<double>(), c->tri64.as<double>(), c->N, rows.as<int32_t>(), nr, scale,
-                           (double*)out, ld, (int)by_slot, m, rpb);
+                           (double*)out, ld, (int)by_slot, m, rpb, c->Kf.as<double>());
         BEM_CHECK_LAUNCH();
     };
     auto launch32 = [&](auto kernel, const bem::DBuf& rows, int64_t nr, const double* scale, void* out) {
@@ -502,15 +511,21 @@ void launch_far_assemble(bem_ctx* c) {
     // K' block of floating rows (FP64 in both modes) for the constraint rows
     const bool kf = nflt > 0 && (c->opt.constraint_form == 0 || c->has_sheet);
     if (!mixed || kf) launch_median_records(c, nullptr, c->ev_rec);
-    if (npot > 0) {
-        if (mixed) launch32(k_far<0>, c->rows_pot, npot, nullptr, A);
-        else launch64(k_far64<0>, c->rows_pot, npot, nullptr, false, mask, A, c->ld);
+    // FP64 with a K' block: the floating rows' two kinds share the pairs' distances (2,020 of 16,656 potential
+    // rows of 19,732 panels are floating: 0.15 + 0.20 ms in launches of their own, 0.26 together)
+    const bool both = kf && !mixed;
+    const DBuf& pot = both ? c->rows_dir : c->rows_pot;
+    const int64_t np = both ? npot - nflt : npot;
+    if (np > 0) {
+        if (mixed) launch32(k_far<0>, pot, np, nullptr, A);
+        else launch64(k_far64<0>, pot, np, nullptr, false, mask, A, c->ld);
     }
     if (nint > 0) {
         if (mixed) launch32(k_far<1>, c->rows_int, nint, scale_int, A);
         else launch64(k_far64<1>, c->rows_int, nint, scale_int, false, mask, A, c->ld);
     }
-    if (kf) launch64(k_far64<1>, c->rows_flt, nflt, scale_one, true, nullptr, c->Kf.p, c->N);
+    if (both) launch64(k_far64<2>, c->rows_flt, nflt, scale_one, false, mask, A, c->ld);
+    else if (kf) launch64(k_far64<1>, c->rows_flt, nflt, scale_one, true, nullptr, c->Kf.p, c->N);
 }
 
 void launch_near_csr(bem_ctx* c, const uint64_t* mask, int64_t T, DBuf& ptr, DBuf& row, DBuf& col, int64_t* nnz,

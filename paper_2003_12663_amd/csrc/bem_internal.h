@@ -148,7 +148,7 @@ struct bem_ctx {
     bem::DBuf tr_cases;                          // staging of the nodal basis's per-load-case line runs
     bem::DBuf far64, far32, tri64;
     bem::DBuf pan64, pan32;                 // far64 / far32 panel-major: [Np][FAR_REC]
-    bem::DBuf rows_pot, rows_int, rows_flt, row_slot;
+    bem::DBuf rows_pot, rows_dir, rows_int, rows_flt, row_slot;
     bem::DBuf A64, A32, Kf;                 // dense operator (FP64 or FP32) and the K' block of floating rows
     bem::DBuf cons_part;                    // slab sums of a floating body's constraint row
     bem::DBuf nearmask, near_ptr, near_row, near_col, near_val;
