@@ -378,11 +378,13 @@ __global__ __launch_bounds__(256) void k_constraint(const double* __restrict__ K
     const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t y = blockIdx.y;
     const int64_t a0 = s0 + y * per, a1 = (a0 + per < s1) ? a0 + per : s1;
+    const int64_t jc = j < N ? j : N - 1;
     double acc = 0.0, asum = 0.0;
+#pragma unroll 8
     for (int64_t s = a0; s < a1; ++s) {
         const int64_t i = rows_flt[s];
         const double a = tri64[(int64_t)TRI_REC * i + TR_A];
-        if (j < N) acc += a * (c_kp * Kf[s * N + j] + (i == j ? c_self : 0.0));
+        acc += a * (c_kp * Kf[s * N + jc] + (i == j ? c_self : 0.0));
         asum += a;
     }
     if (j < N) part[y * N + j] = acc;
