@@ -65,8 +65,10 @@ FLOP_FIELD_PAIR = 141
 K_LB_FAR_FETCH_KIB = 5058.2
 K_LB_FAR_WRITE_KIB = 1862.8
 K_LB_FAR_TRAFFIC_BYTES = (2.0 * K_LB_FAR_FETCH_KIB + 1.0 * K_LB_FAR_WRITE_KIB) * 1024.0
-# the same for k_lf_pass, the default one-launch-per-stage layout: not yet taken (None)
+# the same for k_lf_pass, the one-launch-per-stage layout: not taken (None)
 K_LF_PASS_TRAFFIC_BYTES = None
+# and for k_lc_trace, the default layout's one launch for all lines and steps (mostly the clusters' records)
+K_LC_TRACE_TRAFFIC_BYTES = (2.0 * 858419.1 + 1.0 * 1663974.0) * 1024.0
 FLOP_POT_PAIR = 86
 FP64_VALU_PEAK_TFLOPS = 78.6
 HBM_PEAK_GBS = 8000.0
@@ -583,8 +585,8 @@ def main():
     t1 = time.perf_counter()
     ms_step = (t1 - t0) * 1e3 / args.steps
     print(f"[bench] timed {args.steps} steps: {ms_step:.1f} ms/step", file=sys.stderr, flush=True)
-    # regular pairs and launches of the two-kernel far passes (k_lb_far) and of the one-launch stages
-    # (k_lf_pass: the last few lines by default, every stage with trace_mode 3)
+    # regular pairs and launches of the two-kernel far passes (k_lb_far), and of the launches that take
+    # whole stages (k_lf_pass) or all lines and steps (k_lc_trace, the default)
     far_launches = ctx.counter("trace_far_launches") / args.steps
     far_pairs = ctx.counter("trace_far_pairs") / args.steps
     pass_launches = ctx.counter("trace_pass_launches") / args.steps
@@ -603,7 +605,8 @@ def main():
             step()
         torch.cuda.synchronize()
         ms_step_prof = (time.perf_counter() - t2) * 1e3 / args.steps
-    fused = far_launches == 0   # one launch per stage throughout (trace_mode 3)
+    fused = far_launches == 0   # no two-kernel passes: all lines in one launch (the default), or one launch per stage
+    cluster = fused and pass_launches <= 1   # k_lc_trace
     tf_n, tf_ms = ctx.kernel_stats("trace_pass" if fused else "trace_far")
     if fused:
         far_launches, far_pairs = pass_launches, pass_pairs
@@ -627,8 +630,8 @@ def main():
                                                 "finalize", "gemv", "gmres_ortho", "gmres_iter", "eval_mask",
                                                 "eval_near_csr", "eval_far", "eval_near", "trace", "trace_far",
                                                 "trace_step", "trace_pass")}
-    # dominant kernel: the far-field pass of the field-line tracer (k_lb_far), one launch per RK4 stage,
-    # every launch of a repeat of the timed steps timed by its own clock stamps (profiling mode 2)
+    # dominant kernel: the field-line tracer's, every launch of a repeat of the timed steps timed by its own
+    # clock stamps (profiling mode 2)
     far_flop_per_launch = far_pairs * FLOP_FIELD_PAIR / far_launches
     far_avg_ms = tf_ms / tf_n if tf_n > 0 else None
     achieved = far_flop_per_launch / (far_avg_ms * 1e-3) / 1e12 if far_avg_ms else None
@@ -712,12 +715,15 @@ def main():
         "kernel_ms_profiled_step": kernel_ms,
         "streamer_integral_sum": float(I.sum().item()),
         "stop_code_counts": {str(k): int(np.sum(st_h == k)) for k in range(6)},
-        "roofline": {"kernel": ("k_lf_pass (one launch per RK4 stage of the field lines: the previous stage's "
+        "roofline": {"kernel": ("k_lc_trace (all field lines and steps in one launch, FP64: regular and near pairs, "
+                                "the exchange of partial fields and the RK4 steps)") if cluster else
+                               ("k_lf_pass (one launch per RK4 stage of the field lines: the previous stage's "
                                 "step, then the regular and near pairs of all live lines, FP64)") if fused else
                                "k_lb_far (far-field pass of the field-line tracer, FP64)", "bound": "alu",
                      "achieved": achieved, "peak": FP64_VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP64_VALU_PEAK_TFLOPS if achieved else None,
-                     "traffic": K_LF_PASS_TRAFFIC_BYTES if fused else K_LB_FAR_TRAFFIC_BYTES,
+                     "traffic": (K_LC_TRACE_TRAFFIC_BYTES if cluster else K_LF_PASS_TRAFFIC_BYTES) if fused else
+                                K_LB_FAR_TRAFFIC_BYTES,
                      "traffic_unit": "bytes per launch (HBM, counters)",
                      "flop_per_pair": FLOP_FIELD_PAIR, "pairs_per_launch": far_pairs / far_launches,
                      "launches_per_step": far_launches, "avg_launch_ms": far_avg_ms,

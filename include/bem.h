@@ -340,8 +340,9 @@ bem_status bem_panel_points(bem_ctx* ctx, int64_t L, const int32_t* panel, const
  *                finish the previous stage of their lines from the partial fields the
  *                previous launch wrote, then evaluate the new stage (at most 131072 panels);
  *                2 = one persistent launch, one workgroup per line; 0 (default) = in FP64 (and
- *                with the LINEAR basis in either precision) clusters of "trace_blocks" blocks that keep their panels in
- *                LDS (from about 27,000 panels on, read them each stage) and run all their
+ *                with the LINEAR basis in either precision) clusters of "trace_blocks" blocks
+ *                that keep their panels in LDS (from about 27,000 panels on, read them each
+ *                stage) and run all their
  *                lines' stages in one cooperative launch, exchanging partial fields through device
  *                memory; otherwise, or where that launch is refused or one of its waits reaches
  *                "trace_spin" polls, 1 while more than "trace_tail" lines are live, then 3 (1
@@ -421,14 +422,15 @@ bem_status bem_autotune(bem_ctx* ctx, const char* cache_path, int32_t* from_cach
  *  enable 0: off.
  *  enable 1: every kernel, by an event pair recorded around each launch.  Names: "geometry",
  *            "far_assemble", "near_mask_csr", "near_assemble", "finalize", "gemv", "gmres_ortho",
- *            "gmres_iter", "eval_mask", "eval_near_csr", "eval_far", "eval_near", "trace" (a
- *            whole field-line call), "trace_step" (the step kernel of a batched pass; every
- *            16th pass is timed, so its launch count is a sample and total_ms covers that
- *            sample), "gemm_f32", "gemm_f64", "gemm_rows", "bgmres_iter", "grad",
+ *            "gmres_iter", "eval_mask" and "eval_near_csr" (FP32 far field only), "eval_far",
+ *            "eval_near", "trace" (a whole field-line call), "trace_step" (the step kernel of a
+ *            batched pass; every 16th pass is timed, so its launch count is a sample and
+ *            total_ms covers that sample), "gemm_f32", "gemm_f64", "gemm_rows", "bgmres_iter",
+ *            "grad",
  *            "grad_reverse", "grad_rows_EH", "grad_panel_far", "grad_panel_near", "gemvT".
  *  enable 1: also "trace_far", every chunked far pass of the two-kernel field-line layout, and
- *            "trace_pass", every launch of the one-launch layout, timed by events carried in
- *            their own dispatches (hipExtLaunchKernelGGL), nothing added to the stream.
+ *            "trace_pass", every launch of the one-launch and cluster layouts, timed by events
+ *            carried in their own dispatches (hipExtLaunchKernelGGL), nothing added to the stream.
  *  enable 2: only "trace_far" and "trace_pass", so that all other work runs as it does
  *            unprofiled, each launch timed by the kernel itself: the earliest block start to
  *            the latest wave end on the device's constant-rate wall clock (with two line
