@@ -158,6 +158,66 @@ __global__ __launch_bounds__(256) void k_scale_div(const double* w, const double
     z[i] = o / d[i];
 }
 
+constexpr int GM_ONE_N = 2048;        // vector length and
+constexpr int64_t GM_ONE = 20480;     // basis entries up to which one block takes the orthogonalisation
+
+// The whole iteration behind the product by one block: w orthogonalised twice against V[0..kc), the next
+// Krylov vector and the product's input from it, its column to the host.  w stays in LDS; a wave
+// takes a dot product, a thread the updates of its entries.  One CU reads the basis four times, some
+// 8 us at GM_ONE entries, against four launches.  Solves of 80, 320 and 1,280 unknowns: 168 -> 140,
+// 208 -> 174, 399 -> 340 us; taken further it loses (1,214 unknowns, 39 iterations: 935 us without, 904 up
+// to 16,384 entries, 937 up to 32,768, 1,027 up to 65,536; 3,682 unknowns: 1,725 and 1,744 us).
+__global__ __launch_bounds__(1024) void k_arnoldi(const double* __restrict__ V, int64_t vstride, int n, int kc,
+                                                  const double* __restrict__ w, const double* __restrict__ d,
+                                                  double* __restrict__ out, double* __restrict__ z,
+                                                  double* __restrict__ host, uint64_t* flag, uint64_t id) {
+    __shared__ double wl[GM_ONE_N], hl[GM_ONE_N], hs[GM_ONE_N], red[16];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    for (int i = tid; i < n; i += 1024) wl[i] = w[i];
+    __syncthreads();
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int k = wv; k < kc; k += 16) {
+            const double* v = V + (int64_t)k * vstride;
+            double a = 0.0;
+#pragma unroll 8
+            for (int i = lane; i < n; i += 64) a = fma(v[i], wl[i], a);
+            a = wave_sum(a);
+            if (lane == 0) {
+                hl[k] = a;
+                hs[k] = pass == 0 ? a : hs[k] + a;
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < n; i += 1024) {
+            double s = wl[i];
+#pragma unroll 8
+            for (int k = 0; k < kc; ++k) s -= hl[k] * V[(int64_t)k * vstride + i];
+            wl[i] = s;
+        }
+        __syncthreads();
+    }
+    double q = 0.0;
+    for (int i = tid; i < n; i += 1024) q = fma(wl[i], wl[i], q);
+    q = wave_sum(q);
+    if (lane == 0) red[wv] = q;
+    __syncthreads();
+    q = 0.0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) q += red[u];
+    const double nrm = sqrt(q);
+    for (int k = tid; k < kc; k += 1024) host_put(host + k, hs[k]);
+    if (tid == 0) host_put(host + kc, nrm);
+    host_done();
+    __syncthreads();
+    if (tid == 0) host_flag(flag, id);
+    if (nrm == 0.0) return;
+    for (int i = tid; i < n; i += 1024) {
+        const double o = wl[i] / nrm;
+        out[i] = o;
+        z[i] = o / d[i];
+    }
+}
+
 // r = b - Ax
 __global__ __launch_bounds__(256) void k_residual(const double* __restrict__ b, const double* __restrict__ Ax, int64_t n,
                                                   double* __restrict__ r) {
@@ -232,6 +292,15 @@ uint64_t queue_iteration(Work& W, int j) {
     else
         launch_matvec(c, W.z, W.w, W.s);
     KTimer to(c, "gmres_ortho");
+    const uint64_t id = ++c->gm_seq;
+    double* next = W.V + (int64_t)kc * W.vs;
+    double* col = W.col + (j & 1) * (W.m + 2);
+    if (n <= GM_ONE_N && kc <= GM_ONE_N && n * kc <= GM_ONE) {
+        hipLaunchKernelGGL(k_arnoldi, dim3(1), dim3(1024), 0, W.s, W.V, W.vs, (int)n, kc, W.w, c->diag.as<double>(), next,
+                           W.z, col, W.flag + (j & 1), id);
+        BEM_CHECK_LAUNCH();
+        return id;
+    }
     const bool sum = GB <= GM_SUM;
     // blocks per dot product: one element per thread, fewer where there are many products
     const int G = std::min(W.G, std::max(8, 1024 / kc));
@@ -260,9 +329,8 @@ uint64_t queue_iteration(Work& W, int j) {
         hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(64), 0, W.s, W.part2, GB, 1, W.Hcol + kc, none, 0, 1);
         BEM_CHECK_LAUNCH();
     }
-    const uint64_t id = ++c->gm_seq;
     hipLaunchKernelGGL(k_scale_div, dim3(GB), dim3(256), 0, W.s, W.w, W.part, sum ? GB : 0, W.Hcol + kc, c->diag.as<double>(),
-                       n, W.V + (int64_t)kc * W.vs, W.z, W.Hcol, j, W.col + (j & 1) * (W.m + 2), W.flag + (j & 1), id);
+                       n, next, W.z, W.Hcol, j, col, W.flag + (j & 1), id);
     BEM_CHECK_LAUNCH();
     return id;
 }

@@ -1,4 +1,5 @@
-"""GMRES at the edges of its iteration: vectors of less than one block up to more than the 128 blocks
+"""GMRES at the edges of its iteration: vectors that one block takes for all or the first of its
+iterations, of less than one block of 256 up to more than the 128 blocks
 that sum a dot product's partials in the kernels that use them, restarts every few iterations,
 iteration limits in the middle of a cycle and right after a queued iteration, and solves in a row on
 the same context (the same to the bit).
@@ -30,7 +31,8 @@ def _residual(c, p, sol):
 
 
 @pytest.mark.parametrize("make,restart", [
-    (lambda: sphere_problem(0), 100), (lambda: sphere_problem(1), 3), (lambda: floating_shell_problem(2), 7),
+    (lambda: sphere_problem(0), 100), (lambda: sphere_problem(3), 100), (lambda: coax_problem(0.018), 100),
+    (lambda: sphere_problem(1), 3), (lambda: floating_shell_problem(2), 7),
     (lambda: coax_problem(0.012), 100), (lambda: coax_problem(0.012), 20), (lambda: coax_problem(0.0028), 100)])
 def test_gmres_residual(bem, make, restart):
     p = make()
