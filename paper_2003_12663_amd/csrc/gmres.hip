@@ -42,10 +42,10 @@ __global__ __launch_bounds__(256) void k_dots(const double* __restrict__ V, int6
 
 // h[k] = sum_b part[k * G + b];  H[k] (+)= h[k].  One wave per k: lane l sums b = l, l + 64, ...
 // in order, then a fixed-order butterfly (a thread summing all G partials in turn was a chain of
-// G dependent adds behind their loads).
+// G dependent adds behind their loads).  host (one k): the result, then `id`, also to the host.
 __global__ __launch_bounds__(64) void k_reduce_parts(const double* __restrict__ part, int G, int kcount,
                                                      double* __restrict__ h, double* __restrict__ Hcol, int accumulate,
-                                                     int take_sqrt) {
+                                                     int take_sqrt, double* host, uint64_t* flag, uint64_t id) {
     const int k = blockIdx.x;
     if (k >= kcount) return;
     double s = 0.0;
@@ -55,6 +55,11 @@ __global__ __launch_bounds__(64) void k_reduce_parts(const double* __restrict__ 
     if (take_sqrt) s = sqrt(s);
     h[k] = s;
     if (Hcol) Hcol[k] = accumulate ? Hcol[k] + s : s;
+    if (host) {
+        host_put(host, s);
+        host_done();
+        host_flag(flag, id);
+    }
 }
 
 constexpr int64_t GM_SUM = 128;   // vector blocks of 256 (see the head of the file)
@@ -258,25 +263,38 @@ struct Work {
     double *V, *w, *z, *h, *part, *part2, *Hcol, *misc;
     double* host;    // pinned host staging
     double* col;     // two columns in coherent host memory,
-    uint64_t* flag;  // and the numbers of the iterations that filled them
+    double* norm;    // a norm,
+    uint64_t* flag;  // and the numbers of the iterations and the norm that filled them
     hipStream_t s;
     bool transpose = false;   // solve with A^T (same Jacobi diagonal)
     dim3 g1() const { return dim3((unsigned)ceil_div(n, 256)); }
 };
 
-// squared-norm -> sqrt into dst[0] (device); also returns it on the host if asked
-void device_norm(Work& W, const double* v, double* dst) {
+// Waits until the host's word `flag` has reached `id`; errors of the stream are raised.
+void wait_flag(Work& W, const uint64_t* flag, uint64_t id) {
+    for (int64_t spin = 1; __atomic_load_n(flag, __ATOMIC_ACQUIRE) < id; ++spin) {
+        if ((spin & 0xffff) != 0) continue;
+        const hipError_t e = hipStreamQuery(W.s);
+        if (e == hipErrorNotReady) continue;
+        BEM_HIP(e);
+        if (__atomic_load_n(flag, __ATOMIC_ACQUIRE) < id) throw Error(BEM_ERR_HIP, "GMRES kernels ended without their answer");
+    }
+}
+
+// |v| into W.misc and, numbered by the value returned, to the host
+uint64_t queue_norm(Work& W, const double* v) {
+    const uint64_t id = ++W.c->gm_seq;
     hipLaunchKernelGGL(k_dots, dim3(W.G, 1), dim3(256), 0, W.s, v, (int64_t)0, W.n, v, W.part, W.G);
     BEM_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(64), 0, W.s, W.part, W.G, 1, dst, (double*)nullptr, 0, 1);
+    hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(64), 0, W.s, W.part, W.G, 1, W.misc, (double*)nullptr, 0, 1, W.norm,
+                       W.flag + 2, id);
     BEM_CHECK_LAUNCH();
+    return id;
 }
 
 double host_norm(Work& W, const double* v) {
-    device_norm(W, v, W.misc);
-    BEM_HIP(hipMemcpyAsync(W.host, W.misc, sizeof(double), hipMemcpyDeviceToHost, W.s));
-    BEM_HIP(hipStreamSynchronize(W.s));
-    return W.host[0];
+    wait_flag(W, W.flag + 2, queue_norm(W, v));
+    return *W.norm;
 }
 
 // Queue iteration j: w = A z, orthogonalised twice against V[0..j], V[j + 1] and the next z from it, its
@@ -320,13 +338,15 @@ uint64_t queue_iteration(Work& W, int j) {
                 hipLaunchKernelGGL(k_dots, dim3(G, kc), dim3(256), 0, W.s, W.V, W.vs, n, W.w, W.part, G);
                 BEM_CHECK_LAUNCH();
             }
-            hipLaunchKernelGGL(k_reduce_parts, dim3((unsigned)kc), dim3(64), 0, W.s, W.part, G, kc, W.h, W.Hcol, pass, 0);
+            hipLaunchKernelGGL(k_reduce_parts, dim3((unsigned)kc), dim3(64), 0, W.s, W.part, G, kc, W.h, W.Hcol, pass, 0,
+                               none, (uint64_t*)nullptr, (uint64_t)0);
             BEM_CHECK_LAUNCH();
             hipLaunchKernelGGL(k_orth<false>, dim3(GB), dim3(1024), 0, W.s, W.V, W.vs, n, kc, W.h, 0, W.Hcol, 0, W.w,
                                none, pass == 1 ? W.part2 : none);
             BEM_CHECK_LAUNCH();
         }
-        hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(64), 0, W.s, W.part2, GB, 1, W.Hcol + kc, none, 0, 1);
+        hipLaunchKernelGGL(k_reduce_parts, dim3(1), dim3(64), 0, W.s, W.part2, GB, 1, W.Hcol + kc, none, 0, 1, none,
+                           (uint64_t*)nullptr, (uint64_t)0);
         BEM_CHECK_LAUNCH();
     }
     hipLaunchKernelGGL(k_scale_div, dim3(GB), dim3(256), 0, W.s, W.w, W.part, sum ? GB : 0, W.Hcol + kc, c->diag.as<double>(),
@@ -335,18 +355,12 @@ uint64_t queue_iteration(Work& W, int j) {
     return id;
 }
 
-// Waits until iteration `id` (with column slot) has handed its column over; errors of the stream are raised.
-void wait_iteration(Work& W, int slot, uint64_t id) {
-    for (int64_t spin = 1;; ++spin) {
-        if (__atomic_load_n(W.flag + slot, __ATOMIC_ACQUIRE) >= id) return;
-        if ((spin & 0xffff) == 0) {
-            const hipError_t e = hipStreamQuery(W.s);
-            if (e == hipErrorNotReady) continue;
-            BEM_HIP(e);
-            if (__atomic_load_n(W.flag + slot, __ATOMIC_ACQUIRE) >= id) return;
-            throw Error(BEM_ERR_HIP, "GMRES iteration ended without its column");
-        }
-    }
+// The first Krylov vector r / |r| (|r| in W.misc) and iteration 0 from it.
+uint64_t queue_start(Work& W, const double* r) {
+    hipLaunchKernelGGL(k_scale_div, W.g1(), dim3(256), 0, W.s, r, W.misc, 0, W.misc, W.c->diag.as<double>(), W.n, W.V, W.z,
+                       W.Hcol, 0, (double*)nullptr, (uint64_t*)nullptr, (uint64_t)0);
+    BEM_CHECK_LAUNCH();
+    return queue_iteration(W, 0);
 }
 
 // One GMRES solve of A x = b (x overwritten; zero initial guess).
@@ -357,12 +371,17 @@ int gmres_core(Work& W, const double* b, double* x, double tol, int max_iter, in
     const double* d = c->diag.as<double>();
     hipLaunchKernelGGL(k_fill, W.g1(), dim3(256), 0, W.s, x, n, 0.0);
     BEM_CHECK_LAUNCH();
-    const double bnorm = host_norm(W, b);
+    // the first iteration is queued before the host has |b|
+    const uint64_t norm_id = queue_norm(W, b);
+    uint64_t id = queue_start(W, b);
     std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m + 1);
+    wait_flag(W, W.flag + 2, norm_id);
+    const double bnorm = *W.norm;
     int iters = 0;
     double relres = 0.0;
     bool converged = false;
     if (bnorm == 0.0) {
+        BEM_HIP(hipStreamSynchronize(W.s));   // the iteration on its way writes to host memory
         *iters_out = 0;
         *relres_out = 0.0;
         return 0;
@@ -387,20 +406,18 @@ int gmres_core(Work& W, const double* b, double* x, double tol, int max_iter, in
             break;
         }
         if (iters >= max_iter) break;
-        hipLaunchKernelGGL(k_scale_div, W.g1(), dim3(256), 0, W.s, r, W.misc, 0, W.misc, d, n, W.V, W.z, W.Hcol, 0,
-                           (double*)nullptr, (uint64_t*)nullptr, (uint64_t)0);
-        BEM_CHECK_LAUNCH();
+        if (iters > 0) id = queue_start(W, r);
         std::fill(g.begin(), g.end(), 0.0);
         std::fill(H.begin(), H.end(), 0.0);
         g[0] = beta;
         int jend = 0;
-        uint64_t id = queue_iteration(W, 0), id_next = 0;
+        uint64_t id_next = 0;
         double r_last = relres, r_prev = relres;
         for (int j = 0; j < m; ++j) {
             // the residual this iteration leads to if it falls by the last one's factor
             const bool more = j + 1 < m && iters + 1 < max_iter, ahead = more && r_last * (r_last / r_prev) > tol;
             if (ahead) id_next = queue_iteration(W, j + 1);
-            wait_iteration(W, j & 1, id);
+            wait_flag(W, W.flag + (j & 1), id);
             const double* col = W.col + (j & 1) * (W.m + 2);
             for (int k = 0; k <= j + 1; ++k) H[(size_t)k * m + j] = col[k];
             const double hn = col[j + 1];
@@ -433,9 +450,8 @@ int gmres_core(Work& W, const double* b, double* x, double tol, int max_iter, in
         BEM_HIP(hipMemcpyAsync(W.h, W.host, sizeof(double) * jend, hipMemcpyHostToDevice, W.s));
         hipLaunchKernelGGL(k_update_x, W.g1(), dim3(256), 0, W.s, W.V, W.vs, n, jend, W.h, d, x);
         BEM_CHECK_LAUNCH();
-        // the pinned staging buffer is reused right away: wait for the copy
-        BEM_HIP(hipStreamSynchronize(W.s));
     }
+    if (iters == 0) BEM_HIP(hipStreamSynchronize(W.s));   // as above
     *iters_out = iters;
     *relres_out = relres;
     return converged ? 0 : 1;
@@ -474,9 +490,10 @@ static void setup_work(bem_ctx* c, Work& W) {
     W.part2 = W.part + p1;
     W.misc = c->gm_r.as<double>() + 2 * W.vs;
     W.host = c->host_stage.as<double>();
-    gmres_host(c, 2 + 2 * (size_t)(W.m + 2));
+    gmres_host(c, 4 + 2 * (size_t)(W.m + 2));
     W.flag = c->gm_host.as<uint64_t>();
-    W.col = c->gm_host.as<double>() + 2;
+    W.norm = c->gm_host.as<double>() + 3;
+    W.col = c->gm_host.as<double>() + 4;
 }
 
 // A^T x = b (FP64 operator only): the adjoint solve of the gradient.

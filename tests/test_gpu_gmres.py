@@ -78,3 +78,17 @@ def test_gmres_batched_residual(bem, nrhs, restart, mixed):
             res = (b[r] - c.matvec(sol[r:r + 1]).reshape(-1)).norm().item()
             assert res <= tol * b[r].norm().item() + 1e-13 * b.norm(dim=1).max().item()
         assert torch.equal(sol[1], torch.zeros_like(sol[1]))
+
+
+def test_gmres_zero_right_hand_side_and_loose_tolerance(bem):
+    """Solves that end before their first iteration, which is already queued, and normal ones after them."""
+    p = sphere_problem(2)
+    print("[gpu-gmres] zero right-hand side", flush=True)
+    with bem.Context.from_problem(p) as c:
+        c.assemble()
+        ref, _ = c.solve(p.body_V, tol=1e-10)
+        for V, tol in ((np.zeros_like(p.body_V), 1e-10), (p.body_V, 2.0)):
+            sol, info = c.solve(V, tol=tol)
+            assert info["iters"] == 0 and info["converged"] and torch.equal(sol, torch.zeros_like(sol))
+            sol, _ = c.solve(p.body_V, tol=1e-10)
+            assert torch.equal(sol, ref)
