@@ -30,7 +30,7 @@ namespace {
 // FP64: the rule about the centroid, a panel's record (density one) in its lane's registers; the
 // next row's point is requested before a row's arithmetic.  The reach test settles nearly every pair
 // without the circumcentre's distance.  Bound by FP64 issue: 16,656 potential rows of 19,732 panels
-// 1.22 ms (node by node 1.41), 3,076 derivative rows 0.25 ms (0.32).
+// 1.22 ms (node by node 1.41), 3,076 and 2,020 derivative rows 0.50 ms (0.63).
 template <int MODE>
 __global__ __launch_bounds__(256) void k_far64(const double* __restrict__ rec, const double* __restrict__ tri64,
                                                int64_t N, const int32_t* __restrict__ rows, int64_t n_rows,

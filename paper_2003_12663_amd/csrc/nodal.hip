@@ -157,7 +157,8 @@ __device__ __forceinline__ double hat_value(const double* __restrict__ T, int c,
 // on the second orbit), so with f_q the kernel at the nodes, U = sum w f and h_i = w_1 f_1i + rho w_2
 // f_2i its integral is U / 3 + s (h_k - (h_0 + h_1 + h_2) / 3).  A corner lies within reach of its
 // triangle, so corners are looked for only there.  Bound by FP64 issue; the next triangle's record is
-// requested before a triangle's arithmetic.
+// requested before a triangle's arithmetic.  9,036 vertices, 18,064 triangles: 1.17 ms; node by node, with
+// groups of consecutive vertices (2.03 visits) and no request ahead, 1.77.
 template <class T, bool KP>   // T: stored type, double (FP64) or float (MIXED)
 __global__ __launch_bounds__(256) void k_nodal_regular(int64_t nr, int64_t nv, int64_t ld, int64_t n_rt,
                                                        const double* __restrict__ vert,
