@@ -14,9 +14,11 @@
 // 4-5 us to queue one), so up to GM_SUM vector blocks the sums over a dot
 // product's partials are taken by the kernels that use them and the second
 // dot products by the first update: 5 launches where separate sums take 9.
-// Above it every block would read as many partials as vector entries.  1,280
-// unknowns, 13 iterations, with assembly and evaluation: 1.05 -> 0.56 ms;
-// 19,733 unknowns, 61 iterations: 31.0 -> 29.8 ms, of which 27.8 in the products.
+// Above it every block would read as many partials as vector entries.  Small
+// systems take one launch (k_arnoldi).  1,280 unknowns, 13 iterations, with
+// assembly and evaluation: 1.05 ms before, 0.56 with five launches, 0.48 with
+// one; 19,733 unknowns, 61 iterations: 31.0 -> 29.3 ms, of which 27.7 in the
+// products.
 #include <algorithm>
 #include <cmath>
 #include <vector>
