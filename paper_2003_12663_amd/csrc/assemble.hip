@@ -35,7 +35,7 @@ template <int MODE>
 __global__ __launch_bounds__(256) void k_far64(const double* __restrict__ rec, const double* __restrict__ tri64,
                                                int64_t N, const int32_t* __restrict__ rows, int64_t n_rows,
                                                const double* __restrict__ row_scale, double* __restrict__ out, int64_t ld,
-                                               int out_by_slot, uint64_t* __restrict__ mask, int rows_per_block,
+                                               uint64_t* __restrict__ mask, int rows_per_block,
                                                double* __restrict__ kout) {
     const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t jw = (int64_t)blockIdx.x * 256 + (threadIdx.x & ~63u);
@@ -104,11 +104,9 @@ __global__ __launch_bounds__(256) void k_far64(const double* __restrict__ rec, c
             acc = sw * __fma_rn(k.kap0, ir[0], __fma_rn(k.kap, (ir[4] + ir[5]) + ir[6], (ir[1] + ir[2]) + ir[3]));
         if constexpr (MODE == 2)
             if (valid) kout[r * N + j] = reg ? kp : 0.0;
-        if (valid) out[(out_by_slot ? r : i) * ld + j] = reg ? acc : 0.0;
-        if (mask) {
-            const uint64_t m = __ballot(valid && !reg);
-            if ((threadIdx.x & 63) == 0) mask[(jw >> 6) * N + i] = m;
-        }
+        if (valid) out[i * ld + j] = reg ? acc : 0.0;
+        const uint64_t m = __ballot(valid && !reg);
+        if ((threadIdx.x & 63) == 0) mask[(jw >> 6) * N + i] = m;
         i = i1;
         i1 = i2;
 #pragma unroll
@@ -116,20 +114,23 @@ __global__ __launch_bounds__(256) void k_far64(const double* __restrict__ rec, c
     }
 }
 
-// FP32: node by node, classified in FP64 (template argument MODE as above)
-template <int MODE>
-__global__ __launch_bounds__(256) void k_far(const double* __restrict__ far64, const float* __restrict__ farR, int64_t Np,
+// MIXED: node by node, classified in FP64 (template argument MODE as above).  R float: the matrix's FP32 rows;
+// R double: the K' block of floating bodies (out_by_slot, no marks).  The constraint rows made from
+// that block meet FP32 products in a solve of several load cases, which carry an ulp of them to 1e-9 and
+// more of the solution (gmres_batched.hip), so they keep this order of operations and not k_far64's.
+template <int MODE, typename R>
+__global__ __launch_bounds__(256) void k_far(const double* __restrict__ far64, const R* __restrict__ farR, int64_t Np,
                                              const double* __restrict__ tri64, int64_t N,
                                              const int32_t* __restrict__ rows, int64_t n_rows,
-                                             const double* __restrict__ row_scale, float* __restrict__ out, int64_t ld,
-                                             uint64_t* __restrict__ mask, int rows_per_block) {
+                                             const double* __restrict__ row_scale, R* __restrict__ out, int64_t ld,
+                                             int out_by_slot, uint64_t* __restrict__ mask, int rows_per_block) {
     const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;   // < Np always
     const bool valid = j < N;
     const double ccx = far64[(int64_t)(FR_CC + 0) * Np + j];
     const double ccy = far64[(int64_t)(FR_CC + 1) * Np + j];
     const double ccz = far64[(int64_t)(FR_CC + 2) * Np + j];
     const double rr = far64[(int64_t)FR_RR * Np + j];
-    float qx[7], qy[7], qz[7], qw[7];
+    R qx[7], qy[7], qz[7], qw[7];
 #pragma unroll
     for (int q = 0; q < 7; ++q) {
         qx[q] = farR[(int64_t)(FR_X + q) * Np + j];
@@ -145,36 +146,38 @@ __global__ __launch_bounds__(256) void k_far(const double* __restrict__ far64, c
         const double* Ti = tri64 + (int64_t)TRI_REC * i;
         const double xi0 = Ti[TR_C + 0], xi1 = Ti[TR_C + 1], xi2 = Ti[TR_C + 2];
         const bool regular = is_regular(xi0 - ccx, xi1 - ccy, xi2 - ccz, rr) && (j != i);
-        const float x0 = (float)xi0, x1 = (float)xi1, x2 = (float)xi2;
-        float acc;
+        const R x0 = (R)xi0, x1 = (R)xi1, x2 = (R)xi2;
+        R acc;
         if (MODE == 0) {
-            float s = (float)0;
+            R s = (R)0;
 #pragma unroll
             for (int q = 0; q < 7; ++q) {
-                const float dx = x0 - qx[q], dy = x1 - qy[q], dz = x2 - qz[q];
-                const float r2 = dx * dx + dy * dy + dz * dz;
+                const R dx = x0 - qx[q], dy = x1 - qy[q], dz = x2 - qz[q];
+                const R r2 = dx * dx + dy * dy + dz * dz;
                 s += qw[q] * rsqrt_pos(r2);
             }
             acc = s;
         } else {
-            float f0 = 0, f1 = 0, f2 = 0;
+            R f0 = 0, f1 = 0, f2 = 0;
 #pragma unroll
             for (int q = 0; q < 7; ++q) {
-                const float dx = x0 - qx[q], dy = x1 - qy[q], dz = x2 - qz[q];
-                const float r2 = dx * dx + dy * dy + dz * dz;
-                const float ir = rsqrt_pos(r2);
-                const float t = qw[q] * ir * ir * ir;
+                const R dx = x0 - qx[q], dy = x1 - qy[q], dz = x2 - qz[q];
+                const R r2 = dx * dx + dy * dy + dz * dz;
+                const R ir = rsqrt_pos(r2);
+                const R t = qw[q] * ir * ir * ir;
                 f0 += t * dx;
                 f1 += t * dy;
                 f2 += t * dz;
             }
-            const float n0 = (float)Ti[TR_N + 0], n1 = (float)Ti[TR_N + 1], n2 = (float)Ti[TR_N + 2];
-            acc = (n0 * f0 + n1 * f1 + n2 * f2) * (float)row_scale[r];
+            const R n0 = (R)Ti[TR_N + 0], n1 = (R)Ti[TR_N + 1], n2 = (R)Ti[TR_N + 2];
+            acc = (n0 * f0 + n1 * f1 + n2 * f2) * (R)row_scale[r];
         }
-        const float val = regular ? acc : (float)0;
-        if (valid) out[i * ld + j] = val;
-        const uint64_t m = __ballot(valid && !regular);
-        if (wave_live && (threadIdx.x & 63) == 0) mask[(j >> 6) * N + i] = m;
+        const R val = regular ? acc : (R)0;
+        if (valid) out[(out_by_slot ? r : i) * ld + j] = val;
+        if (mask) {
+            const uint64_t m = __ballot(valid && !regular);
+            if (wave_live && (threadIdx.x & 63) == 0) mask[(j >> 6) * N + i] = m;
+        }
     }
 }
 
@@ -492,42 +495,42 @@ void launch_far_assemble(bem_ctx* c) {
     const bool mixed = c->opt.precision == BEM_MIXED;
     uint64_t* mask = c->nearmask.as<uint64_t>();
     const int rpb = c->tune_far_rows;
-    auto launch64 = [&](auto kernel, const bem::DBuf& rows, int64_t nr, const double* scale, bool by_slot, uint64_t* m,
-                        void* out, int64_t ld) {
+    auto launch64 = [&](auto kernel, const bem::DBuf& rows, int64_t nr, const double* scale) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(Np / 256), (unsigned)ceil_div(nr, rpb)), dim3(256), 0, c->stream,
                            c->ev_rec.as<double>(), c->tri64.as<double>(), c->N, rows.as<int32_t>(), nr, scale,
-                           (double*)out, ld, (int)by_slot, m, rpb, c->Kf.as<double>());
+                           c->A64.as<double>(), c->ld, mask, rpb, c->Kf.as<double>());
         BEM_CHECK_LAUNCH();
     };
-    auto launch32 = [&](auto kernel, const bem::DBuf& rows, int64_t nr, const double* scale, void* out) {
+    auto launch_nodes = [&](auto kernel, auto* nodes, const bem::DBuf& rows, int64_t nr, const double* scale, auto* out,
+                            int64_t ld, bool by_slot) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(Np / 256), (unsigned)ceil_div(nr, rpb)), dim3(256), 0, c->stream,
-                           c->far64.as<double>(), c->far32.as<float>(), Np, c->tri64.as<double>(), c->N,
-                           rows.as<int32_t>(), nr, scale, (float*)out, c->ld, mask, rpb);
+                           c->far64.as<double>(), nodes, Np, c->tri64.as<double>(), c->N, rows.as<int32_t>(), nr, scale,
+                           out, ld, (int)by_slot, by_slot ? (uint64_t*)nullptr : mask, rpb);
         BEM_CHECK_LAUNCH();
     };
     const int64_t npot = (int64_t)c->h_rows_pot.size(), nint = (int64_t)c->h_rows_int.size();
     const int64_t nflt = (int64_t)c->h_rows_flt.size();
     double* scale_int = c->gm_misc.as<double>();            // (eps+ - eps-) per interface row
     double* scale_one = scale_int + (nint > 0 ? nint : 1);  // 1 per floating row
-    void* A = mixed ? c->A32.p : c->A64.p;
     // K' block of floating rows (FP64 in both modes) for the constraint rows
     const bool kf = nflt > 0 && (c->opt.constraint_form == 0 || c->has_sheet);
-    if (!mixed || kf) launch_median_records(c, nullptr, c->ev_rec);
-    // FP64 with a K' block: the floating rows' two kinds share the pairs' distances (2,020 of 16,656 potential
+    if (mixed) {
+        const float* nodes = c->far32.as<float>();
+        float* A = c->A32.as<float>();
+        if (npot > 0) launch_nodes(k_far<0, float>, nodes, c->rows_pot, npot, nullptr, A, c->ld, false);
+        if (nint > 0) launch_nodes(k_far<1, float>, nodes, c->rows_int, nint, scale_int, A, c->ld, false);
+        if (kf)
+            launch_nodes(k_far<1, double>, (const double*)c->far64.as<double>(), c->rows_flt, nflt, scale_one,
+                         c->Kf.as<double>(), c->N, true);
+        return;
+    }
+    launch_median_records(c, nullptr, c->ev_rec);
+    // with a K' block the floating rows' two kinds share the pairs' distances (2,020 of 16,656 potential
     // rows of 19,732 panels are floating: 0.15 + 0.20 ms in launches of their own, 0.26 together)
-    const bool both = kf && !mixed;
-    const DBuf& pot = both ? c->rows_dir : c->rows_pot;
-    const int64_t np = both ? npot - nflt : npot;
-    if (np > 0) {
-        if (mixed) launch32(k_far<0>, pot, np, nullptr, A);
-        else launch64(k_far64<0>, pot, np, nullptr, false, mask, A, c->ld);
-    }
-    if (nint > 0) {
-        if (mixed) launch32(k_far<1>, c->rows_int, nint, scale_int, A);
-        else launch64(k_far64<1>, c->rows_int, nint, scale_int, false, mask, A, c->ld);
-    }
-    if (both) launch64(k_far64<2>, c->rows_flt, nflt, scale_one, false, mask, A, c->ld);
-    else if (kf) launch64(k_far64<1>, c->rows_flt, nflt, scale_one, true, nullptr, c->Kf.p, c->N);
+    const int64_t np = kf ? npot - nflt : npot;
+    if (np > 0) launch64(k_far64<0>, kf ? c->rows_dir : c->rows_pot, np, nullptr);
+    if (nint > 0) launch64(k_far64<1>, c->rows_int, nint, scale_int);
+    if (kf) launch64(k_far64<2>, c->rows_flt, nflt, scale_one);
 }
 
 void launch_near_csr(bem_ctx* c, const uint64_t* mask, int64_t T, DBuf& ptr, DBuf& row, DBuf& col, int64_t* nnz,

@@ -16,6 +16,14 @@
 // right-hand sides cannot break them down).  Orthogonalisation is CGS2 in
 // FP64 on the device; the host reads one Hessenberg column per recurrence
 // and iteration.
+//
+// The order of the FP64 sums is part of the mixed mode's results: an ulp in a
+// basis vector flips some FP32 roundings of the next product's input, and from
+// there the recurrences part by the FP32 products' own noise (1e-9 to 1e-8 of
+// the solution, all of it within the tolerance).  So the mixed mode keeps one
+// order, whatever FP64 mode does: dot products split by their number
+// (dot_split), partials summed one after another (SERIAL), norms by the same
+// two kernels.
 #include <cmath>
 #include <vector>
 
@@ -99,19 +107,28 @@ __global__ __launch_bounds__(256) void k_b_dots(const double* __restrict__ V, in
         part[((int64_t)r * m1 + k0 + q) * G + blockIdx.x] = (red[q][0] + red[q][1]) + (red[q][2] + red[q][3]);
 }
 
-// nrm[r * nstride] = sqrt(sum_b part), one wave per vector
+// nrm[r * nstride] = sqrt(sum_b part), one wave per vector; SERIAL: the sum one after another
+template <bool SERIAL>
 __global__ __launch_bounds__(64) void k_b_norm(const double* __restrict__ part, int G, double* __restrict__ nrm,
                                                int nstride) {
+    const double* p = part + (int64_t)blockIdx.x * G;
     double s = 0.0;
-    for (int b = threadIdx.x; b < G; b += 64) s += part[(int64_t)blockIdx.x * G + b];
-    s = wave_sum(s);
+    if constexpr (SERIAL) {
+        if (threadIdx.x == 0)
+#pragma unroll 8
+            for (int b = 0; b < G; ++b) s += p[b];
+    } else {
+        for (int b = threadIdx.x; b < G; b += 64) s += p[b];
+        s = wave_sum(s);
+    }
     if (threadIdx.x == 0) nrm[(int64_t)blockIdx.x * nstride] = sqrt(s);
 }
 
 // W[r] -= sum_k h[r][k] V[r][k] with h[r][k] the sum of the G partials of k_b_dots, taken by every block in
 // the same order; block 0 of a vector sets Hcol[r][k] to it or adds it.  norm: also the partials of
-// |W[r]|^2 of the result, norm[r gridDim.x + block].  (A launch of its own for the sums took 5.7 us,
-// three times an iteration.)
+// |W[r]|^2 of the result, norm[r gridDim.x + block].  SERIAL: the partials one after another, a lane a
+// sum.  (A launch of its own for the sums took 5.7 us, three times an iteration.)
+template <bool SERIAL>
 __global__ __launch_bounds__(256) void k_b_orth(const double* __restrict__ V, int m1, int64_t ld, int64_t n, int kcount,
                                                 const double* __restrict__ part, int G, double* __restrict__ Hcol,
                                                 int hstride, int accumulate, double* __restrict__ W,
@@ -123,13 +140,15 @@ __global__ __launch_bounds__(256) void k_b_orth(const double* __restrict__ V, in
     double s = i < n ? w[i] : 0.0;
     for (int k0 = 0; k0 < kcount; k0 += 256) {
         const int nk = kcount - k0 < 256 ? kcount - k0 : 256;
-        for (int k = tid >> 3; k < ((nk + 31) & ~31); k += 32) {   // 8 lanes a sum
+        constexpr int LS = SERIAL ? 1 : 8;   // lanes a sum
+        for (int k = tid / LS; k < ((nk + 256 / LS - 1) / (256 / LS)) * (256 / LS); k += 256 / LS) {
             double a = 0.0;
             if (k < nk)
-                for (int b = tid & 7; b < G; b += 8) a += part[((int64_t)r * m1 + k0 + k) * G + b];
+#pragma unroll 8
+                for (int b = tid % LS; b < G; b += LS) a += part[((int64_t)r * m1 + k0 + k) * G + b];
 #pragma unroll
-            for (int o = 4; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
-            if (k < nk && (tid & 7) == 0) {
+            for (int o = LS / 2; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+            if (k < nk && tid % LS == 0) {
                 hl[k] = a;
                 double* H = Hcol + (int64_t)r * hstride + k0 + k;
                 if (blockIdx.x == 0) *H = accumulate ? *H + a : a;
@@ -276,19 +295,26 @@ void apply(BW& w, const double* src, int64_t sstride, bool exact) {
     product(w, exact);
 }
 
-// blocks per dot product: about 2048 blocks per launch in total, each at least a few waves of work
+// blocks per dot product of `ndots`: about 2048 blocks per launch in total, each at least a few waves of work
 int dot_split(const BW& w, int ndots) {
     const int64_t g = 2048 / std::max(ndots, 1);
     return (int)std::max<int64_t>(1, std::min<int64_t>(g, w.G));
 }
 
-// norms of the nr vectors v[r * ld] into w.h[r * hs] and to the host
-void norms(BW& w, const double* v, std::vector<double>& out) {
+// norms of the nr vectors v[r * ld] into dst[r * hs]
+void queue_norms(BW& w, const double* v, double* dst) {
     const int G = dot_split(w, w.nr), hs = w.m + 2;
     hipLaunchKernelGGL(k_b_dots, dim3(G, 1, w.nr), dim3(256), 0, w.s, v, 1, w.ld, w.n, 1, v, w.part, G);
     BEM_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_b_norm, dim3((unsigned)w.nr), dim3(64), 0, w.s, w.part, G, w.h, hs);
+    auto kernel = w.c->opt.precision == BEM_MIXED ? k_b_norm<true> : k_b_norm<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)w.nr), dim3(64), 0, w.s, w.part, G, dst, hs);
     BEM_CHECK_LAUNCH();
+}
+
+// norms of the nr vectors v[r * ld] into w.h[r * hs] and to the host
+void norms(BW& w, const double* v, std::vector<double>& out) {
+    const int hs = w.m + 2;
+    queue_norms(w, v, w.h);
     BEM_HIP(hipMemcpyAsync(w.host, w.h, sizeof(double) * w.nr * hs, hipMemcpyDeviceToHost, w.s));
     BEM_HIP(hipStreamSynchronize(w.s));
     out.resize(w.nr);
@@ -314,6 +340,7 @@ int bgmres(BW& w, const double* B, double* X, double tol, int max_iter, bool exa
            std::vector<double>& bnorm) {
     bem_ctx* c = w.c;
     const int nr = w.nr, m = w.m, m1 = w.m1, hs = m + 2;
+    const bool mixed = c->opt.precision == BEM_MIXED;   // see the head of the file
     const double* d = c->diag.as<double>();
     std::vector<double> H((size_t)nr * (m + 1) * m), cs((size_t)nr * m), sn((size_t)nr * m), g((size_t)nr * (m + 1)),
         yv((size_t)nr * m1);
@@ -356,18 +383,21 @@ int bgmres(BW& w, const double* B, double* X, double tol, int max_iter, bool exa
         for (int j = 0; j < m; ++j) {
             KTimer tj(c, "bgmres_iter");
             // W = A (V[:, j] / d) is on its way
-            const int G = dot_split(w, (int)ceil_div(j + 1, DOT_K) * nr), GB = (int)ceil_div(w.n, 256);
+            const int G = dot_split(w, (mixed ? j + 1 : (int)ceil_div(j + 1, DOT_K)) * nr);
+            const int GB = mixed ? 0 : (int)ceil_div(w.n, 256);
             double* norm = w.part + (size_t)nr * m1 * w.G;
             for (int pass = 0; pass < 2; ++pass) {
                 hipLaunchKernelGGL(k_b_dots, dim3(G, ceil_div(j + 1, DOT_K), nr), dim3(256), 0, w.s, w.V, m1, w.ld,
                                    w.n, j + 1, w.W, w.part, G);
                 BEM_CHECK_LAUNCH();
-                hipLaunchKernelGGL(k_b_orth, w.gv(), dim3(256), 0, w.s, w.V, m1, w.ld, w.n, j + 1, w.part, G, w.Hcol,
-                                   hs, pass, w.W, pass == 1 ? norm : (double*)nullptr);
+                hipLaunchKernelGGL((mixed ? k_b_orth<true> : k_b_orth<false>), w.gv(), dim3(256), 0, w.s, w.V, m1, w.ld,
+                                   w.n, j + 1, w.part, G, w.Hcol, hs, pass, w.W,
+                                   pass == 1 && !mixed ? norm : (double*)nullptr);
                 BEM_CHECK_LAUNCH();
             }
+            if (mixed) queue_norms(w, w.W, w.Hcol + j + 1);
             const uint64_t id = ++c->gm_seq;
-            hipLaunchKernelGGL(k_b_next, w.gv(), dim3(256), 0, w.s, w.W, w.ld, norm, GB, w.Hcol, hs, w.n, d,
+            hipLaunchKernelGGL(k_b_next, w.gv(), dim3(256), 0, w.s, w.W, w.ld, norm, GB, w.Hcol + j + 1, hs, w.n, d,
                                w.V + (int64_t)(j + 1) * w.ld, (int64_t)m1 * w.ld, in32(w, exact_apply),
                                in64(w, exact_apply), in_rows(w, exact_apply), w.Hcol, j, w.col, w.flag, id);
             BEM_CHECK_LAUNCH();
