@@ -20,6 +20,7 @@
 // all three hats of the near triangles into its row, so the first pass keeps
 // few registers and many waves in flight.
 #include <cmath>
+#include <type_traits>
 
 #include "bem_device.h"
 #include "median_device.h"
@@ -140,6 +141,22 @@ __device__ __forceinline__ double hat_value(const double* __restrict__ T, int c,
     return (lam * I0 + (g0 * J0 + g1 * J1 + g2 * J2) / two_area) * INV4PI;
 }
 
+// The rule's barycentric coordinate of local vertex c at node q (node order of
+// the panel records: centroid, then the orbits (a, a, 1 - 2a) for a = a1, a2
+// with the odd coordinate last, middle, first).
+struct NodeBary {
+    double b[7];
+    __device__ NodeBary(int c) {
+        const double s15 = sqrt(15.0);
+        const double a1 = (6.0 - s15) / 21.0, a2 = (6.0 + s15) / 21.0;
+        b[0] = 1.0 / 3.0;
+#pragma unroll
+        for (int q = 1; q <= 3; ++q) b[q] = (c == 3 - q) ? 1.0 - 2.0 * a1 : a1;
+#pragma unroll
+        for (int q = 4; q <= 6; ++q) b[q] = (c == 6 - q) ? 1.0 - 2.0 * a2 : a2;
+    }
+};
+
 // Regular pairs of the vertex rows (KP false) or of the centroid rows below (KP true: x the centroid of
 // triangle trow[i], the kernel n . (x - y)/|x - y|^3 in place of 1/|x - y|).
 // One wave: rows i0 + lane, the 16 columns of column group cg (neighbouring vertices).  The wave walks the
@@ -159,7 +176,9 @@ __device__ __forceinline__ double hat_value(const double* __restrict__ T, int c,
 // triangle, so corners are looked for only there.  Bound by FP64 issue; the next triangle's record is
 // requested before a triangle's arithmetic.  9,036 vertices, 18,064 triangles: 1.17 ms; node by node, with
 // groups of consecutive vertices (2.03 visits) and no request ahead, 1.77.
-template <class T, bool KP>   // T: stored type, double (FP64) or float (MIXED)
+// NODES (MIXED, whose products take FP32 inputs and carry an ulp of the operator into the solutions of
+// several load cases: gmres_batched.hip): node by node over the records pan64, every sum in the nodes' order.
+template <class T, bool KP, bool NODES>   // T: stored type, double (FP64) or float (MIXED)
 __global__ __launch_bounds__(256) void k_nodal_regular(int64_t nr, int64_t nv, int64_t ld, int64_t n_rt,
                                                        const double* __restrict__ vert,
                                                        const int32_t* __restrict__ trow,
@@ -169,6 +188,7 @@ __global__ __launch_bounds__(256) void k_nodal_regular(int64_t nr, int64_t nv, i
                                                        const int32_t* __restrict__ grp_tri,
                                                        const uint32_t* __restrict__ grp_loc,
                                                        const double* __restrict__ rec,
+                                                       const double* __restrict__ pan64,
                                                        const double* __restrict__ tri64, T* __restrict__ A) {
     constexpr int PF = MD_REACH + 1;             // the part of a record that every pair reads
     __shared__ double tile[4][NODAL_COLS][65];   // padded: the row-segment reads stride 65
@@ -241,7 +261,35 @@ __global__ __launch_bounds__(256) void k_nodal_regular(int64_t nr, int64_t nv, i
         if (l1 != 0xffu) tile[wv][l1][lane] += __fma_rn(hs, h1, base);
         if (l2 != 0xffu) tile[wv][l2][lane] += __fma_rn(hs, h2, base);
     };
-    if (e0 < e1) {
+    if constexpr (NODES) {
+        const NodeBary nb0(0), nb1(1), nb2(2);
+        for (int32_t e = e0; e < e1; ++e) {
+            const int64_t t = grp_tri[e];
+            const uint32_t loc = grp_loc[e];
+            const double* P = pan64 + (int64_t)FAR_REC * t;
+            const int32_t* tv = tri + 3 * t;
+            const bool mine = KP ? t == own : (tv[0] == i || tv[1] == i || tv[2] == i);
+            if (mine || !is_regular(x0 - P[FR_CC], x1 - P[FR_CC + 1], x2 - P[FR_CC + 2], P[FR_RR])) continue;
+            double f[7], w[7];
+#pragma unroll
+            for (int q = 0; q < 7; ++q) {
+                const double d0 = x0 - P[FR_X + q], d1 = x1 - P[FR_Y + q], d2 = x2 - P[FR_Z + q];
+                const double ir = rsqrt_pos(d0 * d0 + d1 * d1 + d2 * d2);
+                w[q] = P[FR_W + q];
+                f[q] = KP ? w[q] * (d0 * n0 + d1 * n1 + d2 * n2) * (ir * ir * ir) : ir;
+            }
+            auto hat = [&](uint32_t l, const NodeBary& nb) {
+                if (l == 0xffu) return;
+                double s = 0.0;
+#pragma unroll
+                for (int q = 0; q < 7; ++q) s += KP ? f[q] * nb.b[q] : w[q] * nb.b[q] * f[q];
+                tile[wv][l][lane] += s;
+            };
+            hat(loc & 0xffu, nb0);
+            hat((loc >> 8) & 0xffu, nb1);
+            hat((loc >> 16) & 0xffu, nb2);
+        }
+    } else if (e0 < e1) {
         auto fetch = [&](int64_t t, double (&v)[PF]) {
             const double* r = rec + (int64_t)MED_REC * t;
 #pragma unroll
@@ -730,11 +778,12 @@ static void nodal_assemble_t(bem_ctx* c, T* A, double* Atail, int64_t tail_row0)
     hipStream_t s = c->stream;
     const int64_t n_rt = ceil_div(nv, 256), n_cg = ceil_div(ceil_div(nv, NODAL_COLS), 8) * 8;
     if (n_rt * n_cg > ((int64_t)1 << 31) - 1) throw Error(BEM_ERR_INVALID, "too many vertices for the LINEAR basis");
-    launch_median_records(c, nullptr, c->ev_rec);
-    hipLaunchKernelGGL((k_nodal_regular<T, false>), dim3((unsigned)(n_rt * n_cg)), dim3(256), 0, s, nv, nv, ld, n_rt,
+    constexpr bool NODES = std::is_same<T, float>::value;
+    if (!NODES) launch_median_records(c, nullptr, c->ev_rec);
+    hipLaunchKernelGGL((k_nodal_regular<T, false, NODES>), dim3((unsigned)(n_rt * n_cg)), dim3(256), 0, s, nv, nv, ld, n_rt,
                        c->vert.as<double>(), (const int32_t*)nullptr, c->tri.as<int32_t>(), c->grp_col.as<int32_t>(),
                        c->grp_ptr.as<int32_t>(), c->grp_tri.as<int32_t>(), c->grp_loc.as<uint32_t>(), c->ev_rec.as<double>(),
-                       c->tri64.as<double>(), A);
+                       c->pan64.as<double>(), c->tri64.as<double>(), A);
     BEM_CHECK_LAUNCH();
     const int64_t Np = (int64_t)(c->far64.bytes / (sizeof(double) * FAR_REC));
     const int64_t nch = ceil_div(c->N, 64);
@@ -761,10 +810,11 @@ static void nodal_assemble_t(bem_ctx* c, T* A, double* Atail, int64_t tail_row0)
         double* Kc = c->nod_Kc.as<double>();
         const int64_t n_rtc = ceil_div(nc, 256);
         if (n_rtc * n_cg > ((int64_t)1 << 31) - 1) throw Error(BEM_ERR_INVALID, "too many centroid rows");
-        hipLaunchKernelGGL((k_nodal_regular<double, true>), dim3((unsigned)(n_rtc * n_cg)), dim3(256), 0, s, nc, nv, ld,
+        hipLaunchKernelGGL((k_nodal_regular<double, true, NODES>), dim3((unsigned)(n_rtc * n_cg)), dim3(256), 0, s, nc, nv, ld,
                            n_rtc, (const double*)nullptr, c->nod_trow.as<int32_t>(), c->tri.as<int32_t>(),
                            c->grp_col.as<int32_t>(), c->grp_ptr.as<int32_t>(), c->grp_tri.as<int32_t>(),
-                           c->grp_loc.as<uint32_t>(), c->ev_rec.as<double>(), c->tri64.as<double>(), Kc);
+                           c->grp_loc.as<uint32_t>(), c->ev_rec.as<double>(), c->pan64.as<double>(),
+                           c->tri64.as<double>(), Kc);
         BEM_CHECK_LAUNCH();
         hipLaunchKernelGGL((k_nodal_near<double, true>), dim3((unsigned)(ceil_div(nc, 8) * 8)), dim3(64), 0, s, nc, ld,
                            c->N, Np, (const int32_t*)nullptr, (const double*)nullptr, c->nod_trow.as<int32_t>(),

@@ -12,7 +12,7 @@ import hashlib
 import numpy as np
 import pytest
 
-from workloads import coax_problem, electrode_line_starts, floating_shell_problem, sphere_problem
+from workloads import coax_conductors_problem, coax_problem, electrode_line_starts, floating_shell_problem, sphere_problem
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -21,6 +21,7 @@ MESHES = {
     "sphere3": lambda: sphere_problem(3, V0=50.0),                # 1,280 panels, no floating body
     "shell2": lambda: floating_shell_problem(2, V0=80.0),         # 960 panels, one floating body
     "coax": lambda: coax_problem(0.012),                          # 2,192 panels, floating ring and interface
+    "conductors": lambda: coax_conductors_problem(0.008),         # nodal basis: 1,912 vertices, net-charge row
 }
 
 
@@ -86,3 +87,18 @@ def test_lines(bem, mesh, nrhs):
     """The integrals of 30 lines followed with those solutions."""
     print(f"[gpu-mixed-cases] lines {mesh} rhs={nrhs}", flush=True)
     assert solve(bem, mesh, nrhs, lines=30) == LINES[mesh, nrhs]
+
+
+NODAL = {
+    ("conductors", 2): ("f30685ac7a1ea230", 44), ("conductors", 5): ("b189a552328b308a", 44),
+    ("conductors", 64): ("15a430ce238210b4", 44), ("shell2", 2): ("221fc9c8e20933b7", 19),
+    ("shell2", 5): ("0b25a22be3dd3ab2", 19), ("shell2", 64): ("27cf965e50a2354d", 19),
+}
+
+
+@pytest.mark.parametrize("mesh,nrhs", sorted(NODAL))
+def test_nodal_solutions(bem, mesh, nrhs):
+    """The nodal basis: vertex rows in FP32 from FP64 sums over the rule's nodes, and a constraint row with
+    (shell2) and without a K' term."""
+    print(f"[gpu-mixed-cases] nodal {mesh} rhs={nrhs}", flush=True)
+    assert solve(bem, mesh, nrhs, basis=bem.BASIS_LINEAR, constraint_form=int(mesh != "shell2")) == NODAL[mesh, nrhs]
