@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256, 2) void k_sp_near(int64_t P, int64_t K, int64_
                 }
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         const int nq = total - base < SP_Q ? total - base : SP_Q;
         for (int q = lane; q < nq; q += 64) {
             const int j = list[wv][q];
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256, 2) void k_sp_near(int64_t P, int64_t K, int64_
             acc[7] = fma(sg, 0.5 * (Jac[0][2] + Jac[2][0]), acc[7]);
             acc[8] = fma(sg, 0.5 * (Jac[1][2] + Jac[2][1]), acc[8]);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
     }
 #pragma unroll
     for (int c = 0; c < SP_NC; ++c) acc[c] = wave_sum(acc[c]);

@@ -141,6 +141,14 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// Hands what the lanes of a wave have written to LDS to the wave's other lanes: the barrier alone orders no
+// memory, so the compiler could move a lane's loads above another's stores.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Hand-off to the host through coherent host memory while the kernel runs on: every thread's host_put()s,
 // host_done() by all of them, a barrier, then one thread's host_flag().  The stores are system-scope ones,
 // so waiting for them orders them before the flag; a system-scope fence would also write back the

@@ -203,7 +203,7 @@ __global__ __launch_bounds__(256) void k_ev_near(int64_t P, int64_t K, int64_t K
                 }
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         const int nq = total - base < EV_Q ? total - base : EV_Q;
         for (int q = lane; q < nq; q += 64) {
             const int64_t j = list[wv][q];
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(256) void k_ev_near(int64_t P, int64_t K, int64_t K
             e1 = fma(s, F1, e1);
             e2 = fma(s, F2, e2);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
     }
     phi = wave_sum(phi);
     e0 = wave_sum(e0);
