@@ -389,7 +389,8 @@ bem_status bem_panel_points(bem_ctx* ctx, int64_t L, const int32_t* panel, const
  *  "trace_spin":  persistent launches: polls of one wait between their blocks before the launch
  *                 gives up (0..2^30; default 2^22, seconds; a safety bound, not reached in normal
  *                 runs).  The one-launch layout's call then fails with BEM_ERR_HIP; the cluster
- *                 layout's lines run again in the other layout
+ *                 layout's lines run again, to the end in launches whose blocks wait for nothing
+ *                 (trace_mode 1)
  *  "trace_blocks": cluster layout: blocks per cluster (8, 16, 32; 0, the default: the fewest
  *                 whose LDS holds the panels; raised to 32 where a smaller count does not)
  *  "trace_lpb":   one-launch layout: line slots per block (1, 2, 4, 8; 0, the default: by the

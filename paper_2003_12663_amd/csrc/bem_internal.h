@@ -320,9 +320,11 @@ void launch_trace_nodal_cases(bem_ctx* c, int32_t nrhs, const double* sol, int64
 void launch_trace_batched(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const int32_t* line_rhs,
                           const double* starts, const bem_trace_params* tp, int32_t* n_steps, int32_t* stop_code,
                           double* path, double* integral, uint8_t* exceeds, bool fused_tail);   // trace_batched.hip
-// clusters of blocks that keep their panels in LDS for the whole run (trace_cluster.hip); false:
-// nothing done (the device or the panel count does not allow it)
-bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const int32_t* line_rhs,
+// clusters of blocks that keep their panels in LDS for the whole run (trace_cluster.hip).  NOT_TAKEN: nothing
+// done (the device or the sizes do not allow it); GAVE_UP: a wait between blocks reached its bound
+// (other work holds the CUs they need), so the lines have to run in a layout without such waits
+enum class TraceCluster { DONE, NOT_TAKEN, GAVE_UP };
+TraceCluster launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const int32_t* line_rhs,
                           const double* starts, const bem_trace_params* tp, int32_t* n_steps, int32_t* stop_code,
                           double* path, double* integral, uint8_t* exceeds);
 // one launch per RK4 stage (trace_fused.hip); fused_trace_blocks: its panel blocks of 256 rnd

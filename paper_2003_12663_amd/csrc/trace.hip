@@ -370,9 +370,13 @@ void launch_trace(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const 
     // step kernel per stage while many lines are live, one launch per stage for the last few
     // (measured on the 19,732-panel coax: 47 against 64 us a stage at 256 lines, 21.4 against
     // 17.1 us at 16, 16.1 against 12.4 us at 3)
-    if (c->trace_mode == 0 && (c->opt.precision == BEM_FP64 || c->opt.basis == BEM_BASIS_LINEAR) &&
-        launch_trace_cluster(c, nrhs, sol, L, line_rhs, starts, tp, n_steps, stop_code, path, integral, exceeds))
-        return;
+    bool waits = true;   // whether launches whose blocks wait for each other may be taken
+    if (c->trace_mode == 0 && (c->opt.precision == BEM_FP64 || c->opt.basis == BEM_BASIS_LINEAR)) {
+        const TraceCluster r =
+            launch_trace_cluster(c, nrhs, sol, L, line_rhs, starts, tp, n_steps, stop_code, path, integral, exceeds);
+        if (r == TraceCluster::DONE) return;
+        waits = r != TraceCluster::GAVE_UP;
+    }
     const int mode = c->trace_mode != 0 ? c->trace_mode : 1;
     if (mode == 1 || mode == 3) {
         if (c->opt.basis == BEM_BASIS_LINEAR && nrhs > 1 && line_rhs)
@@ -382,7 +386,7 @@ void launch_trace(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const 
             launch_trace_fused(c, nrhs, sol, L, line_rhs, starts, tp, n_steps, stop_code, path, integral, exceeds);
         else
             launch_trace_batched(c, nrhs, sol, L, line_rhs, starts, tp, n_steps, stop_code, path, integral, exceeds,
-                                 trace_fused_tail(c));
+                                 waits && trace_fused_tail(c));
         return;
     }
     KTimer t(c, "trace");

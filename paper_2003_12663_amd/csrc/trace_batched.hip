@@ -1092,16 +1092,19 @@ void launch_trace_nodal_cases(bem_ctx* c, int32_t nrhs, const double* sol, int64
         hipLaunchKernelGGL(k_gather_starts, dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, c->stream, m, didx, starts,
                            tst);
         BEM_CHECK_LAUNCH();
-        if (c->trace_mode == 0 &&
-            launch_trace_cluster(c, 1, sol + (int64_t)r * c->n, m, nullptr, tst, tp, tns, tsc, path ? tpath : nullptr,
-                                 integral ? tI : nullptr, exceeds ? tex : nullptr)) {
+        const TraceCluster done =
+            c->trace_mode == 0
+                ? launch_trace_cluster(c, 1, sol + (int64_t)r * c->n, m, nullptr, tst, tp, tns, tsc,
+                                       path ? tpath : nullptr, integral ? tI : nullptr, exceeds ? tex : nullptr)
+                : TraceCluster::NOT_TAKEN;
+        if (done == TraceCluster::DONE) {
         } else if (trace_fused_layout(c))
             launch_trace_fused(c, 1, sol + (int64_t)r * c->n, m, nullptr, tst, tp, tns, tsc, path ? tpath : nullptr,
                                integral ? tI : nullptr, exceeds ? tex : nullptr);
         else
             launch_trace_batched(c, 1, sol + (int64_t)r * c->n, m, nullptr, tst, tp, tns, tsc,
                                  path ? tpath : nullptr, integral ? tI : nullptr, exceeds ? tex : nullptr,
-                                 trace_fused_tail(c));
+                                 done != TraceCluster::GAVE_UP && trace_fused_tail(c));
         hipLaunchKernelGGL(k_scatter_lines, dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, c->stream, m, didx, tns,
                            tsc, tI, tex, tpath, pstride, n_steps, stop_code, integral, exceeds, path);
         BEM_CHECK_LAUNCH();

@@ -800,9 +800,9 @@ const void* lc_kernel(int W, int B, bool res, int sw, bool nodal) {
 
 }  // namespace
 
-bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const int32_t* line_rhs,
-                          const double* starts, const bem_trace_params* tp, int32_t* n_steps, int32_t* stop_code,
-                          double* path, double* integral, uint8_t* exceeds) {
+TraceCluster launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const int32_t* line_rhs,
+                                  const double* starts, const bem_trace_params* tp, int32_t* n_steps,
+                                  int32_t* stop_code, double* path, double* integral, uint8_t* exceeds) {
     if (c->coop_launch < 0) {
         int v = 0;
         BEM_HIP(hipDeviceGetAttribute(&v, hipDeviceAttributeCooperativeLaunch, c->device));
@@ -810,12 +810,12 @@ bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L
     }
     int cus = 0;
     BEM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
-    if (c->coop_launch == 0 || cus < LC_XCD_CUS) return false;
+    if (c->coop_launch == 0 || cus < LC_XCD_CUS) return TraceCluster::NOT_TAKEN;
     const int64_t N = c->N;
     if (!line_rhs) nrhs = 1;   // every line takes the first load case
     // nodal basis (one load case; FP64 in either precision): three density values a panel
     const bool nodal = c->opt.basis == BEM_BASIS_LINEAR;
-    if (nodal && nrhs > 1) return false;
+    if (nodal && nrhs > 1) return TraceCluster::NOT_TAKEN;
     const int nd = nodal ? 3 : nrhs;
     // blocks per cluster: as few as hold the panels (and the load cases' densities) in LDS.  Fewer
     // blocks exchange faster and leave more clusters to share the lines (us a turn, 1,280 panels,
@@ -833,11 +833,11 @@ bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L
     while (B < 32 && (per_panel + per_dens) * (size_t)ceil_div(N, B) > room) B *= 2;
     const int NC = cus / LC_XCD_CUS * (LC_XCD_CUS / B);
     const int64_t P = ceil_div(N, B);
-    if (P > 65535) return false;   // a held pair carries its panel's index in 16 bits
+    if (P > 65535) return TraceCluster::NOT_TAKEN;   // a held pair carries its panel's index in 16 bits
     const bool res = per_panel * (size_t)P <= room;
     // nodal panels beyond LDS: their records and densities from memory each turn lose to the two-kernel
     // layout where the pairs take the time (54,882 panels, 256 lines of 200 steps: 69.7 against 62.2 ms)
-    if (nodal && !res && L > (int64_t)NC * 8) return false;
+    if (nodal && !res && L > (int64_t)NC * 8) return TraceCluster::NOT_TAKEN;
     const int sw = nd == 1 ? 0 : (res && (per_panel + per_dens) * (size_t)P <= room ? 1 : 2);
     const size_t dyn = res ? (per_panel + (sw == 1 ? per_dens : 0)) * (size_t)P : 0;
     // waves per block: 8 are the faster exchange and step (1 line, 19,732 panels: equal; 8 lines,
@@ -849,7 +849,7 @@ bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L
     if (dyn > 0) BEM_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn));
     int per_cu = 0;
     BEM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, 64 * W, dyn));
-    if (per_cu < 1) return false;
+    if (per_cu < 1) return TraceCluster::NOT_TAKEN;
 
     KTimer t(c, "trace");
     LCArgs A;
@@ -920,7 +920,7 @@ bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L
             c->event_pool.push_back(eb);
         }
         kclock_end(c);
-        return false;
+        return TraceCluster::NOT_TAKEN;
     }
     if (timed) {
         BEM_HIP(hipEventRecord(eb, c->stream));
@@ -932,13 +932,13 @@ bool launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L
     int32_t* host = c->host_stage.as<int32_t>() + 32;
     BEM_HIP(hipMemcpyAsync(host, A.err, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
     BEM_HIP(hipStreamSynchronize(c->stream));
-    // a wait reached its bound (another kernel held CUs that a cluster's blocks needed for seconds):
-    // the caller runs the lines again in a layout whose blocks wait for nothing
-    if (*host != 0) return false;
+    // a wait reached its bound (another kernel held CUs that a cluster's blocks needed for seconds): the
+    // caller runs the lines again, one pass after another, in launches whose blocks wait for nothing
+    if (*host != 0) return TraceCluster::GAVE_UP;
     hipLaunchKernelGGL(k_lc_count, dim3(1), dim3(64), 0, c->stream, A.counts,
                        reinterpret_cast<unsigned long long*>(c->counters.p) + 2);
     BEM_CHECK_LAUNCH();
-    return true;
+    return TraceCluster::DONE;
 }
 
 }  // namespace bem

@@ -122,6 +122,39 @@ def test_wait_bound_falls_back(bem):
     _check(bem, sphere_problem(2), 40, trace_spin=0)
 
 
+@pytest.mark.parametrize("nodal,nrhs", [(False, 1), (True, 1), (True, 2)])
+def test_recovery_waits_for_nothing(bem, nodal, nrhs):
+    """After a wait at its bound the lines end in launches without waits: with three lines of 40 steps the
+    default's tail would begin after 32 passes, and its persistent launch would fail at the same bound
+    of zero polls.  Once more in a call of the gradient's kind: the forward run of streamer_grad."""
+    p = sphere_problem(2, V0=50.0)
+    print(f"[gpu-cluster] recovery nodal={nodal} rhs={nrhs}", flush=True)
+    L, h, steps = 3, 1e-3, 40
+    starts, _, _ = electrode_line_starts(p, L, seed=9)
+    x = np.stack([_nodal_density(p, 9 + r) for r in range(nrhs)]) if nodal else _density(p, nrhs, 9)
+    owner = (np.arange(L) % nrhs).astype(np.int32)
+    o = oracle.Oracle(p, constraint_form=1)
+    follow = o.p1_trace if nodal else o.trace
+    ref = [follow(x[owner[l]], starts[l:l + 1], oracle.trace_params(h=h, max_steps=steps)) for l in range(L)]
+    ns_o, st_o, I_o = (np.concatenate([r[k] for r in ref]) for k in range(3))
+    kw = dict(basis=bem.BASIS_LINEAR, constraint_form=1) if nodal else {}
+    with bem.Context.from_problem(p, **kw) as c:
+        c.set_tuning("trace_spin", 0)
+        c.set_tuning("trace_few", 0)
+        tp = bem.trace_params(h=h, max_steps=steps)
+        sol = torch.tensor(x, device="cuda")
+        lr = torch.tensor(owner, device="cuda") if nrhs > 1 else None
+        I, ns, st, _ = c.streamer_integral(sol, starts, tp, line_rhs=lr)
+        assert c.counter("trace_far_launches") >= 4 * steps   # the passes of the recovery, to the last step
+        assert np.array_equal(ns.cpu().numpy(), ns_o) and np.array_equal(st.cpu().numpy(), st_o)
+        assert np.abs(I.cpu().numpy() - I_o).max() <= 1e-10 * np.abs(I_o).max()
+        if not nodal:
+            c.assemble()
+            before = c.counter("trace_far_launches")
+            c.streamer_grad(sol, starts, np.ones(L), tp)
+            assert c.counter("trace_far_launches") > before
+
+
 def test_line_groups_agree_with_single_lines(bem):
     """A line's result does not depend on how many others run beside it, beyond rounding."""
     p = sphere_problem(3)
