@@ -391,6 +391,8 @@ bem_status bem_panel_points(bem_ctx* ctx, int64_t L, const int32_t* panel, const
  *                 runs).  The one-launch layout's call then fails with BEM_ERR_HIP; the cluster
  *                 layout's lines run again, to the end in launches whose blocks wait for nothing
  *                 (trace_mode 1)
+ *  "trace_cluster": trace_mode 0 and the forward run of bem_streamer_grad: 1 (default) = the cluster
+ *                 layout where it can run; 0 = never, as on a device that refuses it
  *  "trace_blocks": cluster layout: blocks per cluster (8, 16, 32; 0, the default: the fewest
  *                 whose LDS holds the panels; raised to 32 where a smaller count does not)
  *  "trace_lpb":   one-launch layout: line slots per block (1, 2, 4, 8; 0, the default: by the

@@ -208,6 +208,7 @@ struct bem_ctx {
     int32_t tune_trace_tail = 16;     // trace_mode 0: live lines at or below which the one-launch layout takes over
     int32_t tune_trace_loop = 4;      // one-launch layout: line slots at or below which one persistent launch runs the rest
     int32_t tune_trace_spin = 1 << 22;   // persistent launch: polls of one wait between its blocks at most
+    int32_t tune_trace_cluster = 1;   // trace_mode 0: the cluster layout where it can run (1) or not (0)
     int32_t tune_trace_blocks = 0;    // cluster layout: blocks per cluster (8, 16, 32; 0: by the panel count)
     int32_t coop_launch = -1;         // the device takes cooperative launches (1) or not (0); -1: not asked yet
     int32_t grad_batch = 131072;      // points per batch of the gradient's pair passes (bounds scratch memory)

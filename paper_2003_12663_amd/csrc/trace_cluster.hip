@@ -803,6 +803,7 @@ const void* lc_kernel(int W, int B, bool res, int sw, bool nodal) {
 TraceCluster launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const int32_t* line_rhs,
                                   const double* starts, const bem_trace_params* tp, int32_t* n_steps,
                                   int32_t* stop_code, double* path, double* integral, uint8_t* exceeds) {
+    if (c->tune_trace_cluster == 0) return TraceCluster::NOT_TAKEN;
     if (c->coop_launch < 0) {
         int v = 0;
         BEM_HIP(hipDeviceGetAttribute(&v, hipDeviceAttributeCooperativeLaunch, c->device));
