@@ -376,3 +376,23 @@ def test_stage_fields_in_batches(bem, oracle_mod, batch):
     assert a["ns"].min() < a["ns"].max() or a["ns"].min() > 0
     for k in ("dvert", "dV", "dstart"):
         assert np.abs(a[k] - b[k]).max() <= 1e-11 * np.abs(a[k]).max(), k
+
+
+@pytest.mark.parametrize("make,kw", [
+    (lambda: floating_shell_problem(2, V0=80.0), dict(L=60, steps=40, h=5e-3, nrhs=2)),   # several lines a group
+    (lambda: sphere_problem(1, V0=50.0), dict(L=5, steps=700, h=1e-3)),                   # a line longer than a group
+])
+def test_stage_fields_in_groups(bem, oracle_mod, make, kw):
+    """A load case's fields are held for 8 grad_batch steps at a time, whole lines: several groups, the
+    last one ragged, and lines that are a group each, give the gradient of one group (sums in another
+    order: 1e-11 of the largest entry)."""
+    p = make()
+    a = _case(bem, oracle_mod, p, **kw)
+    b = _case(bem, oracle_mod, p, batch=64, **kw)
+    nrhs = kw.get("nrhs", 1)
+    if nrhs > 1:
+        assert min(a["ns"][r::nrhs].sum() for r in range(nrhs)) > 2 * 8 * 64
+    else:
+        assert a["ns"].min() > 8 * 64
+    for k in ("dvert", "dV", "dstart"):
+        assert np.abs(a[k] - b[k]).max() <= 1e-11 * np.abs(a[k]).max(), k
