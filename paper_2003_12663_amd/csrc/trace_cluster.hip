@@ -847,7 +847,9 @@ TraceCluster launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, i
     // room for their own arrays too
     const int W = !nodal && L > (int64_t)NC * 8 && dyn <= lds_room(12) ? 12 : 8;
     const void* f = lc_kernel(W, B, res, sw, nodal);
-    if (dyn > 0) BEM_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn));
+    // the attribute is the process's, not this call's: always the most that a CU has, so that no other
+    // thread's call finds less than it needs
+    if (dyn > 0) BEM_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_room(W)));
     int per_cu = 0;
     BEM_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, 64 * W, dyn));
     if (per_cu < 1) return TraceCluster::NOT_TAKEN;
