@@ -263,6 +263,34 @@ __device__ __noinline__ LCVec3 lc_nodal_E(const double* __restrict__ T, double x
     return E;
 }
 
+// Cluster and rank of a block.  Consecutive block ids go to the 8 XCDs in turn: cluster cl takes ids = cl
+// mod 8 (B of the ids on that XCD, where a cluster is a part of one).  Where the clusters do not deal
+// out evenly to 8 (a part of the GPU with fewer CUs), they take the ids in turn among themselves.
+struct LCPlace {
+    int cl, k;
+};
+__host__ __device__ constexpr LCPlace lc_place(int id, int NC, int B) {
+    const int xg = NC % 8 == 0 ? 8 : NC, xi = id % xg, xm = id / xg;
+    return LCPlace{xi + xg * (xm / B), xm % B};
+}
+// every (cluster, rank) by exactly one block, whatever the number of clusters
+constexpr bool lc_places_all(int NC, int B) {
+    bool seen[64 * 32] = {};
+    for (int id = 0; id < NC * B; ++id) {
+        const LCPlace p = lc_place(id, NC, B);
+        if (p.cl < 0 || p.cl >= NC || p.k < 0 || p.k >= B || seen[p.cl * B + p.k]) return false;
+        seen[p.cl * B + p.k] = true;
+    }
+    return true;
+}
+constexpr bool lc_places_all() {
+    for (int xcds = 1; xcds <= 16; ++xcds)
+        for (int B = 8; B <= LC_XCD_CUS; B *= 2)
+            if (!lc_places_all(xcds * (LC_XCD_CUS / B), B)) return false;
+    return true;
+}
+static_assert(lc_places_all(), "blocks of the cluster layout");
+
 // W: waves of a block; B: blocks of a cluster; RES: the block's panels in LDS (else read from the image each turn);
 // SW: densities from the records (0), of several load cases from LDS (1) or from memory (2);
 // NODAL: the density is the nodal one (its three values a panel where SW 1, 2 read load cases')
@@ -288,11 +316,8 @@ __global__ __launch_bounds__(64 * W) void k_lc_trace(LCArgs P) {
     kclock_start(P.kts);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // consecutive block ids go to the 8 XCDs in turn: cluster cl takes ids = cl mod 8 (B of the
-    // ids on that XCD, where a cluster is a part of one)
-    const int xg = P.NC < 8 ? P.NC : 8;
-    const int xi = blockIdx.x % xg, xm = blockIdx.x / xg;
-    const int cl = xi + xg * (xm / B), k = xm % B;
+    const LCPlace place = lc_place((int)blockIdx.x, P.NC, B);
+    const int cl = place.cl, k = place.k;
     const int64_t nlines = cl < P.L ? (P.L - cl + P.NC - 1) / P.NC : 0;   // lines cl, cl + NC, ...
     if (nlines == 0) {   // uniform over the cluster
         kclock_stop(P.kts);
