@@ -159,7 +159,9 @@ int64_t bem_n_unknowns(const bem_ctx* ctx);
 /* Assemble the collocation system of Eqs. Final1-Final4 (Sec. 4 quadrature:
  * regular pairs by the 7-point rule, near-singular and singular pairs by the
  * closed forms for flat triangles, done in a second pass over a compacted
- * near list).  Errors: OOM (checked before allocating), HIP. */
+ * near list).  Scratch memory of up to 1 GiB stays with the context for its next
+ * assembly, until bem_compress or bem_destroy; more is given back before the
+ * call returns.  Errors: OOM (checked before allocating), HIP. */
 bem_status bem_assemble(bem_ctx* ctx);
 
 /* Copy rows [row0, row0 + n_rows) of the assembled operator as FP64 into

@@ -564,11 +564,14 @@ bem_status bem_assemble(bem_ctx* c) {
                   : sizeof(double) * (size_t)n * ld;
     need += sizeof(uint64_t) * (size_t)nblk * N;                 // near masks
     need += (size_t)N * 160 * (mixed ? 16 : 8);                   // near list, ~90-160 pairs per row
+    need += sizeof(int64_t) * (size_t)(N + 1) + bem::near_csr_bytes(N, N);
+    if (!mixed) need += bem::median_records_bytes(c);
     if (c->opt.constraint_form == 0 || c->has_sheet) need += sizeof(double) * nflt * N;
     size_t free_b = 0, total_b = 0;
     BEM_HIP(hipMemGetInfo(&free_b, &total_b));
-    const size_t have = free_b + c->A64.bytes + c->A32.bytes + c->Kf.bytes + c->nearmask.bytes + c->near_col.bytes +
-                        c->near_row.bytes + c->near_val.bytes;
+    const size_t have = free_b + c->A64.bytes + c->A32.bytes + c->Kf.bytes + c->nearmask.bytes + c->csr_tmp.bytes +
+                        c->near_ptr.bytes + c->near_col.bytes + c->near_row.bytes + c->near_val.bytes +
+                        (mixed ? 0 : c->ev_rec.bytes);
     if (need > have) throw bem::Error(BEM_ERR_OOM, "assembly needs " + std::to_string(need >> 20) + " MiB, " +
                                                        std::to_string(have >> 20) + " MiB free");
     c->assembled = false;
@@ -589,11 +592,12 @@ bem_status bem_assemble(bem_ctx* c) {
     if (mixed) c->near_val.alloc(sizeof(double) * (c->near_nnz > 0 ? c->near_nnz : 1));
     bem::launch_near_assemble(c);
     bem::launch_finalize(c);
-    // the marks and the K' block stay for the next assembly where they are small: giving them back and
-    // taking them again is 0.2-0.3 ms of a 0.7 ms assembly at 7,712 panels.  Larger ones (a matrix
-    // of 64 GB and up, by the marks alone) leave the memory to the caller.
-    if (c->nearmask.bytes + c->Kf.bytes > ASSEMBLY_SCRATCH_KEPT) {
+    // the marks, the list's counts and the K' block stay for the next assembly where they are small: giving
+    // them back and taking them again is 0.2-0.3 ms of a 0.7 ms assembly at 7,712 panels.  Larger ones (a
+    // matrix of 64 GB and up, by the marks alone) leave the memory to the caller.
+    if (c->nearmask.bytes + c->csr_tmp.bytes + c->Kf.bytes > ASSEMBLY_SCRATCH_KEPT) {
         c->nearmask.release();
+        c->csr_tmp.release();
         c->Kf.release();
     }
     BEM_HIP(hipStreamSynchronize(c->stream));
@@ -846,6 +850,7 @@ bem_status bem_compress(bem_ctx* c, double eps, double eta_adm, int32_t leaf, be
     c->A32.release();
     c->Kf.release();
     c->nearmask.release();
+    c->csr_tmp.release();
     bem::HmStats st{};
     bem::hmatrix_build(c, eps, eta_adm, leaf, &st);
     c->near_nnz = 0;

@@ -533,15 +533,21 @@ void launch_far_assemble(bem_ctx* c) {
     if (kf) launch64(k_far64<2>, c->rows_flt, nflt, scale_one);
 }
 
+size_t near_csr_bytes(int64_t N, int64_t T) {
+    const int64_t nb = ceil_div(T, 256), C = ceil_div(ceil_div(N, 64), CSR_G);
+    return sizeof(int64_t) * (size_t)(T + 2 * nb + 1) + sizeof(int32_t) * (size_t)(C * T);
+}
+
 void launch_near_csr(bem_ctx* c, const uint64_t* mask, int64_t T, DBuf& ptr, DBuf& row, DBuf& col, int64_t* nnz,
                      const char* tname) {
     KTimer t(c, tname);
     const int64_t nblk = ceil_div(c->N, 64);   // waves that own at least one real panel
     const int64_t nb = ceil_div(T, 256), C = ceil_div(nblk, CSR_G);
-    // ptr [T + 1], then per row its offset in its block's rows, per block of rows its total and its
-    // offset, and per (chunk, row) the counts
-    ptr.alloc(sizeof(int64_t) * (size_t)(2 * T + 2 * nb + 2) + sizeof(int32_t) * (size_t)(C * T));
-    int64_t* loc = ptr.as<int64_t>() + (T + 1);
+    ptr.alloc(sizeof(int64_t) * (size_t)(T + 1));
+    // per row its offset in its block's rows, per block of rows its total and its offset, and per (chunk, row)
+    // the counts
+    c->csr_tmp.alloc(near_csr_bytes(c->N, T));
+    int64_t* loc = c->csr_tmp.as<int64_t>();
     int64_t* bsum = loc + T;
     int64_t* boff = bsum + nb;
     int32_t* cnt = reinterpret_cast<int32_t*>(boff + nb + 1);

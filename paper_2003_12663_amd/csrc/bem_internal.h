@@ -152,6 +152,7 @@ struct bem_ctx {
     bem::DBuf A64, A32, Kf;                 // dense operator (FP64 or FP32) and the K' block of floating rows
     bem::DBuf cons_part;                    // slab sums of a floating body's constraint row
     bem::DBuf nearmask, near_ptr, near_row, near_col, near_val;
+    bem::DBuf csr_tmp;                      // counts of a near list while it is built (launch_near_csr)
     bem::DBuf diag;
     int64_t near_nnz = 0;
     bool assembled = false;
@@ -273,14 +274,16 @@ void launch_quad_pair_integrals(bem_ctx* c, int64_t P, const double* pts, const 
                                 double* F);
 // the Sec. 4 rule for the assembly's near list into sf[4 k .. 4 k + 3] (duffy.hip)
 void launch_near_duffy(bem_ctx* c, int64_t nnz, const int32_t* row, const int32_t* col, double* sf);
-// records of the 7-point rule about the centroid with the densities sol (or none), in B groups (geometry.hip)
 constexpr int NODAL_COLS = 16;   // columns of a group of the nodal basis's regular pass
-void launch_check_points(bem_ctx* c, int64_t P, const double* pts, const int32_t* on_panel, int32_t* bad);
-void gmres_host(bem_ctx* c, size_t words);
+void launch_check_points(bem_ctx* c, int64_t P, const double* pts, const int32_t* on_panel, int32_t* bad);   // eval.hip
+void gmres_host(bem_ctx* c, size_t words);                                                           // gmres.hip
+// records of the 7-point rule about the centroid with the densities sol (or none), in B groups (geometry.hip)
 void launch_median_records(bem_ctx* c, const double* sol, DBuf& out, int B = 1, int64_t P = 0);
+size_t median_records_bytes(const bem_ctx* c);   // of one group
 void launch_panel_points(bem_ctx* c, int64_t L, const int32_t* panel, const double* bary, double offset,
                          double* out);                                // geometry.hip
 void launch_far_assemble(bem_ctx* c);                              // assemble.hip
+size_t near_csr_bytes(int64_t N, int64_t T);   // of csr_tmp for T rows (assemble.hip)
 void launch_near_csr(bem_ctx* c, const uint64_t* mask, int64_t n_targets, DBuf& ptr, DBuf& row, DBuf& col,
                      int64_t* nnz, const char* tname);             // assemble.hip
 void launch_near_assemble(bem_ctx* c);                             // assemble.hip

@@ -160,6 +160,8 @@ __global__ __launch_bounds__(256) void k_median_records(int64_t N, int64_t Np, i
 
 }  // namespace
 
+size_t median_records_bytes(const bem_ctx* c) { return sizeof(double) * MED_REC * (size_t)c->N; }
+
 void launch_median_records(bem_ctx* c, const double* sol, DBuf& out, int B, int64_t P) {
     const int64_t N = c->N, Np = (int64_t)(c->far64.bytes / (sizeof(double) * FAR_REC));
     if (P == 0) P = ceil_div(N, B);
