@@ -3,7 +3,10 @@
 // m_0 + m_1 + m_2 = 0), so with t = x - c, T = |t|^2 and p_i = t . m_i the squared node distances are
 // T, T - 2 p_i + |m_i|^2 and T - 2 rho p_i + rho^2 |m_i|^2: two operations a node instead of six, and
 // sums over the nodes of w f(r) d (d = t - c_q m_i) take the nodes' f alone: t sum w f - sum_i m_i (sum
-// c_q w f).  On a regular pair |t| is at least 5 circumradii, so nothing cancels.
+// c_q w f).  On a regular pair a node is at least (eta - 1) R away (R the circumradius) and |m_i| below R,
+// so a squared distance comes from numbers at most (1 + 1 / (eta - 1))^2 times its own size: 1.44 at the
+// usual eta = 6, 9 at 1.5.  At eta = 1 the panel's shape bounds that; on the meshes of the tests the results
+// are then 1e-15 of the largest from the node-by-node form's.
 #pragma once
 
 #include "bem_device.h"

@@ -1,12 +1,13 @@
 """Far from the usual eta = 6 of the Sec. 4 classification, against the oracle with the same eta.
 
 At 40 nearly every pair takes its closed form, so that a point's list of near pairs fills a wave's LDS
-list several times over."""
+list several times over.  At 1 and 1.5 regular pairs come as close as a circumradius or two, where the
+rule about the centroid takes its node distances from larger numbers than they are."""
 
 import numpy as np
 import pytest
 
-from workloads import electrode_line_starts, sphere_problem
+from workloads import coax_problem, electrode_line_starts, floating_shell_problem, sphere_problem
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -20,7 +21,36 @@ def bem():
     return bem
 
 
-@pytest.mark.parametrize("eta", [40.0])
+@pytest.mark.parametrize("make", [lambda: floating_shell_problem(2), lambda: coax_problem(0.018)])
+@pytest.mark.parametrize("eta", [1.0, 1.5])
+def test_rows_and_field(bem, oracle_mod, make, eta):
+    """Every row to 1e-12 of its largest entry; potential and field at and off the panels to 1e-10."""
+    p = make()
+    print(f"[gpu-eta] rows N={p.n_tri} eta={eta}", flush=True)
+    o = oracle_mod.Oracle(p, eta=eta)
+    cen = p.vert[p.tri].mean(axis=1)
+    x = np.concatenate([1.0 + 0.3 * np.sin(cen @ [1.0, 2.0, 3.0]), np.zeros(p.n_float)])
+    with bem.Context.from_problem(p, eta=eta) as c:
+        c.assemble()
+        A, G = o.assemble(), c.copy_rows(0, c.n).cpu().numpy()
+        assert (np.abs(G - A) <= 1e-12 * np.abs(A).max(axis=1, keepdims=True)).all()
+        for pts, on in ((cen, np.arange(p.n_tri, dtype=np.int32)), (cen * 1.003, None), (cen * 1.1, None)):
+            phi, E = c.eval_field(torch.tensor(x, device="cuda"), pts, on_panel=on)
+            for got, want in zip((phi[0], E[0]), o.eval(x, pts, on_panel=on)):
+                assert np.abs(got.cpu().numpy() - want).max() <= 1e-10 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("eta", [1.0, 1.5])
+def test_nodal_rows(bem, oracle_mod, eta):
+    p = floating_shell_problem(2)
+    print(f"[gpu-eta] nodal rows N={p.n_tri} eta={eta}", flush=True)
+    with bem.Context.from_problem(p, eta=eta, basis=bem.BASIS_LINEAR, constraint_form=1) as c:
+        c.assemble()
+        A, G = oracle_mod.Oracle(p, eta=eta, constraint_form=1).p1_assemble(), c.copy_rows(0, c.n).cpu().numpy()
+    assert (np.abs(G - A) <= 1e-12 * np.abs(A).max(axis=1, keepdims=True)).all()
+
+
+@pytest.mark.parametrize("eta", [1.5, 40.0])
 def test_gradient(bem, oracle_mod, eta):
     """dJ along a direction of the vertices and potentials, 1e-8 of the norms' product (the bar of the
     gradient tests), from the oracle's dual numbers."""
