@@ -346,8 +346,8 @@ bem_status bem_panel_points(bem_ctx* ctx, int64_t L, const int32_t* panel, const
  *                that keep their panels in LDS (from about 27,000 panels on, read them each
  *                stage) and run all their
  *                lines' stages in one cooperative launch, exchanging partial fields through device
- *                memory; otherwise, or where that launch is refused or one of its waits reaches
- *                "trace_spin" polls, 1 while more than "trace_tail" lines are live, then 3 (1
+ *                memory; otherwise, or where that launch is refused, would be slower (many lines
+ *                with many near panels each) or one of its waits reaches "trace_spin" polls, 1 while more than "trace_tail" lines are live, then 3 (1
  *                throughout above 131072 panels).  Layout 3 (and the tail of 0) runs all its remaining stages in one
  *                persistent launch once at most "trace_loop" line slots remain and their grid
  *                fits the GPU at once (cooperative launch): blocks of a line group then exchange
@@ -395,8 +395,9 @@ bem_status bem_panel_points(bem_ctx* ctx, int64_t L, const int32_t* panel, const
  *                 (trace_mode 1)
  *  "trace_cluster": trace_mode 0 and the forward run of bem_streamer_grad: 1 (default) = the cluster
  *                 layout where it can run; 0 = never, as on a device that refuses it
- *  "trace_blocks": cluster layout: blocks per cluster (8, 16, 32; 0, the default: the fewest
- *                 whose LDS holds the panels; raised to 32 where a smaller count does not)
+ *  "trace_blocks": cluster layout: blocks per cluster (8, 16, 32: this layout also where it is
+ *                 slower, raised to 32 where a smaller count does not hold the panels in LDS;
+ *                 0, the default: the fewest whose LDS holds them)
  *  "trace_lpb":   one-launch layout: line slots per block (1, 2, 4, 8; 0, the default: by the
  *                 live count)
  *  "trace_rnd":   one-launch layout: 256-panel rounds per block (1, 2, 4; 0, the default: by

@@ -41,6 +41,7 @@
 // ms for 1024 lines).
 #include <algorithm>
 #include <climits>
+#include <cmath>
 
 #include "bem_device.h"
 #include "median_device.h"
@@ -807,6 +808,25 @@ __global__ __launch_bounds__(256) void k_lc_nodal(int64_t N, int64_t P, int B, c
     o[2 * B * P] = w * (MED_SC * (u1 - mean));
 }
 
+// cnt[block]: pairs of the block's panels with the S sampled starts that are not regular
+__global__ __launch_bounds__(256) void k_lc_near(const double* __restrict__ far64, int64_t Np, int64_t N, int64_t L,
+                                                 int S, const double* __restrict__ starts, int32_t* cnt) {
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;   // < Np
+    const double c0 = far64[(int64_t)FR_CC * Np + j], c1 = far64[(int64_t)(FR_CC + 1) * Np + j],
+                 c2 = far64[(int64_t)(FR_CC + 2) * Np + j], rr = far64[(int64_t)FR_RR * Np + j];
+    int n = 0;
+    for (int s = 0; s < S; ++s) {
+        const double* x = starts + 3 * ((int64_t)s * L / S);
+        n += __popcll(__ballot(j < N && !is_regular(x[0] - c0, x[1] - c1, x[2] - c2, rr)));
+    }
+    __shared__ int red[4];
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(cnt + blockIdx.x, red[0] + red[1] + red[2] + red[3], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // 8 and 16 blocks a cluster only with everything in LDS (launch_trace_cluster)
 template <int W, bool ND>
 const void* lc_kernel_of(int B, bool res, int sw) {
@@ -821,6 +841,37 @@ const void* lc_kernel_of(int B, bool res, int sw) {
 const void* lc_kernel(int W, int B, bool res, int sw, bool nodal) {
     if (nodal) return lc_kernel_of<8, true>(B, res, sw);
     return W == 8 ? lc_kernel_of<8, false>(B, res, sw) : lc_kernel_of<12, false>(B, res, sw);
+}
+
+// Whether L lines take less time in the two-kernel layout.  There a line and stage cost more by themselves
+// (partial fields and marks through memory, two launches for all lines); here the near pairs, a quad
+// of lanes each on the few waves of a block, and where 8 blocks hold the panels the regular pairs do.  In ns
+// a line and stage, with v near pairs, measured from 80 to 18,580 panels, eta 6 to 60 (v 80 to 5,600) and 256 to
+// 65,536 lines: the two-kernel layout is ahead where 0.054 v + 0.0024 N (0.0003 N past 8 blocks) is above 11 +
+// 360,000 / L^1.5, with the nodal basis (near pairs one lane of a quad each) where 0.137 v + 0.0025 N
+// (0.001 N) is above 15 + 300,000 / L^1.5.  ms, this layout and the other: 2,192 panels, v 299, 4096 lines of
+// 20 steps 12.3 and 10.1, of 1024 lines (40 steps) 6.9 and 7.2; v 1175, 1024 lines 18.2 and 11.5; nodal, 3,816
+// panels, v 100, 4096 lines 14.3 and 11.2.  Lines keep about as many near panels as their starts have, so v is
+// taken at 64 of the starts.
+bool lc_slower(bem_ctx* c, int64_t L, const double* starts, int B, bool nodal) {
+    if (L < 256) return false;
+    const double per_near = nodal ? 0.137 : 0.054, l = (double)L;
+    const double per_panel = B == 8 ? (nodal ? 0.0025 : 0.0024) : (nodal ? 0.001 : 0.0003);
+    const double v0 = ((nodal ? 15.0 + 3.0e5 / (l * std::sqrt(l)) : 11.0 + 3.6e5 / (l * std::sqrt(l))) -
+                       per_panel * (double)c->N) / per_near;
+    if (v0 >= (double)c->N) return false;
+    if (v0 <= 0.0) return true;
+    constexpr int S = 64;
+    const int64_t Np = (int64_t)(c->far64.bytes / (sizeof(double) * FAR_REC)), nb = ceil_div(c->N, 256);
+    c->check_host.alloc(sizeof(int32_t) * (size_t)nb, hipHostMallocCoherent);
+    hipLaunchKernelGGL(k_lc_near, dim3((unsigned)nb), dim3(256), 0, c->stream, c->far64.as<double>(), Np, c->N, L, S,
+                       starts, c->check_host.as<int32_t>());
+    BEM_CHECK_LAUNCH();
+    BEM_HIP(hipStreamSynchronize(c->stream));
+    int64_t n = 0;
+    const volatile int32_t* cnt = c->check_host.as<int32_t>();
+    for (int64_t b = 0; b < nb; ++b) n += cnt[b];
+    return (double)n > v0 * S;
 }
 
 }  // namespace
@@ -864,6 +915,7 @@ TraceCluster launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, i
     // nodal panels beyond LDS: their records and densities from memory each turn lose to the two-kernel
     // layout where the pairs take the time (54,882 panels, 256 lines of 200 steps: 69.7 against 62.2 ms)
     if (nodal && !res && L > (int64_t)NC * 8) return TraceCluster::NOT_TAKEN;
+    if (c->tune_trace_blocks == 0 && lc_slower(c, L, starts, B, nodal)) return TraceCluster::NOT_TAKEN;
     const int sw = nd == 1 ? 0 : (res && (per_panel + per_dens) * (size_t)P <= room ? 1 : 2);
     const size_t dyn = res ? (per_panel + (sw == 1 ? per_dens : 0)) * (size_t)P : 0;
     // waves per block: 8 are the faster exchange and step (1 line, 19,732 panels: equal; 8 lines,

@@ -3,7 +3,8 @@
 Without it (trace_cluster 0, as on a device that refuses the cooperative launch) the lines run in the
 two-kernel layout and then its one-launch tail: the handover between the two, in FP64 and with the nodal
 basis, with counters that show that both parts ran.  With it (the default): the stops at a line's first
-stage, and lines of several load cases.  Step counts and stop codes exact, integrals 1e-10 relative (the
+stage, lines of several load cases, and many lines with many near panels, which go to the two-kernel
+layout.  Step counts and stop codes exact, integrals 1e-10 relative (the
 workload's FP64 bar), against the oracle."""
 
 import numpy as np
@@ -130,3 +131,25 @@ def test_load_cases_of_the_default(bem, coax):
         sel = np.nonzero(owner == r)[0]
         _compare([t[torch.tensor(sel, device="cuda")] for t in got[:3]],
                  o.trace(xs[r], starts[sel], oracle.trace_params(**kw)))
+
+
+@pytest.mark.parametrize("nodal,L", [(False, 4096), (True, 1100)])
+def test_many_lines_with_many_near_panels(bem, nodal, L):
+    """At eta = 40 every panel of this sphere is near.  That many lines take the two-kernel layout (the cluster
+    layout is slower), unless trace_blocks asks for the other; few of them, and as many at the usual eta,
+    take the cluster layout.  The same results either way."""
+    p = sphere_problem(2, V0=50.0)
+    print(f"[gpu-tail] many lines nodal={nodal} L={L}", flush=True)
+    x = np.concatenate([60.0 * (1.0 + 0.3 * np.sin((p.vert if nodal else p.vert[p.tri].mean(axis=1)) @ [1.0, 2.0, 0.5])),
+                        np.zeros(p.n_float)])
+    starts, _, _ = electrode_line_starts(p, L, seed=13)
+    kw = dict(h=1e-3, max_steps=2)
+    base = dict(basis=bem.BASIS_LINEAR, constraint_form=1) if nodal else {}
+    sol, tp = torch.tensor(x[None], device="cuda"), bem.trace_params(**kw)
+    for eta, few, blocks, cluster in ((40.0, L, 0, False), (40.0, L, 8, True), (40.0, 200, 0, True), (6.0, L, 0, True)):
+        o = oracle.Oracle(p, eta=eta, constraint_form=1)
+        with bem.Context.from_problem(p, eta=eta, **base) as c:
+            c.set_tuning("trace_blocks", blocks)
+            got = c.streamer_integral(sol, starts[:few], tp)
+            assert (c.counter("trace_far_launches") == 0) == cluster
+        _compare(got, (o.p1_trace if nodal else o.trace)(x, starts[:few], oracle.trace_params(**kw)))
