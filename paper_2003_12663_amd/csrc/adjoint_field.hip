@@ -178,20 +178,16 @@ __global__ __launch_bounds__(256, 2) void k_sp_near(int64_t P, int64_t K, int64_
         const int v = __shfl_up(incl, o, 64);
         if (lane >= o) incl += v;
     }
-    const int total = __shfl(incl, 63, 64);
-    const int off = incl - cnt;
+    const int total = __shfl(incl, 63, 64), last = incl;   // the lane's marks are [last - cnt, last) of the list
+    int pos = incl - cnt;
+    int64_t w = lane;
+    uint32_t word = w < KS ? mrow[w] : 0;
     for (int base = 0; base < total; base += SP_Q) {
-        if (off + cnt > base && off < base + SP_Q) {
-            int pos = off;
-            for (int64_t w = lane; w < KS && pos < base + SP_Q; w += 64) {
-                uint32_t m = mrow[w];
-                while (m) {
-                    const int b = __builtin_ctz(m);
-                    m &= m - 1;
-                    if (pos >= base && pos < base + SP_Q) list[wv][pos - base] = (int32_t)(w * SP_C + b);
-                    ++pos;
-                }
-            }
+        const int end = last < base + SP_Q ? last : base + SP_Q;   // the lane goes on where its last round ended
+        for (; pos < end; ++pos) {
+            while (word == 0) word = mrow[w += 64];
+            list[wv][pos - base] = (int32_t)(w * SP_C + __builtin_ctz(word));
+            word &= word - 1;
         }
         wave_sync();
         const int nq = total - base < SP_Q ? total - base : SP_Q;

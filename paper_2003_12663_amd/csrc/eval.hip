@@ -189,19 +189,16 @@ __global__ __launch_bounds__(256) void k_ev_near(int64_t P, int64_t K, int64_t K
         const int v = __shfl_up(incl, o, 64);
         if (lane >= o) incl += v;
     }
-    const int total = __shfl(incl, 63, 64), off = incl - cnt;
+    const int total = __shfl(incl, 63, 64), last = incl;   // the lane's marks are [last - cnt, last) of the list
+    int pos = incl - cnt;
+    int64_t w = lane;
+    uint32_t word = w < KS ? mrow[w] : 0;
     for (int base = 0; base < total; base += EV_Q) {
-        if (off + cnt > base && off < base + EV_Q) {
-            int pos = off;
-            for (int64_t w = lane; w < KS && pos < base + EV_Q; w += 64) {
-                uint32_t m = mrow[w];
-                while (m) {
-                    const int b = __builtin_ctz(m);
-                    m &= m - 1;
-                    if (pos >= base && pos < base + EV_Q) list[wv][pos - base] = (int32_t)(w * EV_C + b);
-                    ++pos;
-                }
-            }
+        const int end = last < base + EV_Q ? last : base + EV_Q;   // the lane goes on where its last round ended
+        for (; pos < end; ++pos) {
+            while (word == 0) word = mrow[w += 64];
+            list[wv][pos - base] = (int32_t)(w * EV_C + __builtin_ctz(word));
+            word &= word - 1;
         }
         wave_sync();
         const int nq = total - base < EV_Q ? total - base : EV_Q;
