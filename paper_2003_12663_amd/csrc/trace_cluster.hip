@@ -846,17 +846,18 @@ const void* lc_kernel(int W, int B, bool res, int sw, bool nodal) {
 // Whether L lines take less time in the two-kernel layout.  There a line and stage cost more by themselves
 // (partial fields and marks through memory, two launches for all lines); here the near pairs, a quad
 // of lanes each on the few waves of a block, and where 8 blocks hold the panels the regular pairs do.  In ns
-// a line and stage, with v near pairs, measured from 80 to 18,580 panels, eta 6 to 60 (v 80 to 5,600) and 256 to
-// 65,536 lines: the two-kernel layout is ahead where 0.054 v + 0.0024 N (0.0003 N past 8 blocks) is above 11 +
+// a line and stage, with v near pairs, measured from 80 to 65,216 panels, eta 6 to 60 (v 80 to 5,600) and 256 to
+// 65,536 lines: the two-kernel layout is ahead where 0.054 v + 0.0024 N (past 8 blocks 0.0003 N, where the
+// records come from memory 0.0005 N) is above 11 +
 // 360,000 / L^1.5, with the nodal basis (near pairs one lane of a quad each) where 0.137 v + 0.0025 N
 // (0.001 N) is above 15 + 300,000 / L^1.5.  ms, this layout and the other: 2,192 panels, v 299, 4096 lines of
 // 20 steps 12.3 and 10.1, of 1024 lines (40 steps) 6.9 and 7.2; v 1175, 1024 lines 18.2 and 11.5; nodal, 3,816
 // panels, v 100, 4096 lines 14.3 and 11.2.  Lines keep about as many near panels as their starts have, so v is
 // taken at 64 of the starts.
-bool lc_slower(bem_ctx* c, int64_t L, const double* starts, int B, bool nodal) {
+bool lc_slower(bem_ctx* c, int64_t L, const double* starts, int B, bool res, bool nodal) {
     if (L < 256) return false;
     const double per_near = nodal ? 0.137 : 0.054, l = (double)L;
-    const double per_panel = B == 8 ? (nodal ? 0.0025 : 0.0024) : (nodal ? 0.001 : 0.0003);
+    const double per_panel = B == 8 ? (nodal ? 0.0025 : 0.0024) : nodal ? 0.001 : res ? 0.0003 : 0.0005;
     const double v0 = ((nodal ? 15.0 + 3.0e5 / (l * std::sqrt(l)) : 11.0 + 3.6e5 / (l * std::sqrt(l))) -
                        per_panel * (double)c->N) / per_near;
     if (v0 >= (double)c->N) return false;
@@ -915,7 +916,7 @@ TraceCluster launch_trace_cluster(bem_ctx* c, int32_t nrhs, const double* sol, i
     // nodal panels beyond LDS: their records and densities from memory each turn lose to the two-kernel
     // layout where the pairs take the time (54,882 panels, 256 lines of 200 steps: 69.7 against 62.2 ms)
     if (nodal && !res && L > (int64_t)NC * 8) return TraceCluster::NOT_TAKEN;
-    if (c->tune_trace_blocks == 0 && lc_slower(c, L, starts, B, nodal)) return TraceCluster::NOT_TAKEN;
+    if (c->tune_trace_blocks == 0 && lc_slower(c, L, starts, B, res, nodal)) return TraceCluster::NOT_TAKEN;
     const int sw = nd == 1 ? 0 : (res && (per_panel + per_dens) * (size_t)P <= room ? 1 : 2);
     const size_t dyn = res ? (per_panel + (sw == 1 ? per_dens : 0)) * (size_t)P : 0;
     // waves per block: 8 are the faster exchange and step (1 line, 19,732 panels: equal; 8 lines,
