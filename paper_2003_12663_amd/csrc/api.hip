@@ -346,11 +346,11 @@ bem_status bem_create(int64_t n_vert, const double* vert, int64_t n_tri, const i
         // column of every corner
         constexpr int64_t G = bem::NODAL_COLS;
         const int64_t ng = (n_vert + G - 1) / G;
-        grp_col = row_order;
-        std::vector<int32_t> at(n_vert);   // place of each vertex in grp_col
-        for (int64_t g = 0; g < ng; ++g)
-            std::sort(grp_col.begin() + g * G, grp_col.begin() + std::min(n_vert, (g + 1) * G));
-        for (int64_t i = 0; i < n_vert; ++i) at[grp_col[i]] = (int32_t)i;
+        grp_col.resize(n_vert);
+        std::vector<int32_t> at(n_vert), next(ng);   // place of each vertex in grp_col (first in row_order)
+        for (int64_t i = 0; i < n_vert; ++i) at[row_order[i]] = (int32_t)i;
+        for (int64_t g = 0; g < ng; ++g) next[g] = (int32_t)(g * G);
+        for (int64_t v = 0; v < n_vert; ++v) grp_col[at[v] = next[at[v] / G]++] = (int32_t)v;
         grp_ptr.assign(ng + 1, 0);
         for (int64_t j = 0; j < n_tri; ++j) {
             const int64_t g0 = at[tri[3 * j]] / G, g1 = at[tri[3 * j + 1]] / G, g2 = at[tri[3 * j + 2]] / G;
@@ -429,7 +429,7 @@ bem_status bem_create(int64_t n_vert, const double* vert, int64_t n_tri, const i
     for (int64_t i = 0; i < n_tri; ++i) {
         if (c->h_body_kind[tri_body[i]] == BEM_INTERFACE)
             c->h_rows_int.push_back((int32_t)i);
-        else
+        else if (c->h_body_fidx[tri_body[i]] < 0)
             c->h_rows_pot.push_back((int32_t)i);
     }
     for (int32_t f = 0; f < c->n_float; ++f)
@@ -438,6 +438,7 @@ bem_status bem_create(int64_t n_vert, const double* vert, int64_t n_tri, const i
                 slot[i] = (int32_t)c->h_rows_flt.size();
                 c->h_rows_flt.push_back((int32_t)i);
             }
+    c->h_rows_pot.insert(c->h_rows_pot.end(), c->h_rows_flt.begin(), c->h_rows_flt.end());   // floating bodies' last
     const int64_t Np = (c->N + 255) / 256 * 256;
     hipStream_t s = c->stream;
     c->host_stage.alloc(sizeof(double) * 4096);
@@ -476,10 +477,6 @@ bem_status bem_create(int64_t n_vert, const double* vert, int64_t n_tri, const i
     upload(c->rows_pot, c->h_rows_pot.data(), c->h_rows_pot.size(), s);
     upload(c->rows_int, c->h_rows_int.data(), c->h_rows_int.size(), s);
     upload(c->rows_flt, c->h_rows_flt.data(), c->h_rows_flt.size(), s);
-    std::vector<int32_t> rows_dir;   // potential rows that are not a floating body's
-    for (int32_t i : c->h_rows_pot)
-        if (slot[i] < 0) rows_dir.push_back(i);
-    upload(c->rows_dir, rows_dir.data(), rows_dir.size(), s);
     upload(c->row_slot, slot.data(), slot.size(), s);
     // interface-row scales (eps+ - eps-) followed by ones for the K' rows of floating bodies
     std::vector<double> scales;

@@ -528,7 +528,7 @@ void launch_far_assemble(bem_ctx* c) {
     // with a K' block the floating rows' two kinds share the pairs' distances (2,020 of 16,656 potential
     // rows of 19,732 panels are floating: 0.15 + 0.20 ms in launches of their own, 0.26 together)
     const int64_t np = kf ? npot - nflt : npot;
-    if (np > 0) launch64(k_far64<0>, kf ? c->rows_dir : c->rows_pot, np, nullptr);
+    if (np > 0) launch64(k_far64<0>, c->rows_pot, np, nullptr);   // the floating bodies' are its last
     if (nint > 0) launch64(k_far64<1>, c->rows_int, nint, scale_int);
     if (kf) launch64(k_far64<2>, c->rows_flt, nflt, scale_one);
 }

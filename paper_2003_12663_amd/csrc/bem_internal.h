@@ -131,7 +131,8 @@ struct bem_ctx {
     // nodal basis (opt.basis == BEM_BASIS_LINEAR): body of each vertex and the fan of each
     // vertex, fan[fan_ptr[k] .. fan_ptr[k+1]) = (triangle << 2) | local index, triangles ascending
     std::vector<int32_t> h_vert_body;
-    std::vector<int32_t> h_rows_pot, h_rows_int, h_rows_flt;   // row segments by kind (Sec. 4)
+    // row segments by kind (Sec. 4); the floating bodies' are also the last of the potential ones
+    std::vector<int32_t> h_rows_pot, h_rows_int, h_rows_flt;
 
     bem::DBuf vert, tri, tri_body, body_kind, body_epsp, body_epsm, body_fidx, flt_coef;
     bem::DBuf vert_body, fan_ptr, fan, nodal_mass, nodal_bounds, row_order;   // nodal basis only
@@ -148,7 +149,7 @@ struct bem_ctx {
     bem::DBuf tr_cases;                          // staging of the nodal basis's per-load-case line runs
     bem::DBuf far64, far32, tri64;
     bem::DBuf pan64, pan32;                 // far64 / far32 panel-major: [Np][FAR_REC]
-    bem::DBuf rows_pot, rows_dir, rows_int, rows_flt, row_slot;
+    bem::DBuf rows_pot, rows_int, rows_flt, row_slot;
     bem::DBuf A64, A32, Kf;                 // dense operator (FP64 or FP32) and the K' block of floating rows
     bem::DBuf cons_part;                    // slab sums of a floating body's constraint row
     bem::DBuf nearmask, near_ptr, near_row, near_col, near_val;
