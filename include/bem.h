@@ -435,8 +435,9 @@ bem_status bem_autotune(bem_ctx* ctx, const char* cache_path, int32_t* from_cach
  *            "grad",
  *            "grad_reverse", "grad_rows_EH", "grad_panel_far", "grad_panel_near", "gemvT".
  *  enable 1: also "trace_far", every chunked far pass of the two-kernel field-line layout, and
- *            "trace_pass", every launch of the one-launch and cluster layouts, timed by events
- *            carried in their own dispatches (hipExtLaunchKernelGGL), nothing added to the stream.
+ *            "trace_pass", every launch of the one-launch layout, timed by events carried in
+ *            their own dispatches (hipExtLaunchKernelGGL), nothing added to the stream, and the
+ *            cluster layout's launch, by events recorded around it.
  *  enable 2: only "trace_far" and "trace_pass", so that all other work runs as it does
  *            unprofiled, each launch timed by the kernel itself: the earliest block start to
  *            the latest wave end on the device's constant-rate wall clock (with two line

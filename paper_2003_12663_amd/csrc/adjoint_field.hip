@@ -23,7 +23,7 @@
 //
 //  k_sp_far     - (256 points x panel range) blocks, one point per lane, panel
 //                 records read at wave-uniform addresses: E and H of the regular
-//                 pairs by the 7-point rule about the centroid (trace_cluster.hip),
+//                 pairs by the 7-point rule about the centroid (median_device.h),
 //                 near pairs as bit masks.
 //  k_sp_near    - one wave per point: the ranges' partial sums, the near pairs by
 //                 the closed forms differentiated with dual numbers (one pair per
@@ -60,8 +60,8 @@ __device__ __forceinline__ double la_dalpha(const LAArgs& a, double e) {
 
 // E and H of the regular pairs of up to 256 points (one per lane, at pts[pstride p]) with the panels
 // [span y, span (y + 1)) of the records `rec` (densities in them): part[y][p][9], and the bit masks
-// of the other pairs, mask[p][word].  Bound by FP64 issue: about 190 instructions a pair (the
-// node-by-node form takes 245).
+// of the other pairs, mask[p][word].  Bound by FP64 issue: 15 FP64 instructions to test a pair and 175
+// for a regular one's sums (the node-by-node form takes 245 in all).
 __global__ __launch_bounds__(SP_T) void k_sp_far(const double* __restrict__ rec, int64_t N, int64_t P, int64_t span,
                                                  int64_t KS, const double* __restrict__ pts, int64_t pstride,
                                                  double* __restrict__ part, uint32_t* __restrict__ mask) {
@@ -91,13 +91,13 @@ __global__ __launch_bounds__(SP_T) void k_sp_far(const double* __restrict__ rec,
             const double pb = __fma_rn(t0, m10, __fma_rn(t1, m11, t2 * m12));
             const double pc2 = -(pa + pb);
             double g[7], u[7];   // r^-3 and r^-5 at c, c + m_i, c + rho m_i
-            med_r3r5(T, k, g[0], u[0]);
-            med_r3r5(__fma_rn(-2.0, pa, T + v[9]), k, g[1], u[1]);
-            med_r3r5(__fma_rn(-2.0, pb, T + v[10]), k, g[2], u[2]);
-            med_r3r5(__fma_rn(-2.0, pc2, T + v[11]), k, g[3], u[3]);
-            med_r3r5(__fma_rn(k.m2rho, pa, __fma_rn(k.rho2, v[9], T)), k, g[4], u[4]);
-            med_r3r5(__fma_rn(k.m2rho, pb, __fma_rn(k.rho2, v[10], T)), k, g[5], u[5]);
-            med_r3r5(__fma_rn(k.m2rho, pc2, __fma_rn(k.rho2, v[11], T)), k, g[6], u[6]);
+            med_r3r5(T, g[0], u[0]);
+            med_r3r5(__fma_rn(-2.0, pa, T + v[9]), g[1], u[1]);
+            med_r3r5(__fma_rn(-2.0, pb, T + v[10]), g[2], u[2]);
+            med_r3r5(__fma_rn(-2.0, pc2, T + v[11]), g[3], u[3]);
+            med_r3r5(__fma_rn(k.m2rho, pa, __fma_rn(k.rho2, v[9], T)), g[4], u[4]);
+            med_r3r5(__fma_rn(k.m2rho, pb, __fma_rn(k.rho2, v[10], T)), g[5], u[5]);
+            med_r3r5(__fma_rn(k.m2rho, pc2, __fma_rn(k.rho2, v[11], T)), g[6], u[6]);
             const double sg = v[MD_DENS];
             // E = G t - (h_0 - h_2) m_0 - (h_1 - h_2) m_1
             const double G = __fma_rn(k.kap0, g[0], __fma_rn(k.kap, (g[4] + g[5]) + g[6], (g[1] + g[2]) + g[3]));

@@ -136,8 +136,8 @@ struct bem_ctx {
 
     bem::DBuf vert, tri, tri_body, body_kind, body_epsp, body_epsm, body_fidx, flt_coef;
     bem::DBuf vert_body, fan_ptr, fan, nodal_mass, nodal_bounds, row_order;   // nodal basis only
-    // per group of 16 consecutive vertex columns: the triangles holding one of its vertices
-    // (ascending) and the local column of each corner (8 bits each, 0xff outside the group)
+    // groups of NODAL_COLS neighbouring vertex columns (grp_col, ascending in a group): the triangles holding
+    // one of a group's vertices (ascending) and the local column of each corner (8 bits each, 0xff outside)
     bem::DBuf grp_col, grp_ptr, grp_tri, grp_loc;
     bem::DBuf nod_pan64, nod_far64, nod_ones;   // nodal density folded into the panel records (field lines)
     // nodal rows that need n . E, taken at triangle centroids: the centroid rows (triangles of

@@ -71,7 +71,7 @@ constexpr int EV_Q = 128;   // near pairs per round of a wave in k_ev_near
 // Bound by FP64 issue; the next panel's record is requested before a panel's arithmetic.  E at 19,732
 // centroids: 1.71 ms and 0.14 ms of k_ev_near; node by node over LDS tiles it took 2.30 ms, and 0.35 ms
 // more for a mask pass of its own and the near list with its wait of the host.  1000 points against
-// 2,192 panels: 21 + 28 us, before 180.
+// 2,192 panels: 21 + 25 us, before 180.
 template <bool PHI>
 __global__ __launch_bounds__(256) void k_ev_far(const double* __restrict__ rec, int64_t N, int64_t P, int64_t span,
                                                 int64_t KS, const double* __restrict__ pts,

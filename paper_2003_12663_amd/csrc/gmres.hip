@@ -172,8 +172,10 @@ constexpr int64_t GM_ONE = 20480;     // basis entries up to which one block tak
 // Krylov vector and the product's input from it, its column to the host.  w stays in LDS; a wave
 // takes a dot product, a thread the updates of its entries.  One CU reads the basis four times, some
 // 8 us at GM_ONE entries, against four launches.  Solves of 80, 320 and 1,280 unknowns: 168 -> 140,
-// 208 -> 174, 399 -> 340 us; taken further it loses (1,214 unknowns, 39 iterations: 935 us without, 904 up
-// to 16,384 entries, 937 up to 32,768, 1,027 up to 65,536; 3,682 unknowns: 1,725 and 1,744 us).
+// 208 -> 174, 399 -> 340 us.  GM_ONE: the time of 26 solves (13 meshes of 80 to 2,562 unknowns in both bases,
+// tolerances 1e-6 and 1e-10, 2 to 42 iterations) over that without this kernel, geometric mean, is 0.842 with
+// 8,192 entries, 0.833 with 12,288, 0.835 with 16,384, 0.832 with 20,480, 0.835 with 24,576, 0.839 with
+// 32,768 and 0.851 with 49,152: level from 12,288 to 24,576.  At 3,682 unknowns it gains nothing.
 __global__ __launch_bounds__(1024) void k_arnoldi(const double* __restrict__ V, int64_t vstride, int n, int kc,
                                                   const double* __restrict__ w, const double* __restrict__ d,
                                                   double* __restrict__ out, double* __restrict__ z,

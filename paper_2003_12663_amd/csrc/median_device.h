@@ -52,7 +52,7 @@ __device__ __forceinline__ double med_r3(double r2, const MedConst& k) {
     return __fma_rn(y3 * e, __fma_rn(e, k.c1875, k.c15), y3);
 }
 // r^-3 and r^-5
-__device__ __forceinline__ void med_r3r5(double r2, const MedConst&, double& r3, double& r5) {
+__device__ __forceinline__ void med_r3r5(double r2, double& r3, double& r5) {
     const double ir = rsqrt_pos(r2);
     const double ir2 = ir * ir;
     r3 = ir * ir2;

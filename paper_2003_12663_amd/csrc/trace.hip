@@ -361,11 +361,12 @@ void launch_trace(bem_ctx* c, int32_t nrhs, const double* sol, int64_t L, const 
     if (L == 0) return;
     int cus = 0;
     BEM_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
-    // default where the far field is FP64 (FP64 contexts, and the nodal basis in either precision): clusters of blocks resident for the whole run (measured faster
-    // than the two-kernel layout with its tails from 1 to 4096 lines and 320 to 57,230 panels, ms a
-    // run: 19,732 panels 36 -> 20 with 1 line, 167 -> 107 with 256, 467 -> 440 with 4096 lines of 300
-    // steps; 1,280 panels, 16 lines 13.4 -> 4.6)
-    // otherwise: all lines advance together (measured faster than one workgroup per line for
+    // default where the far field is FP64 (FP64 contexts, and the nodal basis in either precision): clusters
+    // of blocks resident for the whole run, where that is the faster layout (lc_slower in
+    // trace_cluster.hip).  ms a run, the two-kernel layout with its tail and this one: 19,732 panels
+    // 36 and 20 with 1 line, 167 and 107 with 256, 467 and 440 with 4096 lines of 300 steps; 1,280
+    // panels, 16 lines 13.4 and 4.6.
+    // default in MIXED, and where the cluster layout does not run: all lines advance together (measured faster than one workgroup per line for
     // 4 to 4096 lines; the per-line layout is bound by per-CU load bandwidth), a far pass and a
     // step kernel per stage while many lines are live, one launch per stage for the last few
     // (measured on the 19,732-panel coax: 47 against 64 us a stage at 256 lines, 21.4 against

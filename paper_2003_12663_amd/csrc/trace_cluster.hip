@@ -1,5 +1,6 @@
 // Field lines and the streamer integral by clusters of blocks that stay on the GPU for the whole
-// run (Sec. 1, Eq. Breakdowncrit; RK4 on dx/ds = dir E/|E|): the default layout in FP64.
+// run (Sec. 1, Eq. Breakdowncrit; RK4 on dx/ds = dir E/|E|): the default layout in FP64, but for many
+// lines with many near panels each (lc_slower).
 //
 // A cluster is B blocks on the CUs of one XCD.  Block k of a cluster holds the panels j = k, k + B,
 // ... in its LDS for the whole call; line l belongs to cluster l mod NC and sits in one of the
@@ -402,7 +403,7 @@ __global__ __launch_bounds__(64 * W) void k_lc_trace(LCArgs P) {
         double a0 = 0.0, a1 = 0.0, a2 = 0.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
         // output word (li, c) of this thread in the sums below, over Q lanes
         const int Q = 1 << lq, oq = tid & (Q - 1), ow = tid >> lq, oc = ow & 3, ol = ow >> 2;
-        int base = 0;   // uniform over the block
+        int base = 0;   // uniform over the wave, which stops where its held pairs fill up
         for (;;) {
             uint32_t* q = nq[wv];
             int qn = 0, mine = LC_NONE;   // pairs held by the wave; the last one held for this thread
